@@ -98,7 +98,8 @@ typedef struct specext_desc {
   int32_t n_tree;         /* T in [1, SPECEXT_MAX_TREE] */
   int32_t chunk_size;     /* 0 < B <= 2^24; only read when want_scores != 0.  The bf16 matrix-core
                              kernels need B to be a multiple of 32 (and, for head_dim 64, kp_stride_l = 64);
-                             other values take the vector-ALU kernel. */
+                             other multiples of 4 take the matrix-core kernel with fp32 probabilities, as
+                             fp32 inputs do, other values the vector-ALU kernel. */
   int32_t want_scores;    /* != 0: also leave per-chunk partial sums in the workspace */
   int32_t num_splits;     /* pieces the prefix is cut into; 0 = choose automatically */
   float softmax_scale;    /* 0 = 1/sqrt(d) */
@@ -152,7 +153,8 @@ int specext_workspace_init(void* workspace, size_t workspace_bytes, void* stream
  *
  * Pointers must be 16-byte aligned and strides multiples of 8 elements.
  * Arithmetic: logits, softmax statistics and the P V sums are fp32 (P and V enter the
- * matrix cores as bf16).  With bf16 inputs, head_dim 128 and more than 32 rows per KV
+ * matrix cores as bf16; as fp32 with fp32 inputs, and P as an exact sum of three bf16
+ * terms where bf16 inputs take the kernel with fp32 probabilities).  With bf16 inputs, head_dim 128 and more than 32 rows per KV
  * head the per-split partial outputs cross memory as fp16 after a per-row power-of-two
  * rescale (11 bits against the row's largest element, whatever the scale of V); the
  * rescale exponent travels in the split's softmax reference, so the magnitudes of V

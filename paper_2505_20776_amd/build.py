@@ -16,8 +16,9 @@ LIB_PATH = os.path.join(PKG_DIR, "libspecext.so")
 # reductions one canonicalising instruction per operand
 EXTRA_FLAGS = {"prefix_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                "prefix_mfma_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans"],
+               "prefix_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans"],
                "prefill_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-fno-honor-nans"]}
-SOURCES = ["api.hip", "prefix_generic.hip", "prefix_mfma.hip", "prefix_mfma_rows.hip", "tree_merge.hip", "retrieval.hip",
+SOURCES = ["api.hip", "prefix_generic.hip", "prefix_mfma.hip", "prefix_mfma_rows.hip", "prefix_f32.hip", "tree_merge.hip", "retrieval.hip",
            "accept.hip", "materialized.hip", "prefill_rows.hip", "calibrate.hip"]
 
 

@@ -115,13 +115,16 @@ int resolve(const specext_desc* d, AttnParams* p) {
   // head_dim 64 (small draft models): the row-split kernel with two keys per LDS row, which needs the
   // keys of a head contiguous in memory and at least one 64-key tile
   const bool mfma64_ok = mfma_common && p->d == 64 && p->kp_sl == 64 && p->L >= 64;
+  // Everything else of bf16 and all of fp32: the matrix-core kernel with fp32 probabilities, unless the chunks are no
+  // whole numbers of its four-key score blocks or a query or key stride leaves its 32-bit offsets within a tile.
+  const bool f32_ok = (!p->want_scores || p->B % 4 == 0) && !(d->flags & SPECEXT_FLAG_VALU_PREFIX) && p->kp_sl <= (1 << 22);
   if (mfma64_ok) {
     p->use_mfma = 2;
     p->rows_per_group = p->M > 128 ? 256 : 128;
     p->part_f16 = 0;
   } else if (!mfma_ok) {
-    p->use_mfma = 0;
-    p->rows_per_group = 64;
+    p->use_mfma = f32_ok ? 3 : 0;
+    p->rows_per_group = !f32_ok || p->M > 32 ? 64 : p->M > 16 ? 32 : 16;
   } else if (p->M <= 32) {
     p->use_mfma = 1;
     p->rows_per_group = 32;
@@ -130,7 +133,7 @@ int resolve(const specext_desc* d, AttnParams* p) {
     p->rows_per_group = p->M > 128 ? 256 : 128;
     p->part_f16 = 1;
   }
-  p->score_gran = p->use_mfma ? 32 : p->B;
+  p->score_gran = p->use_mfma == 3 ? (p->B % 16 == 0 ? 16 : p->B % 8 == 0 ? 8 : 4) : p->use_mfma ? 32 : p->B;
   p->n_sub = p->want_scores ? (p->L + p->score_gran - 1) / p->score_gran : 0;
 
   // Split the prefix.  Every split but the last holds keys_per_split keys: a
@@ -142,8 +145,11 @@ int resolve(const specext_desc* d, AttnParams* p) {
     p->keys_per_split = 128;
     return SPECEXT_OK;
   }
+  // (the fp32-probability kernel keeps the reference of every score block beside its sum, so a chunk may lie in two splits
+  // and a split is cut at whole stages of its four key groups)
   int64_t unit = p->use_mfma == 1 ? 128 : 64;
-  if (p->want_scores) unit = unit / gcd64(unit, p->B) * p->B;
+  if (p->use_mfma == 3) unit = p->in_dtype == SPECEXT_BF16 ? 128 : 64;     // a stage
+  if (p->want_scores && p->use_mfma != 3) unit = unit / gcd64(unit, p->B) * p->B;
   int want = d->num_splits;
   if (want == 0) {
     // one workgroup per compute unit: splits x KV heads x row groups ~ CU count
@@ -155,7 +161,10 @@ int resolve(const specext_desc* d, AttnParams* p) {
     // add to the merge, fewer leave most compute units idle)
     const int by_256 = static_cast<int>((p->L + 255) / 256), by_128 = static_cast<int>((p->L + 127) / 128);
     const int by_len = by_256 > (by_128 < 16 ? by_128 : 16) ? by_256 : (by_128 < 16 ? by_128 : 16);
-    if (want > by_len) want = by_len;
+    // fp32-probability kernel: its matrix work per key is many times the merge's, so one stage per split is enough
+    const int by_stage = static_cast<int>((p->L + unit - 1) / unit);
+    const int most = p->use_mfma != 3 ? by_len : by_stage < 64 ? by_stage : 64;
+    if (want > most) want = most;
     if (want < 1) want = 1;
   }
   if (want > SPECEXT_MAX_SPLITS) want = SPECEXT_MAX_SPLITS;
@@ -297,6 +306,7 @@ int verify_attn_on(const specext_desc* desc, const void* q, const void* k_prefix
   if (p.S > 0) {
     const hipError_t e = p.use_mfma == 2   ? launch_prefix_mfma_rows(p, s)
                          : p.use_mfma == 1 ? launch_prefix_mfma(p, s)
+                         : p.use_mfma == 3 ? launch_prefix_f32(p, s)
                                            : launch_prefix_generic(p, s);
     if (e != hipSuccess) return SPECEXT_ERR_LAUNCH_FAILED;
   }

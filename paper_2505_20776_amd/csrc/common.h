@@ -54,12 +54,12 @@ struct AttnParams {
   const uint64_t* cookie;   // kWorkspaceCookie once the workspace was initialised; null = do not check (library-owned memory)
   int32_t Hq, Hkv, G, d, L, T, M;
   int32_t B, C, S, keys_per_split, want_scores;
-  int32_t score_gran, n_sub;      // keys per score block (32 on the MFMA path, else B) and their count
-  int32_t use_mfma;               // 0 vector-ALU kernel, 1 matrix-core key-split kernel, 2 matrix-core row-split kernel
+  int32_t score_gran, n_sub;      // keys per score block (32: bf16 matrix-core kernels; 4, 8 or 16: fp32-probability kernel; else B) and their count
+  int32_t use_mfma;               // 0 vector-ALU kernel; matrix cores: 1 key-split, 2 row-split, 3 fp32-probability kernel
   int32_t rows_per_group;         // query rows of one KV head that one workgroup covers
   int32_t part_f16;               // part_o [S][rows][d] holds the unnormalised O as fp16 (1: row-split kernel) or fp32 (0)
   int32_t fused_tail;             // 1: the row-split kernel also runs the tree pass and the merge (no second launch)
-  int32_t head_fastest;           // row-split kernel: grid x = KV head, y = split (else x = split, y = KV head)
+  int32_t head_fastest;           // row-split and fp32-probability kernels: grid x = KV head, y = split (else x = split, y = KV head)
   int32_t spin_limit;             // polls of the arrival counter before a workgroup hands its slice to the last arriver
   int32_t in_dtype, out_dtype;
   float scale_log2;
@@ -98,6 +98,7 @@ hipError_t launch_materialized_scores(const MatParams& mp, int32_t score_row, co
 hipError_t launch_prefix_generic(const AttnParams& p, hipStream_t stream);
 hipError_t launch_prefix_mfma(const AttnParams& p, hipStream_t stream);        // key-split kernel (use_mfma == 1)
 hipError_t launch_prefix_mfma_rows(const AttnParams& p, hipStream_t stream);   // row-split kernel (use_mfma == 2)
+hipError_t launch_prefix_f32(const AttnParams& p, hipStream_t stream);         // fp32-probability kernel (use_mfma == 3)
 hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream);
 // score_row >= 0: that row; -1: every row; row_path != nullptr: the row is read on the device,
 // row_path[*row_count - 1] (row 0 when *row_count <= 0)

@@ -1,0 +1,462 @@
+// Prefix pass of Hybrid Tree Attention (SpecExtend Sec. 3.1) on the gfx950 matrix cores with
+// fp32 probabilities: fp32 inputs, and the bf16 problems that the two bf16 kernels do not take
+// (chunk sizes that are no multiple of 32, prefixes shorter than their key tile, head_dim 64
+// with strided keys), which keep the fp32 arithmetic they always had.
+//
+// What bounds it.  With fp32 inputs both products run on v_mfma_f32_16x16x4_f32, 256 flop per
+// clock and compute unit (157 TFLOP/s, 1/16 of the bf16 rate): a tree of 60 nodes with four
+// heads per group is matrix-bound (0.12 us of K/V traffic per us of matrix work), everything
+// else - softmax, LDS reads, loads - fits beside it.  One thread per query row on the vector
+// ALUs, which this replaces, left three of a compute unit's four SIMDs idle and read every K/V
+// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 29 us
+// (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first tile, 4.3 us, the
+// workgroup's own merge and stores, 4 us, and 20 % of the loop).
+// With bf16 inputs Q K^T is exact in bf16 products, and the probabilities go into P V as three
+// bf16 terms whose sum is the fp32 value (8 + 8 + 8 mantissa bits), so that nothing is rounded
+// and the product runs at a third of the bf16 rate instead of the fp32 one's sixteenth (4109
+// keys, 60 nodes: 6250 us before, 19 us here).
+//
+// Shape.  A workgroup owns 16 * NSUB * RB query rows of one KV head and one split of the keys.
+// Its waves form RB row groups x KG key groups: the key groups take the split's tiles in turns
+// and are merged through LDS at the end, so that few rows (a draft level, a toy) still keep four
+// SIMDs busy and the split count - the partial outputs that cross memory - stays low.
+//   tile    one key group's step: 16 keys (fp32) or 32 keys (bf16), the same bytes
+//   stage   KG tiles, one workgroup barrier; the ring in LDS holds 128 KB of stages (two of
+//           64 KB, four for head_dim 64), requested ahead by direct global->LDS loads
+// Workgroups of 128 rows with two key groups (half as many reads of every key, twice the partial
+// outputs) measured slower: 32 against 29 us (fp32, 2K), 20.0 against 18.7 us (bf16, 4109).
+// Matrix-core mapping, transposed so that a lane owns one query row (l & 15) in both products:
+//   S^T[key][row]   = K Q^T     A = K rows from LDS, B = Q in registers.  The contraction index
+//                               is permuted alike on both sides: a lane quarter (l >> 4) takes
+//                               the 16-byte pieces 4 j + quarter of a row.
+//   O^T[dcol][row] += V^T P^T   B = P^T straight from the S^T accumulators (lane quarter q holds
+//                               keys 4 q .. 4 q + 3), A = V.  fp32: one 16-byte read per key gives
+//                               four consecutive columns, each the operand of its own product.
+//                               bf16: ds_read_b64_tr_b16 as in the other kernels.
+#include "mfma_util.h"
+
+namespace specext {
+namespace {
+
+constexpr int KG = 4;                             // key groups of a workgroup
+constexpr int kRingBytes = 128 * 1024;
+
+template <int D, bool BF16>
+struct Tile {
+  static constexpr int kElem = BF16 ? 2 : 4;
+  static constexpr int kKeys = BF16 ? 32 : 16;
+  static constexpr int kRowBytes = D * kElem;              // 128, 256 or 512
+  static constexpr int kPieces = kRowBytes / 16;           // 16-byte pieces of a row
+  static constexpr int kBytes = kKeys * kRowBytes;         // 8 KB (D = 128) or 4 KB
+  static constexpr int kLoads = kBytes / 1024;             // direct loads of one wave per K or V tile
+  static constexpr int kRowsPerLoad = 1024 / kRowBytes;
+  // 16-byte piece `c` of row `r` sits at piece c ^ k_swz(r) (K) or c ^ v_swz(r) (V) of its LDS row, so that the
+  // operand reads spread over the banks: 16 rows x one piece for K; for a bf16 V 8 rows x 32 bytes (an fp32 V row is
+  // read 256 consecutive bytes at a time and needs none)
+  static __device__ __forceinline__ int k_swz(int r) { return kRowBytes == 128 ? (r >> 1) & 7 : r & 15; }
+  static __device__ __forceinline__ int v_swz(int r) {
+    return !BF16 ? 0 : kRowBytes == 128 ? ((r >> 1) & 3) << 1 : (r & 7) << 1;
+  }
+};
+
+constexpr int stages_of(int stage_bytes) { return kRingBytes / stage_bytes < 4 ? kRingBytes / stage_bytes : 4; }
+
+// value + the value of the lane 16 away (within a pair of 16-lane rows)
+__device__ __forceinline__ float rows16_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float rows16_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int D, bool BF16, int NSUB, int RB, bool SCORES>
+__global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) {
+  using T = Tile<D, BF16>;
+  constexpr int kStageBytes = KG * 2 * T::kBytes;
+  constexpr int kStages = stages_of(kStageBytes);
+  constexpr int kLoadsPerStage = 2 * T::kLoads / RB;       // of one wave
+  constexpr int kSubTiles = T::kKeys / 16;                 // S^T blocks of 16 keys per tile
+  constexpr int kQRegs = BF16 ? D / 32 : D / 16;           // 16-byte pieces of a query row per lane
+  constexpr int kOBlocks = D / 16;                         // 16 x 16 output blocks per 16 rows
+  constexpr int kRows = 16 * NSUB;                         // query rows of a wave
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb = wave % RB;                                // row group
+  const int kg = wave / RB;                                // key group
+  const int li = lane & 15;
+  const int qt = lane >> 4;                                // lane quarter
+
+  const int split = p.head_fastest ? blockIdx.y : blockIdx.x;
+  const int g = p.head_fastest ? blockIdx.x : blockIdx.y;
+  const int row0 = (blockIdx.z * RB + rb) * kRows;
+  const int key_lo = split * p.keys_per_split;
+  const int key_hi = min(p.L, key_lo + p.keys_per_split);
+  const int n_tiles = (key_hi - key_lo + T::kKeys - 1) / T::kKeys;
+  const int n_stages = (n_tiles + KG - 1) / KG;
+  const int my_tiles = (n_tiles - kg + KG - 1) / KG;       // tiles of this key group: one in each of the first stages
+
+  const int64_t key_bytes = p.kp_sl * T::kElem;
+  const unsigned char* kbase = static_cast<const unsigned char*>(p.kp) + static_cast<int64_t>(g) * p.kp_sh * T::kElem;
+  const unsigned char* vbase = static_cast<const unsigned char*>(p.vp) + static_cast<int64_t>(g) * p.kp_sh * T::kElem;
+  const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_void*)lds));
+  const int ld_row = lane / T::kPieces;                    // row within one load
+  const int ld_piece = lane % T::kPieces;
+
+  // this wave's share of the tile of its key group in stage st; keys past the split's end repeat its last one (masked below)
+  auto issue_stage = [&](int st) {
+    if (st >= my_tiles) return;
+    const int key0 = key_lo + (st * KG + kg) * T::kKeys;
+    const int last = key_hi - 1 - key0;
+    const unsigned dst = lds0 + (st % kStages) * kStageBytes + kg * (2 * T::kBytes);
+    const unsigned char* ksrc = kbase + key0 * key_bytes;
+    const unsigned char* vsrc = vbase + key0 * key_bytes;
+#pragma unroll
+    for (int i = 0; i < T::kLoads / RB; ++i) {
+      const int u = rb + i * RB;
+      const int r = u * T::kRowsPerLoad + ld_row;
+      const unsigned off = static_cast<unsigned>(min(r, last)) * static_cast<unsigned>(key_bytes);
+      load_to_lds_16(dst + u * 1024, off + ((ld_piece ^ T::k_swz(r)) << 4), ksrc);
+      load_to_lds_16(dst + T::kBytes + u * 1024, off + ((ld_piece ^ T::v_swz(r)) << 4), vsrc);
+    }
+  };
+  issue_stage(0);
+
+  // queries (B operand of S^T); rows past the last one repeat it and are never stored
+  uintx4 qf[NSUB][kQRegs];
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) {
+    const int m = min(row0 + 16 * s + li, p.M - 1);
+    const int t = m / p.G;
+    const int h = g * p.G + (m - t * p.G);
+    const unsigned char* src = static_cast<const unsigned char*>(p.q) + (t * p.q_st + h * p.q_sh) * T::kElem + 16 * qt;
+#pragma unroll
+    for (int j = 0; j < kQRegs; ++j) qf[s][j] = *reinterpret_cast<const uintx4*>(src + 64 * j);
+  }
+  // All query loads have landed before the loop starts; said through the builtin so that the compiler's own wait
+  // bookkeeping sees it and adds no vmcnt(0) inside the loop, which would wait for the stage just requested
+  // (0x0F70 = vmcnt(0), other counters untouched).
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+  for (int st = 1; st < kStages - 1; ++st) issue_stage(st);
+
+  floatx4 acc[NSUB][kOBlocks];
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+    for (int b = 0; b < kOBlocks; ++b) acc[s][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float ref[NSUB], run_sum[NSUB];      // reference logit (raw units) the exponentials are taken against; lane-partial sum
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) {
+    ref[s] = -INFINITY;
+    run_sum[s] = 0.f;
+  }
+  const float c = p.scale_log2;
+  const float lazy_raw = kLazyLog2 / c;
+  const int gran_log2 = __builtin_ctz(p.score_gran);
+
+  // A tile in three parts: the logits (and the V fragments: all that reads the ring), the softmax, the second product (from
+  // registers).  With every wave in the same order both waves of a SIMD would be in their softmax at the same time and the
+  // matrix pipe idle; so the upper half of a workgroup of eight waves (wave w + 4 shares wave w's SIMD) starts a stage with
+  // the second product of the tile before (bf16 inputs, 4109 keys: 18.7 instead of 19.9 us; fp32 inputs: equal).
+  floatx4 s_acc[NSUB][kSubTiles];      // the tile's logits, then its probabilities
+  bf16x8 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
+  uintx4 vf[kOBlocks];                 // fp32: [key i of the quarter][64-column block]; bf16: [16-column block]
+  auto tile_logits = [&](int st) __attribute__((always_inline)) {
+    const unsigned char* ktile = lds + (st % kStages) * kStageBytes + kg * (2 * T::kBytes);
+    const unsigned char* vtile = ktile + T::kBytes;
+    // all K fragments of the tile are requested before the first product (one at a time, every product would wait for
+    // its own LDS read)
+    uintx4 kf[kSubTiles][kQRegs];
+#pragma unroll
+    for (int u = 0; u < kSubTiles; ++u)
+#pragma unroll
+      for (int j = 0; j < kQRegs; ++j) {
+        const int r = 16 * u + li;
+        kf[u][j] = *reinterpret_cast<const uintx4*>(ktile + r * T::kRowBytes + (((4 * j + qt) ^ T::k_swz(r)) << 4));
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kSubTiles; ++u) {
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) s_acc[s][u] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < kQRegs; ++j) {
+        if constexpr (BF16) {
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s)
+            s_acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[u][j]),
+                                                                  __builtin_bit_cast(bf16x8, qf[s][j]), s_acc[s][u], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s) {
+              const uint32_t kb = kf[u][j][e], qb = qf[s][j][e];
+              s_acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kb), __uint_as_float(qb), s_acc[s][u], 0, 0, 0);
+            }
+        }
+      }
+    }
+    // and the V fragments before the softmax, which hides their reads
+#pragma unroll
+    for (int b = 0; b < kOBlocks; ++b) {
+      if constexpr (BF16) {
+        shortx4 half[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int r = 16 * u + 4 * qt + (li >> 2);
+          const unsigned char* src = vtile + r * T::kRowBytes + (((2 * b + ((li & 3) >> 1)) ^ T::v_swz(r)) << 4) + ((li & 1) << 3);
+          half[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)src);
+        }
+        vf[b] = __builtin_bit_cast(uintx4, __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7));
+      } else {
+        vf[b] = *reinterpret_cast<const uintx4*>(vtile + (4 * qt + b / (D / 64)) * T::kRowBytes + ((16 * (b % (D / 64)) + li) << 4));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // A product's result may be read ten wait states after its issue at the earliest.  The compiler counts them, but where
+    // the branch below follows the last product directly it counts along the branch's long side only and reads too early
+    // on the short one (seen in its output: two states, and the register's previous content in the row maximum), so the
+    // states are spelled out here.
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+      for (int u = 0; u < kSubTiles; ++u) asm volatile("" : "+v"(s_acc[s][u]));
+    asm volatile("s_nop 9");
+  };
+  auto tile_softmax = [&](int st) __attribute__((always_inline)) {
+    // online softmax; lane quarter qt holds keys 16 u + 4 qt + i of the tile
+    const int key0 = key_lo + (st * KG + kg) * T::kKeys;
+    const int left = key_hi - key0;
+    if (left < T::kKeys) {
+#pragma unroll
+      for (int u = 0; u < kSubTiles; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (16 * u + 4 * qt + i >= left) {
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s) s_acc[s][u][i] = -INFINITY;
+          }
+    }
+    float mx[NSUB];
+    bool grow = false;
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) {
+      mx[s] = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < kSubTiles; ++u)
+        mx[s] = fmaxf(mx[s], fmaxf(fmaxf(s_acc[s][u][0], s_acc[s][u][1]), fmaxf(s_acc[s][u][2], s_acc[s][u][3])));
+      grow |= mx[s] > ref[s] + lazy_raw;
+    }
+    if (__any(grow)) {                 // some row of this wave outgrew its reference: move every reference up
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s) {
+        const float new_ref = fmaxf(ref[s], halves_max(rows16_max(mx[s])));
+        const float alpha = fast_exp2((ref[s] - new_ref) * c);     // 0 on the first tile
+        ref[s] = new_ref;
+        run_sum[s] *= alpha;
+#pragma unroll
+        for (int b = 0; b < kOBlocks; ++b) acc[s][b] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) {
+      const float mc = ref[s] * c;
+#pragma unroll
+      for (int u = 0; u < kSubTiles; ++u) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(fmaf(s_acc[s][u][i], c, -mc));
+        float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
+        run_sum[s] += part;
+        if (SCORES) {
+          // one (sum, reference) pair per score_gran keys: 4 (a lane quarter), 8 or 16
+          if (p.score_gran >= 8) part = rows16_sum(part);
+          if (p.score_gran >= 16) part = halves_sum(part);
+          const int key = key0 + 16 * u + 4 * qt;
+          const int m = row0 + 16 * s + li;
+          if (((4 * qt) & (p.score_gran - 1)) == 0 && key < key_hi && m < p.M)
+            *reinterpret_cast<floatx2*>(p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + (key >> gran_log2)) * p.M + m) * 2) =
+                floatx2{part, mc};
+        }
+      }
+    }
+    if constexpr (BF16) {
+      // P as three bf16 terms: the rounded value, the rounded rest and the rest of that (each subtraction is exact)
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float x = s_acc[s][e >> 2][e & 3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const __bf16 b = static_cast<__bf16>(x);
+            pf[s][k][e] = b;
+            x -= static_cast<float>(b);
+          }
+        }
+    }
+  };
+  auto second_product = [&]() __attribute__((always_inline)) {
+    if constexpr (BF16) {
+#pragma unroll
+      for (int b = 0; b < kOBlocks; ++b)
+#pragma unroll
+        for (int k = 2; k >= 0; --k)                        // smallest terms first
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s)
+            acc[s][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[b]), pf[s][k], acc[s][b], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int db = 0; db < D / 64; ++db)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t vb = vf[i * (D / 64) + db][e];
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s)
+              acc[s][4 * db + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vb), s_acc[s][0][i], acc[s][4 * db + e], 0, 0, 0);
+          }
+    }
+  };
+  auto key_loop = [&](auto rotated_c) __attribute__((always_inline)) {
+    constexpr bool kRotated = decltype(rotated_c)::value;
+    for (int st = 0; st < n_stages; ++st) {
+      // this wave's loads of stage st have landed when no more than those of the stages requested behind it are pending
+      // (score stores in between only make the wait longer); its reads of the stage before, whose place is filled next, are done
+      wait_vmcnt_even(kLoadsPerStage * max(0, min(my_tiles - 1 - st, kStages - 2)));
+      if (kRotated) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      lds_barrier();
+      issue_stage(st + kStages - 1);
+      if (kRotated) {
+        if (st > 0 && st <= my_tiles) second_product();
+        if (st < my_tiles) {
+          tile_logits(st);
+          tile_softmax(st);
+        }
+      } else if (st < my_tiles) {
+        tile_logits(st);
+        tile_softmax(st);
+        second_product();
+      }
+    }
+    if (kRotated && my_tiles == n_stages) second_product();
+  };
+  if (RB * KG == 8 && wave >= 4) key_loop(std::integral_constant<bool, true>{});
+  else key_loop(std::integral_constant<bool, false>{});
+
+  // ---- the key groups' partials meet in LDS; key group w finishes the w-th share of the columns and leaves the others ----
+  lds_barrier();                                     // every wave has left the ring
+  constexpr int kShare = kOBlocks / KG;
+  constexpr int kDumpBytes = NSUB * kOBlocks * 1024;       // a wave's O^T, one floatx4 per lane and block
+  float* ml = reinterpret_cast<float*>(lds + RB * KG * kDumpBytes);      // [wave][2][kRows]
+  unsigned char* dump = lds + wave * kDumpBytes + lane * 16;
+  auto columns = [&](int s, int b) {
+    if constexpr (BF16) return acc[s][b];
+    // accumulator 4 db + e holds columns 64 db + 16 qt + 4 i + e: regrouped so that a lane stores consecutive columns
+    return floatx4{acc[s][b & ~3][b & 3], acc[s][(b & ~3) + 1][b & 3], acc[s][(b & ~3) + 2][b & 3], acc[s][(b & ~3) + 3][b & 3]};
+  };
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) {
+    const float sum = halves_sum(rows16_sum(run_sum[s]));
+#pragma unroll
+    for (int b = 0; b < kOBlocks; ++b)
+      if (b / kShare != kg) *reinterpret_cast<floatx4*>(dump + (s * kOBlocks + b) * 1024) = columns(s, b);
+    if (qt == 0) {
+      ml[(wave * 2 + 0) * kRows + 16 * s + li] = ref[s] * c;
+      ml[(wave * 2 + 1) * kRows + 16 * s + li] = sum;
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  lds_barrier();
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s) {
+    const int m = row0 + 16 * s + li;
+    float mw[KG], lw[KG];
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < KG; ++w) {
+      mw[w] = ml[((w * RB + rb) * 2 + 0) * kRows + 16 * s + li];
+      lw[w] = ml[((w * RB + rb) * 2 + 1) * kRows + 16 * s + li];
+      top = fmaxf(top, mw[w]);
+    }
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < KG; ++w) {
+      mw[w] = lw[w] > 0.f ? fast_exp2(mw[w] - top) : 0.f;      // a key group without tiles contributes nothing
+      total = fmaf(lw[w], mw[w], total);
+    }
+    const int64_t slot = static_cast<int64_t>(split) * p.Hq * p.T + g * p.M + m;
+#pragma unroll
+    for (int b = 0; b < kOBlocks; ++b) {
+      if (b / kShare != kg) continue;
+      floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < KG; ++w)                             // in key-group order
+        o += (w == b / kShare ? columns(s, b)
+                              : *reinterpret_cast<const floatx4*>(lds + (w * RB + rb) * kDumpBytes + (s * kOBlocks + b) * 1024 + lane * 16)) *
+             mw[w];
+      const int col = BF16 ? 16 * b + 4 * qt : 64 * (b >> 2) + 16 * qt + 4 * (b & 3);
+      if (m < p.M) *reinterpret_cast<floatx4*>(p.part_o + slot * D + col) = o;
+    }
+    if (kg == 0 && qt == 0 && m < p.M)
+      *reinterpret_cast<floatx2*>(p.part_ml + slot * 2) = floatx2{top, total};
+  }
+}
+
+template <int D, bool BF16, int NSUB, int RB, bool SCORES>
+hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
+  using T = Tile<D, BF16>;
+  constexpr int kWaves = RB * KG;
+  constexpr int kStageBytes = KG * 2 * T::kBytes;
+  constexpr int kRing = stages_of(kStageBytes) * kStageBytes;
+  constexpr int kMergeBytes = kWaves * (NSUB * (D / 16) * 1024 + 2 * 16 * NSUB * 4);
+  constexpr int kLdsBytes = kMergeBytes > kRing ? kMergeBytes : kRing;
+  static_assert(kLdsBytes <= 160 * 1024, "ring and merge area must fit the 160 KB of LDS");
+  auto kernel = prefix_f32_kernel<D, BF16, NSUB, RB, SCORES>;
+  if (kLdsBytes > 64 * 1024) {
+    // more than the default 64 KB of dynamic LDS: raise the cap once per device
+    static std::atomic<bool> attr_set[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!attr_set[dev].load(std::memory_order_acquire)) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+      if (e != hipSuccess) return e;
+      attr_set[dev].store(true, std::memory_order_release);
+    }
+  }
+  const int rows_per_wg = 16 * NSUB * RB;
+  dim3 grid(p.head_fastest ? p.Hkv : p.S, p.head_fastest ? p.S : p.Hkv, (p.M + rows_per_wg - 1) / rows_per_wg);
+  kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(p);
+  return hipGetLastError();
+}
+
+template <int D, bool BF16, int NSUB, int RB>
+hipError_t launch_shape(const AttnParams& p, hipStream_t stream) {
+  return p.want_scores ? launch_one<D, BF16, NSUB, RB, true>(p, stream) : launch_one<D, BF16, NSUB, RB, false>(p, stream);
+}
+
+template <int D, bool BF16>
+hipError_t launch_rows(const AttnParams& p, hipStream_t stream) {
+  switch (p.rows_per_group) {
+    case 16: return launch_shape<D, BF16, 1, 1>(p, stream);
+    case 32: return launch_shape<D, BF16, 2, 1>(p, stream);
+    default: return launch_shape<D, BF16, 2, 2>(p, stream);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_prefix_f32(const AttnParams& p, hipStream_t stream) {
+  if (p.S <= 0) return hipSuccess;
+  const bool bf16 = p.in_dtype == SPECEXT_BF16;
+  if (p.d == 128) return bf16 ? launch_rows<128, true>(p, stream) : launch_rows<128, false>(p, stream);
+  return bf16 ? launch_rows<64, true>(p, stream) : launch_rows<64, false>(p, stream);
+}
+
+}  // namespace specext

@@ -1,8 +1,9 @@
 // Prefix pass of Hybrid Tree Attention (SpecExtend Sec. 3.1), generic kernel.
 //
 // fp32 arithmetic on the vector ALUs for any supported dtype, head_dim and
-// chunk size.  It is the product path for fp32 inputs and for shapes the MFMA
-// kernel does not take.  One thread owns one query row (a tree node of one
+// chunk size: for chunk sizes that are no multiple of four keys, which no matrix-core
+// kernel takes, and as the independent second kernel of cross-checks
+// (SPECEXT_FLAG_VALU_PREFIX).  One thread owns one query row (a tree node of one
 // query head), keeps the query and the running output in registers, and walks
 // its split of the prefix in tiles of 32 keys staged through LDS as fp32.
 // Softmax is the usual online form in base 2; per-chunk sums of the
