@@ -306,7 +306,6 @@ int verify_attn_on(const specext_desc* desc, const void* q, const void* k_prefix
   if (p.S > 0) {
     const hipError_t e = p.use_mfma == 2   ? launch_prefix_mfma_rows(p, s)
                          : p.use_mfma == 1 ? launch_prefix_mfma(p, s)
-                         : p.use_mfma == 3 ? launch_prefix_f32(p, s)
                                            : launch_prefix_generic(p, s);
     if (e != hipSuccess) return SPECEXT_ERR_LAUNCH_FAILED;
   }

@@ -95,10 +95,10 @@ hipError_t launch_prefill_rows(const PrefillParams& p, hipStream_t stream);
 hipError_t launch_materialized(const MatParams& mp, hipStream_t stream);
 hipError_t launch_materialized_scores(const MatParams& mp, int32_t score_row, const int32_t* row_path,
                                       const int32_t* row_count, float* scores, hipStream_t stream);
-hipError_t launch_prefix_generic(const AttnParams& p, hipStream_t stream);
+hipError_t launch_prefix_generic(const AttnParams& p, hipStream_t stream);     // vector-ALU kernel (use_mfma == 0), or (3) the next
+hipError_t launch_prefix_f32(const AttnParams& p, hipStream_t stream);         // fp32-probability kernel
 hipError_t launch_prefix_mfma(const AttnParams& p, hipStream_t stream);        // key-split kernel (use_mfma == 1)
 hipError_t launch_prefix_mfma_rows(const AttnParams& p, hipStream_t stream);   // row-split kernel (use_mfma == 2)
-hipError_t launch_prefix_f32(const AttnParams& p, hipStream_t stream);         // fp32-probability kernel (use_mfma == 3)
 hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream);
 // score_row >= 0: that row; -1: every row; row_path != nullptr: the row is read on the device,
 // row_path[*row_count - 1] (row 0 when *row_count <= 0)

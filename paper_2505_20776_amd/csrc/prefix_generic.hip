@@ -149,6 +149,7 @@ __global__ __launch_bounds__(kRowsPerBlock) void prefix_generic_kernel(AttnParam
 
 hipError_t launch_prefix_generic(const AttnParams& p, hipStream_t stream) {
   if (p.S <= 0) return hipSuccess;
+  if (p.use_mfma == 3) return launch_prefix_f32(p, stream);
   dim3 grid(p.S, p.Hkv, (p.M + kRowsPerBlock - 1) / kRowsPerBlock);
   dim3 block(kRowsPerBlock);
   const bool bf16 = p.in_dtype == SPECEXT_BF16;
