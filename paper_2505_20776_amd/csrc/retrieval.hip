@@ -14,45 +14,85 @@ namespace {
 
 // scores[r][c] = (1/Hq) * sum_h  sum_blocks  blocksum(h, t) * exp2(ref - lse2(h, t)) / |c|
 // The prefix pass leaves one (sum, ref) pair per score block (score_gran keys;
-// a chunk is a whole number of blocks).  A workgroup handles 64 chunks; the heads
-// of a chunk are dealt to four threads (head h goes to thread h mod 4), each adds
-// its heads in ascending order, and the four partial sums are combined in a fixed
+// a chunk is a whole number of blocks).  The heads of a chunk are dealt to the four lanes of a
+// quad (head h to lane h mod 4: with four heads per group a quad's load is 32 consecutive bytes),
+// each adds its heads in ascending order, block by block, and the four sums are combined in a fixed
 // order: a deterministic fp32 sum.
-__global__ __launch_bounds__(256) void chunk_scores_kernel(AttnParams p, int first_row, const int* row_path,
-                                                          const int* row_count, float* scores) {
-  __shared__ float partial[4][64];
-  const int cl = threadIdx.x & 63;
-  const int part = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
-  int t = first_row + blockIdx.y;
-  if (row_path) {                                // the row comes from the acceptance walk: its last accepted node
-    const int cnt = min(*row_count, p.T);            // never past the path array, whatever the count says
-    const int node = cnt > 0 ? row_path[cnt - 1] : 0;
-    t = (node >= 0 && node < p.T) ? node : 0;
-  }
+//
+// What bounds it: every pair group is a 32-byte piece of a line of its own (the pairs of a block are
+// [rows], as the prefix kernels write them), fetched from behind another XCD's L2, so the kernel is one
+// trip to memory if all of a thread's loads are in flight together and enough compute units ask.  Hence
+// one wavefront and 16 chunks per workgroup; 64 chunks per workgroup with a head's loads one after the
+// other took 5.5 us for 512 chunks of one block and 7.9 us for 512 of two (32 heads in 8 groups), this
+// 4.6 us for either.
+constexpr int kScoreChunks = 16;               // chunks per workgroup
+constexpr int kHeadsAtOnce = 8;                // heads of one thread whose loads are in flight together
+
+// the tree row to score: given, or the acceptance walk's last accepted node read on the device
+__device__ __forceinline__ int scored_row(const AttnParams& p, int first_row, const int* row_path, const int* row_count) {
+  if (!row_path) return first_row;
+  const int cnt = min(*row_count, p.T);          // never past the path array, whatever the count says
+  const int node = cnt > 0 ? row_path[cnt - 1] : 0;
+  return (node >= 0 && node < p.T) ? node : 0;
+}
+
+// value of quad lane I in every lane of the quad
+template <int I>
+__device__ __forceinline__ float quad_lane(float v) {
+  return SPECEXT_DPP(v, I * 0x55);
+}
+
+// Sum over the heads `part`, part + 4, ... of one chunk's blocks [sub_lo, sub_hi), at most NSUB of them in flight per head.
+template <int NSUB>
+__device__ __forceinline__ float chunk_head_sum(const AttnParams& p, int t, int part, int sub_lo, int sub_hi) {
   float acc = 0.f;
-  if (c < p.C) {
-    const int per_chunk = p.B / p.score_gran;
-    const int sub_lo = c * per_chunk;
-    const int sub_hi = min(sub_lo + per_chunk, p.n_sub);
-    for (int h = part; h < p.Hq; h += 4) {
+  for (int hb = part; hb < p.Hq; hb += 4 * kHeadsAtOnce) {
+    float l2[kHeadsAtOnce];
+    float2 pair[kHeadsAtOnce][NSUB];
+    const float* src[kHeadsAtOnce];
+#pragma unroll
+    for (int u = 0; u < kHeadsAtOnce; ++u) {
+      const int h = min(hb + 4 * u, p.Hq - 1);                 // heads past the end re-read the last one, unused
       const int g = h / p.G;
       const int m = t * p.G + (h - g * p.G);
-      const float l2 = p.lse2[g * p.M + m];
-      for (int sb = sub_lo; sb < sub_hi; ++sb) {
-        const float2 cp = *reinterpret_cast<const float2*>(
-            p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + sb) * p.M + m) * 2);
-        acc += cp.x * exp2f(cp.y - l2);
+      l2[u] = p.lse2[g * p.M + m];
+      src[u] = p.chunk_part + (static_cast<int64_t>(g) * p.n_sub * p.M + m) * 2;
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b)                            // blocks past the chunk's end re-read its last one, unused
+        pair[u][b] = *reinterpret_cast<const float2*>(src[u] + static_cast<int64_t>(min(sub_lo + b, sub_hi - 1)) * p.M * 2);
+    }
+#pragma unroll
+    for (int u = 0; u < kHeadsAtOnce; ++u) {
+      if (hb + 4 * u < p.Hq) {
+#pragma unroll
+        for (int b = 0; b < NSUB; ++b)
+          if (sub_lo + b < sub_hi) acc += pair[u][b].x * exp2f(pair[u][b].y - l2[u]);
+        for (int sb = sub_lo + NSUB; sb < sub_hi; ++sb) {
+          const float2 cp = *reinterpret_cast<const float2*>(src[u] + static_cast<int64_t>(sb) * p.M * 2);
+          acc += cp.x * exp2f(cp.y - l2[u]);
+        }
       }
     }
   }
-  partial[part][cl] = acc;
-  __syncthreads();
-  if (part == 0 && c < p.C) {
-    const int size = min(p.B, p.L - c * p.B);
-    const float tot = ((partial[0][cl] + partial[1][cl]) + partial[2][cl]) + partial[3][cl];
-    scores[static_cast<int64_t>(blockIdx.y) * p.C + c] = tot / (static_cast<float>(size) * static_cast<float>(p.Hq));
-  }
+  return acc;
+}
+
+__device__ __forceinline__ float chunk_score(const AttnParams& p, int c, float p0, float p1, float p2, float p3) {
+  const int size = min(p.B, p.L - c * p.B);
+  return (((p0 + p1) + p2) + p3) / (static_cast<float>(size) * static_cast<float>(p.Hq));
+}
+
+template <int NSUB>
+__global__ __launch_bounds__(4 * kScoreChunks) void chunk_scores_kernel(AttnParams p, int first_row, const int* row_path,
+                                                                       const int* row_count, float* scores) {
+  const int t = scored_row(p, first_row + blockIdx.y, row_path, row_count);
+  const int c = blockIdx.x * kScoreChunks + (threadIdx.x >> 2);
+  const int part = threadIdx.x & 3;
+  const int per_chunk = p.B / p.score_gran;
+  const int sub_lo = min(c, p.C - 1) * per_chunk;               // chunks past the end re-read the last one, unused
+  const float acc = chunk_head_sum<NSUB>(p, t, part, sub_lo, min(sub_lo + per_chunk, p.n_sub));
+  const float score = chunk_score(p, c, quad_lane<0>(acc), quad_lane<1>(acc), quad_lane<2>(acc), quad_lane<3>(acc));
+  if (part == 0 && c < p.C) scores[static_cast<int64_t>(blockIdx.y) * p.C + c] = score;
 }
 
 // --------------------------------------------------------------------------
@@ -68,16 +108,22 @@ __device__ __forceinline__ uint32_t orderable(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Inclusive prefix sum over the wave, in registers (six data-parallel-primitive steps, no LDS round trips).
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8 within rows of 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Exclusive block prefix sum of one int per thread; returns the block total in `total`.
 __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_sums, int& total) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int n = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += n;
-  }
+  const int incl = wave_inclusive_scan(v);
   __syncthreads();                              // wave_sums may still be read from the previous call
   if (lane == 63) wave_sums[wave] = incl;
   __syncthreads();
@@ -92,7 +138,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_sums, int& 
   return base + incl - v;
 }
 
-// Block-wide count of a predicate (up to kSelPerThread flags per thread, bit u of
+// Block-wide count of a predicate (up to 32 flags per thread, bit u of
 // `flags` = flag u); every thread gets the total.  Wave counts come from ballots;
 // `slots` must hold blockDim.x / 64 ints and alternate between two buffers from
 // call to call so that one barrier per call is enough.
@@ -112,9 +158,7 @@ __device__ __forceinline__ int block_count(unsigned flags, int n_flags, int* slo
 // the top: a bit stays set if at least k keys are >= the candidate.  Scores above V
 // are all taken; of the scores equal to V the lowest-indexed ones fill what is left.
 // A last pass in index order (block scans over the keep flags) writes the output
-// ascending.  Threads hold up to kSelPerThread keys in registers; longer inputs are
-// re-read from memory.
-constexpr int kSelPerThread = 4;
+// ascending.  For inputs that the byte-wise selection does not take; the keys are re-read from memory.
 
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores, int n, int k,
                                                             int* __restrict__ idx_out, int* __restrict__ n_out) {
@@ -128,23 +172,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   if (threadIdx.x < 2 * (kSelThreads / 64)) slots[0][threadIdx.x] = 0;      // slots of absent waves stay zero
   __syncthreads();
 
-  const bool in_regs = n <= kSelThreads * kSelPerThread;
-  uint32_t mine[kSelPerThread];
-#pragma unroll
-  for (int u = 0; u < kSelPerThread; ++u) {
-    const int i = u * kSelThreads + threadIdx.x;
-    mine[u] = (in_regs && i < n) ? orderable(scores[i]) : 0u;       // 0 is below every real key
-  }
-  // how many keys are >= cand (block-wide)
+  // how many keys are >= cand (block-wide), 32 keys per thread per round of ballots
   auto count_ge = [&](uint32_t cand, int* slot) {
-    if (in_regs) {
-      unsigned flags = 0;
-#pragma unroll
-      for (int u = 0; u < kSelPerThread; ++u) flags |= (mine[u] >= cand ? 1u : 0u) << u;
-      const int n_flags = min(kSelPerThread, (n + kSelThreads - 1) / kSelThreads);
-      return block_count(flags, n_flags, slot);
-    }
-    int total = 0;                     // long input: 32 keys per thread per round of ballots
+    int total = 0;
     for (int base = 0; base < n; base += blockDim.x * 32) {
       unsigned flags = 0;
       for (int u = 0; u < 32; ++u) {
@@ -184,33 +214,46 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   }
 }
 
-// Short inputs (n <= kRankMax) get one key per thread and the byte-wise selection below.
+// Inputs of at most kRankMax scores take the byte-wise selection below with one key per thread, those of at most
+// kRadixMax with four (4096 scores of a 128K prefix: 25 us bit by bit as below, 8.2 us so).
 constexpr int kRankMax = 1024;
+constexpr int kRadixMax = 4 * kSelThreads;
+constexpr int kScoreGroupsOneLaunch = 3000;
 
-// One workgroup (blockDim.x a multiple of 64, at least n threads), thread i holding the score
-// of chunk i.  The key of the k-th largest score is found a byte at a time from the top:
+// One workgroup (blockDim.x a multiple of 64), thread i holding the scores of chunks i, i + blockDim.x, ... (KPT of
+// them).  The key of the k-th largest score is found a byte at a time from the top:
 // a 256-bin histogram (LDS atomics) of the keys that match the bytes fixed so far, a
 // suffix scan over the bins, and the bin that holds the k-th key fixes the next byte - four
-// rounds instead of one compare of every key with every other.  Every wave does the scan
+// rounds instead of one compare of every key with every other.  Scores of one row share
+// their leading bits, so the lanes of a wave that hold its first key's bin add as one.  Every wave does the scan
 // for itself (four bins per lane), so a round costs one barrier.  Keys above the threshold
 // are all taken; of the keys equal to it the lowest-indexed ones fill what is left; ballots
 // and one exchange of per-wave counts give the ascending output.
+template <int KPT>
 struct RadixLds {
   __attribute__((aligned(16))) int hist[4][256];     // one histogram per round, all cleared up front
-  int wave_counts[kSelThreads / 64][2];              // per wave: keys above the threshold, keys equal to it
+  int2 wave_counts[KPT * (kSelThreads / 64)];        // per key of a thread and wave: keys above the threshold, equal to it
 };
 
-__device__ __forceinline__ void radix_select_and_write(float score, int n, int k, int* __restrict__ idx_out,
-                                                       int* __restrict__ n_out, RadixLds& sh) {
+template <int KPT>
+__device__ __forceinline__ void radix_select_and_write(const float (&score)[KPT], int n, int k, int* __restrict__ idx_out,
+                                                       int* __restrict__ n_out, RadixLds<KPT>& sh) {
   const int i = threadIdx.x;
   const int lane = i & 63;
-  const int wave = i >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(i >> 6);
+  const int n_waves = blockDim.x >> 6;
+  static_assert(KPT * (kSelThreads / 64) <= 64, "the waves' counts fit one wave");
   const int k_eff = min(k, n);
   if (i == 0) *n_out = k_eff;
   for (int u = k_eff + i; u < k; u += blockDim.x) idx_out[u] = -1;
   if (k_eff == 0) return;
-  const bool live = i < n;
-  const uint32_t key = live ? orderable(score) : 0u;
+  uint32_t key[KPT];
+  bool live[KPT];
+#pragma unroll
+  for (int v = 0; v < KPT; ++v) {
+    live[v] = i + v * static_cast<int>(blockDim.x) < n;
+    key[v] = live[v] ? orderable(score[v]) : 0u;
+  }
   for (int u = i; u < 4 * 256; u += blockDim.x) (&sh.hist[0][0])[u] = 0;
   __syncthreads();
   uint32_t prefix = 0;           // the bytes of the threshold fixed so far (higher bytes first)
@@ -218,20 +261,25 @@ __device__ __forceinline__ void radix_select_and_write(float score, int n, int k
 #pragma unroll
   for (int round = 0; round < 4; ++round) {
     const int shift = 24 - 8 * round;
-    const bool match = live && (round == 0 || (key >> (shift + 8)) == (prefix >> (shift + 8)));
-    if (match) atomicAdd(&sh.hist[round][(key >> shift) & 255u], 1);
+#pragma unroll
+    for (int v = 0; v < KPT; ++v) {
+      const bool match = live[v] && (round == 0 || (key[v] >> (shift + 8)) == (prefix >> (shift + 8)));
+      const uint64_t matching = __ballot(match);
+      if (matching) {
+        const int first = __ffsll(static_cast<long long>(matching)) - 1;
+        const uint32_t bin = (key[v] >> shift) & 255u;
+        const uint32_t first_bin = __builtin_amdgcn_readlane(bin, first);
+        const uint64_t same = __ballot(match && bin == first_bin);
+        if (lane == first) atomicAdd(&sh.hist[round][first_bin], __popcll(same));
+        if (match && bin != first_bin) atomicAdd(&sh.hist[round][bin], 1);
+      }
+    }
     __syncthreads();
     // lane l looks at bins 255 - 4l (first) down to 252 - 4l; `above` = keys in higher bins
     const int4 h = *reinterpret_cast<const int4*>(&sh.hist[round][252 - 4 * lane]);
     const int bins[4] = {h.w, h.z, h.y, h.x};
     const int mine = (h.x + h.y) + (h.z + h.w);
-    int incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
-    int above = incl - mine;
+    int above = wave_inclusive_scan(mine) - mine;
     int bin = -1, left = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -243,114 +291,68 @@ __device__ __forceinline__ void radix_select_and_write(float score, int n, int k
     }
     // exactly one lane found the bin (1 <= need <= number of matching keys)
     const int src = __ffsll(static_cast<long long>(__ballot(bin >= 0))) - 1;
-    prefix |= static_cast<uint32_t>(__shfl(bin, src, 64)) << shift;
-    need = __shfl(left, src, 64);
+    prefix |= static_cast<uint32_t>(__builtin_amdgcn_readlane(bin, src)) << shift;
+    need = __builtin_amdgcn_readlane(left, src);
   }
   // prefix is the k-th largest key; `need` of the keys equal to it are taken, lowest index first
-  const bool greater = live && key > prefix;
-  const bool is_tie = live && key == prefix;
-  const uint64_t bal_greater = __ballot(greater), bal_tie = __ballot(is_tie);
-  if (lane == 0) {
-    sh.wave_counts[wave][0] = __popcll(bal_greater);
-    sh.wave_counts[wave][1] = __popcll(bal_tie);
+#pragma unroll
+  for (int v = 0; v < KPT; ++v) {
+    const uint64_t bal_greater = __ballot(live[v] && key[v] > prefix), bal_tie = __ballot(live[v] && key[v] == prefix);
+    if (lane == 0) sh.wave_counts[v * n_waves + wave] = make_int2(__popcll(bal_greater), __popcll(bal_tie));
   }
   __syncthreads();
-  int ties_before = 0, pos = 0;
-  for (int w = 0; w < wave; ++w) {
-    const int gr = sh.wave_counts[w][0], ti = sh.wave_counts[w][1];
-    pos += gr + min(max(need - ties_before, 0), ti);
-    ties_before += ti;
-  }
+  // lane e of every wave takes the e-th count in index order: ties before it, then outputs before it
+  const int2 count = lane < KPT * n_waves ? sh.wave_counts[lane] : make_int2(0, 0);
+  const int ties_before = wave_inclusive_scan(count.y) - count.y;
+  const int taken = count.x + min(max(need - ties_before, 0), count.y);
+  const int pos_before = wave_inclusive_scan(taken) - taken;
   const uint64_t lower = (uint64_t{1} << lane) - 1;
-  const int tie_rank = ties_before + __popcll(bal_tie & lower);
-  const bool take = greater || (is_tie && tie_rank < need);
-  const uint64_t bal_take = __ballot(take);
-  if (take) idx_out[pos + __popcll(bal_take & lower)] = i;
+#pragma unroll
+  for (int v = 0; v < KPT; ++v) {
+    const bool is_tie = live[v] && key[v] == prefix;
+    const int tie_rank = __builtin_amdgcn_readlane(ties_before, v * n_waves + wave) + __popcll(__ballot(is_tie) & lower);
+    const bool take = (live[v] && key[v] > prefix) || (is_tie && tie_rank < need);
+    const int pos = __builtin_amdgcn_readlane(pos_before, v * n_waves + wave) + __popcll(__ballot(take) & lower);
+    if (take) idx_out[pos] = i + v * static_cast<int>(blockDim.x);
+  }
 }
 
-__global__ __launch_bounds__(kRankMax) void select_short_kernel(const float* __restrict__ scores, int n, int k,
-                                                              int* __restrict__ idx_out, int* __restrict__ n_out) {
-  __shared__ RadixLds radix;
-  const int i = threadIdx.x;
-  radix_select_and_write(i < n ? scores[i] : 0.f, n, k, idx_out, n_out, radix);
+template <int KPT>
+__global__ __launch_bounds__(kSelThreads) void select_radix_kernel(const float* __restrict__ scores, int n, int k,
+                                                                 int* __restrict__ idx_out, int* __restrict__ n_out) {
+  __shared__ RadixLds<KPT> radix;
+  float mine[KPT];
+#pragma unroll
+  for (int v = 0; v < KPT; ++v) {
+    const int i = threadIdx.x + v * blockDim.x;
+    mine[v] = i < n ? scores[i] : 0.f;
+  }
+  radix_select_and_write<KPT>(mine, n, k, idx_out, n_out, radix);
 }
 
 // Chunk scores of one tree row and the top-k over them in one launch (at most kRankMax
-// chunks, 1024 threads).  Scores with the arithmetic of chunk_scores_kernel - the heads of
-// a chunk are dealt to four threads (head h to thread h mod 4), each adds its heads in
-// ascending order, the four sums are combined in the same fixed order: the same bits -
-// a quarter of the threads' number of chunks per pass, all loads of a thread requested
-// before the first is used; then the byte-wise selection above.  scores may be null.
+// chunks, up to 1024 threads), for problems whose pairs one compute unit takes in faster than a second launch
+// costs.  Scores with the arithmetic of chunk_scores_kernel: the same bits.  scores may be null.
 __global__ __launch_bounds__(kRankMax) void score_select_kernel(AttnParams p, int score_row, const int* row_path,
                                                                const int* row_count, int k, float* scores,
                                                                int* __restrict__ idx_out, int* __restrict__ n_out) {
-  __shared__ RadixLds radix;
+  __shared__ RadixLds<1> radix;
   __shared__ float partial[kRankMax][4];
-  int t = score_row;
-  if (row_path) {
-    const int cnt = min(*row_count, p.T);
-    const int node = cnt > 0 ? row_path[cnt - 1] : 0;
-    t = (node >= 0 && node < p.T) ? node : 0;
-  }
+  const int t = scored_row(p, score_row, row_path, row_count);
   const int part = threadIdx.x & 3;
   const int per_chunk = p.B / p.score_gran;
-  constexpr int kHeadsAtOnce = 8;                // heads of one thread whose loads are in flight together
-  constexpr int kChunksAtOnce = 2;               // chunks of one thread, likewise
-  const int chunks_per_pass = blockDim.x / 4;
-  for (int c0 = 0; c0 < p.C; c0 += kChunksAtOnce * chunks_per_pass) {
-    int cs[kChunksAtOnce], sub_lo[kChunksAtOnce], sub_hi[kChunksAtOnce];
-    float acc[kChunksAtOnce];
-#pragma unroll
-    for (int j = 0; j < kChunksAtOnce; ++j) {
-      cs[j] = c0 + j * chunks_per_pass + (threadIdx.x >> 2);
-      const int cl = min(cs[j], p.C - 1);                        // chunks past the end re-read the last one, unused
-      sub_lo[j] = cl * per_chunk;
-      sub_hi[j] = min(sub_lo[j] + per_chunk, p.n_sub);
-      acc[j] = 0.f;
-    }
-    for (int hb = part; hb < p.Hq; hb += 4 * kHeadsAtOnce) {
-      float l2[kHeadsAtOnce];
-      float2 first[kChunksAtOnce][kHeadsAtOnce];
-      const float* src[kChunksAtOnce][kHeadsAtOnce];
-#pragma unroll
-      for (int u = 0; u < kHeadsAtOnce; ++u) {
-        const int h = min(hb + 4 * u, p.Hq - 1);                 // heads past the end re-read the last one, unused
-        const int g = h / p.G;
-        const int m = t * p.G + (h - g * p.G);
-        l2[u] = p.lse2[g * p.M + m];
-#pragma unroll
-        for (int j = 0; j < kChunksAtOnce; ++j) {
-          src[j][u] = p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + sub_lo[j]) * p.M + m) * 2;
-          first[j][u] = *reinterpret_cast<const float2*>(src[j][u]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < kChunksAtOnce; ++j) {
-#pragma unroll
-        for (int u = 0; u < kHeadsAtOnce; ++u) {
-          if (hb + 4 * u < p.Hq) {
-            acc[j] += first[j][u].x * exp2f(first[j][u].y - l2[u]);
-            for (int sb = sub_lo[j] + 1; sb < sub_hi[j]; ++sb) {
-              const float2 cp = *reinterpret_cast<const float2*>(src[j][u] + static_cast<int64_t>(sb - sub_lo[j]) * p.M * 2);
-              acc[j] += cp.x * exp2f(cp.y - l2[u]);
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < kChunksAtOnce; ++j)
-      if (cs[j] < p.C) partial[cs[j]][part] = acc[j];
+  for (int c = threadIdx.x >> 2; c < p.C; c += blockDim.x / 4) {
+    const int sub_lo = c * per_chunk;
+    partial[c][part] = chunk_head_sum<2>(p, t, part, sub_lo, min(sub_lo + per_chunk, p.n_sub));
   }
   __syncthreads();
   const int c = threadIdx.x;
-  float score = 0.f;
+  float score[1] = {0.f};
   if (c < p.C) {
-    const int size = min(p.B, p.L - c * p.B);
-    score = (((partial[c][0] + partial[c][1]) + partial[c][2]) + partial[c][3]) / (static_cast<float>(size) * static_cast<float>(p.Hq));
-    if (scores) scores[c] = score;
+    score[0] = chunk_score(p, c, partial[c][0], partial[c][1], partial[c][2], partial[c][3]);
+    if (scores) scores[c] = score[0];
   }
-  radix_select_and_write(score, p.C, k, idx_out, n_out, radix);
+  radix_select_and_write<1>(score, p.C, k, idx_out, n_out, radix);
 }
 
 // --------------------------------------------------------------------------
@@ -447,8 +449,12 @@ __global__ __launch_bounds__(256) void gather_meta_kernel(const int* __restrict_
 hipError_t launch_chunk_scores(const AttnParams& p, int32_t score_row, const int32_t* row_path,
                                const int32_t* row_count, float* scores, hipStream_t stream) {
   const int rows = (score_row < 0 && !row_path) ? p.T : 1;
-  dim3 grid((p.C + 63) / 64, rows);
-  chunk_scores_kernel<<<grid, dim3(256), 0, stream>>>(p, score_row < 0 ? 0 : score_row, row_path, row_count, scores);
+  const int first = score_row < 0 ? 0 : score_row;
+  dim3 grid((p.C + kScoreChunks - 1) / kScoreChunks, rows), block(4 * kScoreChunks);
+  const int per_chunk = p.B / p.score_gran;
+  if (per_chunk <= 1) chunk_scores_kernel<1><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
+  else if (per_chunk <= 2) chunk_scores_kernel<2><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
+  else chunk_scores_kernel<4><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
   return hipGetLastError();
 }
 
@@ -456,9 +462,15 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
                                const int32_t* row_count, int32_t k, float* scores, int32_t* idx_out, int32_t* n_out,
                                hipStream_t stream) {
   if (p.C > kRankMax) return hipErrorInvalidValue;
-  // at least one thread per chunk (selection), up to eight (scores: two chunks in flight per thread, four threads
-  // per chunk, so that 1024 threads take in 512 chunks in one pass)
-  const int threads = p.C <= 128 ? 256 : p.C <= 256 ? 512 : 1024;
+  // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 3000 on, a launch of its
+  // own for the scores, which every compute unit shares, is the shorter way.  Measured in one launch / in two, without
+  // the 1 - 2 us between two launches: 512 groups 4.6 / 6.0 us, 2056 8.0 / 8.4, 4096 12.0 / 9.1, 8192 13.4 - 16.7 / 9.1.
+  if (scores && static_cast<int64_t>(p.Hkv) * p.n_sub > kScoreGroupsOneLaunch) {
+    const hipError_t e = launch_chunk_scores(p, score_row, row_path, row_count, scores, stream);
+    return e != hipSuccess ? e : launch_select_chunks(scores, p.C, k, idx_out, n_out, stream);
+  }
+  // at least one thread per chunk (selection), up to four (scores: four threads per chunk)
+  const int threads = p.C <= 64 ? 256 : p.C <= 128 ? 512 : 1024;
   score_select_kernel<<<dim3(1), dim3(threads), 0, stream>>>(p, score_row, row_path, row_count, k, scores, idx_out, n_out);
   return hipGetLastError();
 }
@@ -468,7 +480,9 @@ hipError_t launch_select_chunks(const float* scores, int32_t n_chunks, int32_t k
   // a small input needs only as many waves as it has scores (fewer waves, cheaper barriers)
   const int threads = n_chunks >= kSelThreads ? kSelThreads : ((n_chunks + 63) / 64) * 64;
   if (n_chunks <= kRankMax) {
-    select_short_kernel<<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
+    select_radix_kernel<1><<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
+  } else if (n_chunks <= kRadixMax) {
+    select_radix_kernel<4><<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
   } else {
     select_kernel<<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
   }

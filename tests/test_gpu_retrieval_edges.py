@@ -1,0 +1,63 @@
+"""Edges of the score and selection kernels: lengths around one and four keys per thread of the byte-wise selection, all keys
+in one histogram bin, few distinct keys; scores of chunks of one to five blocks with a remainder of heads and chunks, and
+the one-launch form against the two calls on both sides of the line between one launch and two."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from parity_util import check_scores
+from workloads import chain_tree, make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2047, 2048, 3073, 4095, 4096, 4097])
+def test_selection_lengths(n):
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(n)
+    few = rng.integers(0, 3, size=n).astype(np.float32)                     # ties across waves and keys of a thread
+    close = (np.float32(1.0).view(np.uint32) + rng.integers(0, 200, size=n).astype(np.uint32)).view(np.float32)
+    for s in (rng.standard_normal(n).astype(np.float32), few, close, np.full(n, 2.5, np.float32)):
+        for k in (1, 63, n // 3, n - 1, n):
+            sel, n_out, raw = hx.run_select(s, k)
+            assert n_out == k and list(sel) == list(orc.select_chunks(s, k)), f"n={n} k={k}"
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,B", [
+    (6, 3, 500, 32),          # 6 heads: two of four lanes have one head more; 16 chunks
+    (36, 12, 545, 32),        # 36 heads: nine per lane, one past a round of eight; 18 chunks, the last of one token
+    (8, 2, 3000, 96),         # three blocks per chunk
+    (8, 8, 2222, 160),        # five blocks per chunk
+    (32, 32, 3008, 32),       # 32 groups x 94 blocks = 3008: two launches
+    (32, 32, 2976, 32),       # 2976: one
+])
+def test_scores_of_blocks_and_heads(Hq, Hkv, L, B):
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    T, k = 5, 6
+    wl = make_workload("edges", seed=L, dtype="bf16", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, prefix_len=L,
+                       parent=chain_tree(T), chunk_size=B, top_k=k, n_needles=0, value_std=1.0)
+    print(f"[case] scores Hq={Hq} Hkv={Hkv} L={L} B={B}", flush=True)
+    ref = orc.chunk_scores(wl.q, wl.k_prefix, wl.v_prefix, wl.k_tree, wl.v_tree, wl.parent, B)
+    t = [hx.to_device(a, "bf16") for a in (wl.q, wl.k_prefix, wl.v_prefix, wl.k_tree, wl.v_tree)]
+    buf = hx.make_buffers(dtype="bf16", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, prefix_len=L, n_tree=T, chunk_size=B,
+                          want_scores=True)
+    sx.verify_attn(buf.desc, *t, torch.from_numpy(wl.parent).cuda(), buf.out, buf.lse, buf.workspace)
+    sx.chunk_scores(buf.desc, buf.workspace, -1, buf.scores)
+    C = ref.shape[1]
+    path = torch.tensor([0, 3, -1, -1, -1], dtype=torch.int32, device="cuda")
+    for row, with_scores in ((4, True), (2, False), (3, True)):
+        idx, n_out = torch.empty(k, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+        sc, base = hx.guarded((C,), torch.float32)
+        walk = dict(path=path, n_accept=torch.tensor([2], dtype=torch.int32, device="cuda")) if row == 3 else {}
+        sx.chunk_scores_select(buf.desc, buf.workspace, 0 if walk else row, k, idx, n_out, scores=sc if with_scores else None,
+                               **walk)
+        torch.cuda.synchronize()
+        assert hx.guards_intact(base)
+        got = buf.scores[row].cpu().numpy()
+        if with_scores:
+            assert (sc.cpu().numpy() == got).all()                       # the same bits as the call on its own
+        assert int(n_out) == k and list(idx.cpu().numpy()) == list(orc.select_chunks(got, k))
+    buf.check_guards()
+    check_scores(buf.scores.cpu().numpy(), ref, "all rows")
