@@ -1,0 +1,43 @@
+"""Commit of accepted rows at the edges of its work split: more rows than one pass of a workgroup covers (256 threads, K and
+V pieces of 16 bytes), rows of other sizes, a count beyond the launch bound, nodes outside the tree, strided caches."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("layers,heads,T,d,elem,n", [
+    (2, 3, 128, 128, 2, 128),     # 16 passes
+    (1, 1, 9, 128, 2, 9),         # 8 rows in the first pass, one left
+    (3, 2, 8, 64, 4, 8),          # exactly one pass
+    (1, 2, 20, 24, 2, 17),        # rows of 48 bytes: three pieces
+    (1, 2, 5, 128, 4, 0),         # nothing accepted
+])
+def test_commit_passes(layers, heads, T, d, elem, n):
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(T * 10 + d)
+    L, cap = 37, 37 + T
+    dt = {2: torch.int16, 4: torch.int32}[elem]
+    npdt = {2: np.int16, 4: np.int32}[elem]
+    mk = lambda *s: rng.integers(-2 ** 15, 2 ** 15, size=s).astype(npdt)
+    kt, vt, kc, vc = mk(layers, heads, T, d), mk(layers, heads, T, d), mk(layers, heads, cap, d), mk(layers, heads, cap, d)
+    path = rng.permutation(T)[:n].astype(np.int32)
+    raw = np.full(T, -1, np.int32)
+    raw[:n] = path
+    k_dev, k_base = hx.guarded(kc.shape, dt)
+    v_dev, v_base = hx.guarded(vc.shape, dt)
+    k_dev.copy_(torch.from_numpy(kc))
+    v_dev.copy_(torch.from_numpy(vc))
+    to = lambda a: torch.from_numpy(a).cuda()
+    # the count may say more than the bound allows; entries outside the tree are skipped
+    sx.commit_tree_kv(to(kt), to(vt), k_dev, v_dev, to(raw), to(np.array([n if n < T else T + 50], np.int32)), T, T, layers,
+                      heads, d, elem, L, cap)
+    torch.cuda.synchronize()
+    assert hx.guards_intact(k_base) and hx.guards_intact(v_base)
+    for y in range(layers):
+        rk, rv, _ = orc.commit_tree_kv(kc[y], vc[y], kt[y], vt[y], [int(x) for x in path], L)
+        assert (k_dev[y].cpu().numpy() == rk).all() and (v_dev[y].cpu().numpy() == rv).all()
