@@ -353,8 +353,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void tree_merge_kernel(AttnPar
 
 
 // ---------------------------------------------------------------------------------------
-// The same result for the hot configuration (head_dim 128, bf16 inputs, fp16 partials,
-// at most 64 splits), with the work of four rows shared by four wavefronts.
+// The same result for one to 64 splits, with the work of four rows shared by four wavefronts.
 //
 // The kernel above gives a row's whole merge to sixteen lanes of one wave: the launch then
 // has fewer waves than the chip has SIMDs, every wave runs alone on its SIMD and the
@@ -364,13 +363,47 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void tree_merge_kernel(AttnPar
 // chain.  A wave reduces its items to a partial (max, sum, output) in the usual way, the four
 // partials meet in LDS, and wave w finishes row w.  Per wave the instruction stream is a
 // quarter as long and two waves share a SIMD, so issue time no longer bounds the kernel.
+// With fp32 partials (fewer rows, fp32 inputs, head_dim 64) the rows are too few for a wave per four of them to occupy the
+// chip, and a whole attention call is shorter by 0.3 - 0.7 us: 11.7 -> 11.0 us for 8 nodes of 32 heads over 16 splits
+// (bf16), 41.0 -> 40.3 and 48.5 -> 48.2 us for an iteration of 60 nodes with chunks of 16 and with fp32 inputs.
 // Every sum keeps a fixed order: bit-reproducible from run to run.
 constexpr int kShareWaves = 4;               // 8 measured no faster
-constexpr int kShareSlot = 132;               // floats per (wave, row) slot: 128 outputs, max, sum, padding
 
-template <int PER>
+typedef uint32_t uintx8 __attribute__((ext_vector_type(8)));
+template <int N> struct WordsOf;
+template <> struct WordsOf<2> { using type = uintx2; };
+template <> struct WordsOf<4> { using type = uintx4; };
+template <> struct WordsOf<8> { using type = uintx8; };
+// N consecutive words from a pointer aligned to 8 (N = 2) or 16 bytes
+template <int N, bool STREAM>
+__device__ __forceinline__ typename WordsOf<N>::type load_words(const uint32_t* src) {
+  if constexpr (N == 8) {
+    const uintx4 lo = load_words<4, STREAM>(src), hi = load_words<4, STREAM>(src + 4);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  } else {
+    using W = typename WordsOf<N>::type;
+    if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const W*>(src));
+    else return *reinterpret_cast<const W*>(src);
+  }
+}
+
+// element E of a lane's part of a K or V row
+template <bool BF16, class W>
+__device__ __forceinline__ float row_element(const W& w, int e) {
+  const uint32_t word = w[BF16 ? e / 2 : e];
+  return __uint_as_float(!BF16 ? word : e & 1 ? word & 0xffff0000u : word << 16);
+}
+
+template <int D, bool IN_BF16, bool PART_F16, int PER>
 __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(AttnParams p) {
-  constexpr int D = 128, E = 8;
+  constexpr int E = D / 16;                      // elements per lane: 8 or 4
+  constexpr int PW = PART_F16 ? E / 2 : E;       // 32-bit words a lane holds per partial
+  constexpr int RW = IN_BF16 ? E / 2 : E;        // and per K or V row
+  constexpr int kShareSlot = D + 4;              // floats per (wave, row) slot: outputs, max, sum, padding
+  constexpr int kInBytes = IN_BF16 ? 2 : 4;
+  using PartWords = typename WordsOf<PW>::type;
+  using RowWords = typename WordsOf<RW>::type;
+  static_assert(!PART_F16 || D == 128, "fp16 partials are written for head_dim 128 only");
   constexpr int kThreads = kShareWaves * 64;
   static_assert(SPECEXT_MAX_TREE <= kThreads, "one parent entry per thread");
   static_assert(PER >= 1 && PER <= 16, "a group of 16 lanes holds one (max, sum) pair per lane");
@@ -411,16 +444,16 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
       p.part_ml + (static_cast<int64_t>(min(s_lo + li, s_last)) * n_rows + row) * 2));
   float2 ml = make_float2(ml_raw[0], ml_raw[1]);
   const bool ml_valid = li < PER && s_lo + li <= s_last;
-  const int64_t split_words = static_cast<int64_t>(n_rows) * D / 2;
-  const uint32_t* po = reinterpret_cast<const uint32_t*>(p.part_o) + (static_cast<int64_t>(row) * D + li * E) / 2;
-  uintx4 raw[PER];
+  const int64_t split_words = static_cast<int64_t>(n_rows) * (16 * PW);
+  const uint32_t* po = reinterpret_cast<const uint32_t*>(p.part_o) + static_cast<int64_t>(row) * (16 * PW) + li * PW;
+  PartWords raw[PER];
   // (streaming loads: partial lines left behind in the L2s would be hit by the next launch's partial stores, which
   // costs that launch 1.3 - 2 us at prefixes of 2K - 4K tokens, whose K/V stream is too short to evict them first)
   constexpr int kFirst = PER >= 4 ? PER / 2 : PER;      // partials requested before the tree K/V rows
 #pragma unroll
-  for (int u = 0; u < kFirst; ++u) raw[u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4*>(po + min(s_lo + u, s_last) * split_words));
+  for (int u = 0; u < kFirst; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
   float q[E];
-  load_row_part<E, true>(p.q, t * p.q_st + h * p.q_sh + li * E, q);
+  load_row_part<E, IN_BF16>(p.q, t * p.q_st + h * p.q_sh + li * E, q);
 
   {
     bool bad = false;
@@ -450,7 +483,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
   constexpr int kAnc = 8 / kShareWaves;
   int a = t;
   int anc[kAnc];
-  uintx4 kraw[kAnc], vraw[kAnc];
+  RowWords kraw[kAnc], vraw[kAnc];
   auto request_batch = [&]() {
 #pragma unroll
     for (int u = 0; u < kAnc; ++u) {
@@ -466,14 +499,14 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #pragma unroll
     for (int u = 0; u < kAnc; ++u) {
       const int64_t off = g * p.kt_sh + max(anc[u], 0) * p.kt_st + li * E;
-      kraw[u] = *reinterpret_cast<const uintx4*>(static_cast<const uint16_t*>(p.kt) + off);
-      vraw[u] = *reinterpret_cast<const uintx4*>(static_cast<const uint16_t*>(p.vt) + off);
+      kraw[u] = load_words<RW, false>(reinterpret_cast<const uint32_t*>(static_cast<const unsigned char*>(p.kt) + off * kInBytes));
+      vraw[u] = load_words<RW, false>(reinterpret_cast<const uint32_t*>(static_cast<const unsigned char*>(p.vt) + off * kInBytes));
     }
   };
   request_batch();
   // the rest of the partials goes behind the K/V rows, which would otherwise queue behind all of them
 #pragma unroll
-  for (int u = kFirst; u < PER; ++u) raw[u] = __builtin_nontemporal_load(reinterpret_cast<const uintx4*>(po + min(s_lo + u, s_last) * split_words));
+  for (int u = kFirst; u < PER; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
 
 #ifdef SPECEXT_TAIL_STAMPS
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kAnc + PER - kFirst) : "memory");      // the loads requested up front
@@ -496,11 +529,15 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
   for (int u = 0; u < PER; ++u) {
     const float w = lane_read(wgt, grp0 + u);
 #pragma unroll
-    for (int e = 0; e < E / 2; ++e) {
+    for (int e = 0; e < PW; ++e) {
       const uint32_t word = raw[u][e];
-      const halfx2 hh = __builtin_bit_cast(halfx2, word);
-      o[2 * e] = fmaf(static_cast<float>(hh[0]), w, o[2 * e]);
-      o[2 * e + 1] = fmaf(static_cast<float>(hh[1]), w, o[2 * e + 1]);
+      if constexpr (PART_F16) {
+        const halfx2 hh = __builtin_bit_cast(halfx2, word);
+        o[2 * e] = fmaf(static_cast<float>(hh[0]), w, o[2 * e]);
+        o[2 * e + 1] = fmaf(static_cast<float>(hh[1]), w, o[2 * e + 1]);
+      } else {
+        o[e] = fmaf(__uint_as_float(word), w, o[e]);
+      }
     }
   }
 
@@ -511,11 +548,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
     for (int u = 0; u < kAnc; ++u) {
       float dot = 0.f;
 #pragma unroll
-      for (int e = 0; e < E / 2; ++e) {
-        const uint32_t word = kraw[u][e];
-        dot = fmaf(q[2 * e], __uint_as_float(word << 16), dot);
-        dot = fmaf(q[2 * e + 1], __uint_as_float(word & 0xffff0000u), dot);
-      }
+      for (int e = 0; e < E; ++e) dot = fmaf(q[e], row_element<IN_BF16>(kraw[u], e), dot);
       dot = row16_sum(dot);
       sc[u] = anc[u] >= 0 ? dot : -INFINITY;
     }
@@ -533,22 +566,18 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
     for (int u = 0; u < kAnc; ++u) {
       const float pr = anc[u] >= 0 ? fast_exp2(sc[u] - new_max) : 0.f;
 #pragma unroll
-      for (int e = 0; e < E / 2; ++e) {
-        const uint32_t word = vraw[u][e];
-        o[2 * e] = fmaf(pr, __uint_as_float(word << 16), o[2 * e]);
-        o[2 * e + 1] = fmaf(pr, __uint_as_float(word & 0xffff0000u), o[2 * e + 1]);
-      }
+      for (int e = 0; e < E; ++e) o[e] = fmaf(pr, row_element<IN_BF16>(vraw[u], e), o[e]);
       run_sum += pr;
     }
     if (!__any(a >= 0)) break;
     request_batch();
   }
 
-  // the wave's partial goes to LDS; wave w then finishes row w, two output elements per lane
+  // the wave's partial goes to LDS; wave w then finishes row w, one or two output elements per lane
   {
     float* slot = &slots[wave][rg][0];
-    *reinterpret_cast<float4*>(slot + li * E) = make_float4(o[0], o[1], o[2], o[3]);
-    *reinterpret_cast<float4*>(slot + li * E + 4) = make_float4(o[4], o[5], o[6], o[7]);
+#pragma unroll
+    for (int e = 0; e < E; e += 4) *reinterpret_cast<float4*>(slot + li * E + e) = make_float4(o[e], o[e + 1], o[e + 2], o[e + 3]);
     if (li == 0) *reinterpret_cast<float2*>(slot + D) = make_float2(run_max, run_sum);
   }
   __syncthreads();
@@ -561,27 +590,34 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #pragma unroll
   for (int w = 1; w < kShareWaves; ++w) top = fmaxf(top, st[w].x);     // finite: wave 0 holds the node itself
   float total = 0.f;
-  float2 acc = make_float2(0.f, 0.f);
+  constexpr int C = D / 64;                      // columns per lane
+  float acc[C];
+#pragma unroll
+  for (int e = 0; e < C; ++e) acc[e] = 0.f;
 #pragma unroll
   for (int w = 0; w < kShareWaves; ++w) {
     const float wt = st[w].y > 0.f ? fast_exp2(st[w].x - top) : 0.f;
     total = fmaf(st[w].y, wt, total);
-    const float2 v = *reinterpret_cast<const float2*>(&slots[w][wave][lane * 2]);
-    acc.x = fmaf(v.x, wt, acc.x);
-    acc.y = fmaf(v.y, wt, acc.y);
+#pragma unroll
+    for (int e = 0; e < C; ++e) acc[e] = fmaf(slots[w][wave][lane * C + e], wt, acc[e]);
   }
   const float inv = 1.f / total;
   const int fg = static_cast<int>((static_cast<float>(frow) + 0.5f) * (1.0f / static_cast<float>(p.M)));
   const int fm = frow - fg * p.M;
   const int ft = static_cast<int>((static_cast<float>(fm) + 0.5f) * (1.0f / static_cast<float>(p.G)));
   const int fh = fg * p.G + (fm - ft * p.G);
-  const int64_t ooff = ft * p.o_st + fh * p.o_sh + lane * 2;
+  const int64_t ooff = ft * p.o_st + fh * p.o_sh + lane * C;
   if (p.out_dtype == SPECEXT_BF16) {
-    *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(p.out) + ooff) =
-        static_cast<uint32_t>(float_to_bf16_bits(acc.x * inv)) |
-        (static_cast<uint32_t>(float_to_bf16_bits(acc.y * inv)) << 16);
+    uint16_t* dst = static_cast<uint16_t*>(p.out) + ooff;
+    if constexpr (C == 2)
+      *reinterpret_cast<uint32_t*>(dst) = static_cast<uint32_t>(float_to_bf16_bits(acc[0] * inv)) |
+                                          (static_cast<uint32_t>(float_to_bf16_bits(acc[1] * inv)) << 16);
+    else
+      *dst = static_cast<uint16_t>(float_to_bf16_bits(acc[0] * inv));
   } else {
-    *reinterpret_cast<float2*>(static_cast<float*>(p.out) + ooff) = make_float2(acc.x * inv, acc.y * inv);
+    float* dst = static_cast<float*>(p.out) + ooff;
+    if constexpr (C == 2) *reinterpret_cast<float2*>(dst) = make_float2(acc[0] * inv, acc[1] * inv);
+    else *dst = acc[0] * inv;
   }
   if (lane == 0) {
     const float l2 = top + log2f(total);
@@ -602,6 +638,17 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #endif
 }
 
+template <int D, bool IN_BF16, bool PART_F16>
+void launch_shared(const AttnParams& p, dim3 grid, hipStream_t stream) {
+  const dim3 block(kShareWaves * 64);
+  const int per = (p.S + kShareWaves - 1) / kShareWaves;       // splits per wave, rounded up to a power of two
+  if (per <= 1) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 1><<<grid, block, 0, stream>>>(p);
+  else if (per <= 2) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 2><<<grid, block, 0, stream>>>(p);
+  else if (per <= 4) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 4><<<grid, block, 0, stream>>>(p);
+  else if (per <= 8) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 8><<<grid, block, 0, stream>>>(p);
+  else tree_merge_shared_kernel<D, IN_BF16, PART_F16, 16><<<grid, block, 0, stream>>>(p);
+}
+
 }  // namespace
 
 hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream) {
@@ -612,14 +659,12 @@ hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream) {
   if (p.part_f16 && !(p.d == 128 && bf16)) return hipErrorInvalidValue;
   const bool pre = p.S > 0;
 #ifndef SPECEXT_MERGE_ONE_WAVE_PER_ROWS
-  if (p.part_f16 && p.S >= 1 && p.S <= 16 * kShareWaves) {
-    dim3 shared_block(kShareWaves * 64);
-    const int per = (p.S + kShareWaves - 1) / kShareWaves;       // splits per wave, rounded up to a power of two
-    if (per <= 1) tree_merge_shared_kernel<1><<<grid, shared_block, 0, stream>>>(p);
-    else if (per <= 2) tree_merge_shared_kernel<2><<<grid, shared_block, 0, stream>>>(p);
-    else if (per <= 4) tree_merge_shared_kernel<4><<<grid, shared_block, 0, stream>>>(p);
-    else if (per <= 8) tree_merge_shared_kernel<8><<<grid, shared_block, 0, stream>>>(p);
-    else tree_merge_shared_kernel<16><<<grid, shared_block, 0, stream>>>(p);
+  if (p.S >= 1 && p.S <= 16 * kShareWaves) {
+    if (p.part_f16) launch_shared<128, true, true>(p, grid, stream);
+    else if (p.d == 128 && bf16) launch_shared<128, true, false>(p, grid, stream);
+    else if (p.d == 128) launch_shared<128, false, false>(p, grid, stream);
+    else if (bf16) launch_shared<64, true, false>(p, grid, stream);
+    else launch_shared<64, false, false>(p, grid, stream);
     return hipGetLastError();
   }
 #endif
