@@ -43,19 +43,23 @@ __global__ __launch_bounds__(64) void accept_greedy_kernel(const int* __restrict
   }
 }
 
-// grid (layers * KV heads): a workgroup copies the accepted rows of K and of V of one (layer, head), 16 bytes per
-// thread and step, a row of 256 bytes by 16 threads.  What bounds it is the launch and two trips to memory (the
+// grid (layers * KV heads, shares): the workgroups of one (layer, head) copy its accepted rows of K and of V, 16 bytes per
+// thread and pass, a row of 256 bytes by 16 threads.  What bounds it is the launch and two trips to memory (the
 // accepted count and path, then the rows): so the count and the thread's first path entry are requested together, and
 // there is no workgroup per row that may be accepted - 60-node tree, 32 layers of 8 heads: 30720 workgroups, nearly all of
-// which found nothing to do, took 8.5 us, these 256 take 2.8 us.
+// which found nothing to do, took 8.1 us, these 512 take 2.1 us.  Few rows are accepted as a rule and one share would do; of
+// a long accepted chain it takes a pass after the other, hence several shares where the heads leave compute units
+// idle: 128 of 128 rows, one layer of 8 heads 7.4 us with one share, 2.1 us with sixteen; 60 of 60 rows, 32 layers
+// 5.5 us with one, 4.3 us with two.
 constexpr int kCommitThreads = 256;
+constexpr int kCommitBlocks = 512;               // two per compute unit; beyond, the empty ones cost time
 __global__ __launch_bounds__(kCommitThreads) void commit_tree_kv_kernel(
     const uint4* __restrict__ k_tree, const uint4* __restrict__ v_tree, uint4* __restrict__ k_cache,
     uint4* __restrict__ v_cache, const int* __restrict__ path, const int* __restrict__ n_accept, int max_accept, int n_tree,
     int n_kv_heads, int prefix_len, int row_vecs, int64_t tree_sl, int64_t tree_sh, int64_t tree_st, int64_t cache_sy,
     int64_t cache_sh, int64_t cache_sl) {
   // item = (row, K or V, 16-byte piece), K and V of a row next to each other
-  int item = threadIdx.x;
+  int item = blockIdx.y * kCommitThreads + threadIdx.x;
   int row = item / (2 * row_vecs);
   int node = path[min(row, max_accept - 1)];
   const int n = min(max(*n_accept, 0), max_accept);
@@ -72,7 +76,7 @@ __global__ __launch_bounds__(kCommitThreads) void commit_tree_kv_kernel(
       uint4* dst = (is_v ? v_cache : k_cache) + dst0 + row * cache_sl;
       dst[piece] = src[piece];
     }
-    item += kCommitThreads;
+    item += gridDim.y * kCommitThreads;
     row = item / (2 * row_vecs);
     if (row < n) node = path[row];
   }
@@ -95,7 +99,13 @@ hipError_t launch_commit_tree_kv(const void* k_tree, const void* v_tree, void* k
                                  int64_t cache_sy_bytes, int64_t cache_sh_bytes, int64_t cache_sl_bytes,
                                  hipStream_t stream) {
   if (max_accept <= 0) return hipSuccess;
-  commit_tree_kv_kernel<<<dim3(n_layers * n_kv_heads), dim3(kCommitThreads), 0, stream>>>(
+  // several workgroups per (layer, head) while they are no more than kCommitBlocks in all and have a pass each
+  const int64_t heads = static_cast<int64_t>(n_layers) * n_kv_heads;
+  const int64_t passes = (static_cast<int64_t>(max_accept) * 2 * (row_bytes / 16) + kCommitThreads - 1) / kCommitThreads;
+  int64_t share = heads < kCommitBlocks ? kCommitBlocks / heads : 1;
+  if (share > passes) share = passes;
+  if (share < 1) share = 1;
+  commit_tree_kv_kernel<<<dim3(static_cast<unsigned>(heads), static_cast<unsigned>(share)), dim3(kCommitThreads), 0, stream>>>(
       static_cast<const uint4*>(k_tree), static_cast<const uint4*>(v_tree), static_cast<uint4*>(k_cache),
       static_cast<uint4*>(v_cache), path, n_accept, max_accept, n_tree, n_kv_heads, prefix_len, row_bytes / 16,
       tree_sl_bytes / 16, tree_sh_bytes / 16, tree_st_bytes / 16, cache_sy_bytes / 16, cache_sh_bytes / 16,
