@@ -287,9 +287,10 @@ int specext_accept_greedy(const int32_t* parent, const int32_t* draft_token, con
  *   k_tree, v_tree    [n_layers, n_kv_heads, n_tree, head_dim] elements of elem_bytes
  *                     (the tree K/V that the layers' specext_verify_attn calls were given)
  *   k_cache, v_cache  [n_layers, n_kv_heads, cache_capacity, head_dim]
- *   path, n_accept    as written by specext_accept_greedy (device); entries outside
+ *   path, n_accept    as written by specext_accept_greedy (device): path holds
+ *                     min(n_tree, max_accept) entries at least; entries outside
  *                     [0, n_tree) are skipped, n_accept is clamped to max_accept
- *   max_accept        launch bound on the accepted length (<= 128);
+ *   max_accept        launch bound on the accepted length (<= 128; may exceed n_tree);
  *                     prefix_len + max_accept must not exceed cache_capacity
  *   *_stride_*        in elements; 0 = contiguous in the shapes above (separate
  *                     per-layer allocations: one call per layer with n_layers = 1)

@@ -1,6 +1,7 @@
 // What follows the attention in one verification step (SpecExtend Alg. 1): the
 // Verify / Correct loop at temperature 0 walked down the draft tree, and the commit of
 // the accepted tree tokens' K/V rows into the target cache.
+#include "commit_rows.h"
 #include "common.h"
 
 namespace specext {
@@ -51,35 +52,14 @@ __global__ __launch_bounds__(64) void accept_greedy_kernel(const int* __restrict
 // a long accepted chain it takes a pass after the other, hence several shares where the heads leave compute units
 // idle: 128 of 128 rows, one layer of 8 heads 7.4 us with one share, 2.1 us with sixteen; 60 of 60 rows, 32 layers
 // 5.5 us with one, 4.3 us with two.
-constexpr int kCommitThreads = 256;
 constexpr int kCommitBlocks = 512;               // two per compute unit; beyond, the empty ones cost time
 __global__ __launch_bounds__(kCommitThreads) void commit_tree_kv_kernel(
     const uint4* __restrict__ k_tree, const uint4* __restrict__ v_tree, uint4* __restrict__ k_cache,
     uint4* __restrict__ v_cache, const int* __restrict__ path, const int* __restrict__ n_accept, int max_accept, int n_tree,
     int n_kv_heads, int prefix_len, int row_vecs, int64_t tree_sl, int64_t tree_sh, int64_t tree_st, int64_t cache_sy,
     int64_t cache_sh, int64_t cache_sl) {
-  // item = (row, K or V, 16-byte piece), K and V of a row next to each other
-  int item = blockIdx.y * kCommitThreads + threadIdx.x;
-  int row = item / (2 * row_vecs);
-  int node = path[min(row, max_accept - 1)];
-  const int n = min(max(*n_accept, 0), max_accept);
-  const int layer = blockIdx.x / n_kv_heads;
-  const int g = blockIdx.x - layer * n_kv_heads;
-  const int64_t src0 = layer * tree_sl + g * tree_sh;
-  const int64_t dst0 = layer * cache_sy + g * cache_sh + static_cast<int64_t>(prefix_len) * cache_sl;
-  while (row < n) {
-    if (node >= 0 && node < n_tree) {
-      int piece = item - row * (2 * row_vecs);
-      const bool is_v = piece >= row_vecs;
-      if (is_v) piece -= row_vecs;
-      const uint4* src = (is_v ? v_tree : k_tree) + src0 + node * tree_st;
-      uint4* dst = (is_v ? v_cache : k_cache) + dst0 + row * cache_sl;
-      dst[piece] = src[piece];
-    }
-    item += gridDim.y * kCommitThreads;
-    row = item / (2 * row_vecs);
-    if (row < n) node = path[row];
-  }
+  commit_rows(k_tree, v_tree, k_cache, v_cache, path, n_accept, max_accept, n_tree, n_kv_heads, prefix_len, row_vecs, tree_sl,
+              tree_sh, tree_st, cache_sy, cache_sh, cache_sl, threadIdx.x, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
 }  // namespace

@@ -41,3 +41,32 @@ def test_commit_passes(layers, heads, T, d, elem, n):
     for y in range(layers):
         rk, rv, _ = orc.commit_tree_kv(kc[y], vc[y], kt[y], vt[y], [int(x) for x in path], L)
         assert (k_dev[y].cpu().numpy() == rk).all() and (v_dev[y].cpu().numpy() == rv).all()
+
+
+@pytest.mark.parametrize("layers,heads,T,bound,n", [
+    (1, 2, 8, 128, 5),            # a fixed launch bound behind a small tree: the path has 8 entries
+    (1, 1, 4, 128, 4),
+    (32, 32, 4, 64, 3),           # one workgroup per head
+    (1, 2, 5, 6, 0),
+])
+def test_launch_bound_beyond_the_tree(layers, heads, T, bound, n):
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(T + bound)
+    L, cap, d = 11, 11 + bound, 64
+    mk = lambda *s: rng.integers(-2 ** 15, 2 ** 15, size=s).astype(np.int16)
+    kt, vt, kc, vc = mk(layers, heads, T, d), mk(layers, heads, T, d), mk(layers, heads, cap, d), mk(layers, heads, cap, d)
+    path = np.full(T, -1, np.int32)
+    path[:n] = rng.permutation(T)[:n]
+    k_dev, k_base = hx.guarded(kc.shape, torch.int16)
+    v_dev, v_base = hx.guarded(vc.shape, torch.int16)
+    k_dev.copy_(torch.from_numpy(kc))
+    v_dev.copy_(torch.from_numpy(vc))
+    to = lambda a: torch.from_numpy(a).cuda()
+    print(f"[case] commit layers={layers} heads={heads} T={T} bound={bound} n={n}", flush=True)
+    sx.commit_tree_kv(to(kt), to(vt), k_dev, v_dev, to(path), to(np.array([n], np.int32)), bound, T, layers, heads, d, 2, L, cap)
+    torch.cuda.synchronize()
+    assert hx.guards_intact(k_base) and hx.guards_intact(v_base)
+    for y in range(layers):
+        rk, rv, _ = orc.commit_tree_kv(kc[y], vc[y], kt[y], vt[y], [int(x) for x in path[:n]], L)
+        assert (k_dev[y].cpu().numpy() == rk).all() and (v_dev[y].cpu().numpy() == rv).all()
