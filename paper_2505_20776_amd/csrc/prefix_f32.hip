@@ -256,7 +256,8 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
 #pragma unroll
       for (int s = 0; s < NSUB; ++s) {
         const float new_ref = fmaxf(ref[s], halves_max(rows16_max(mx[s])));
-        const float alpha = fast_exp2((ref[s] - new_ref) * c);     // 0 on the first tile
+        // 0 on the first tile; a row may have seen nothing but logits of minus infinity yet
+        const float alpha = new_ref > -INFINITY ? fast_exp2((ref[s] - new_ref) * c) : 1.f;
         ref[s] = new_ref;
         run_sum[s] *= alpha;
 #pragma unroll
@@ -266,10 +267,11 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) {
       const float mc = ref[s] * c;
+      const float base = mc > -INFINITY ? mc : 0.f;
 #pragma unroll
       for (int u = 0; u < kSubTiles; ++u) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(fmaf(s_acc[s][u][i], c, -mc));
+        for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(fmaf(s_acc[s][u][i], c, -base));
         float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
         run_sum[s] += part;
         if (SCORES) {

@@ -1,0 +1,87 @@
+"""Values at the edge of the range through the prefix kernel with fp32 probabilities and the merge behind it: infinities, logits
+and scales near the ends of fp32.  Each case is a call that plain fp32 attention answers."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# as at the fp32-probability kernel's tests: a logit and with it a probability off by 5.6e-5 at most
+TOL = 1e-4
+
+
+def _run(dtype, q, k, v, *, chunk=16, scale=0.0, splits=0, v_tree=None, parent=None):
+    """Output, log-sum-exp and chunk scores of the library and of fp64; the tree's keys are zero."""
+    import paper_2505_20776_amd as sx
+    dt, code = (torch.bfloat16, sx.SPECEXT_BF16) if dtype == "bf16" else (torch.float32, sx.SPECEXT_F32)
+    q, k, v = q.to(dt), k.to(dt), v.to(dt)
+    T, hq, d = q.shape
+    hkv, L, _ = k.shape
+    G = hq // hkv
+    kt = torch.zeros((hkv, T, d), dtype=dt)
+    vt = torch.zeros((hkv, T, d), dtype=dt) if v_tree is None else v_tree.to(dt)
+    parent = [-1] * T if parent is None else parent
+    desc = sx.make_desc(dtype=code, out_dtype=sx.SPECEXT_F32, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=L, n_tree=T,
+                        chunk_size=chunk, want_scores=True, softmax_scale=scale, num_splits=splits)
+    ws = torch.zeros(sx.workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    out, lse = torch.empty((T, hq, d), device="cuda"), torch.empty((hq, T), device="cuda")
+    n_chunks = -(-L // chunk)
+    scores = torch.empty((T, n_chunks), device="cuda")
+    sx.verify_attn(desc, q.cuda(), k.cuda(), v.cuda(), kt.cuda(), vt.cuda(), torch.tensor(parent, dtype=torch.int32).cuda(), out,
+                   lse, ws)
+    sx.chunk_scores(desc, ws, -1, scores)
+    torch.cuda.synchronize()
+
+    sees = torch.zeros((T, T), dtype=torch.bool)
+    for i in range(T):
+        j = i
+        while j >= 0:
+            sees[i, j] = True
+            j = parent[j]
+    ref, ref_lse, ref_p = torch.empty((T, hq, d), dtype=torch.float64), torch.empty((hq, T), dtype=torch.float64), 0.0
+    for h in range(hq):
+        kk, vv = torch.cat([k[h // G], kt[h // G]]).double(), torch.cat([v[h // G], vt[h // G]]).double()
+        s = (q[:, h].double() @ kk.t()) * (scale or 1 / math.sqrt(d))
+        s[:, L:].masked_fill_(~sees, -math.inf)
+        ref_lse[h] = torch.logsumexp(s, 1)
+        p = torch.exp(s - ref_lse[h][:, None])
+        ref_p = ref_p + p[:, :L] / hq
+        # a key of probability zero contributes nothing, whatever its value
+        ref[:, h] = torch.stack([(p[t, p[t] > 0, None] * vv[p[t] > 0]).sum(0) for t in range(T)])
+    size = torch.tensor([min(chunk, L - c * chunk) for c in range(n_chunks)], dtype=torch.float64)
+    ref_scores = torch.nn.functional.pad(ref_p, (0, n_chunks * chunk - L)).view(T, n_chunks, chunk).sum(2) / size
+    return (out.cpu().double(), lse.cpu().double(), scores.cpu().double()), (ref, ref_lse, ref_scores)
+
+
+def _check(got, want, tol=TOL):
+    (out, lse, scores), (ref, ref_lse, ref_scores) = got, want
+    finite = torch.isfinite(ref)
+    assert torch.equal(out[~finite], ref[~finite])            # the same infinities (no case here has a NaN)
+    assert torch.isfinite(out[finite]).all()
+    assert (out - ref)[finite].abs().max() <= tol * ref[finite].abs().max()
+    assert ((lse - ref_lse).abs() <= tol * ref_lse.abs().clamp(min=1)).all()
+    assert torch.isfinite(scores).all() and (scores - ref_scores).abs().max() <= tol * ref_scores.max()
+
+
+def _draw(seed, T, hq, hkv, L, d):
+    gen = torch.Generator().manual_seed(seed)
+    r = lambda *s: torch.randn(s, generator=gen)  # noqa: E731
+    return r(T, hq, d), r(hkv, L, d), r(hkv, L, d)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("masked,splits", [(16, 0), (48, 1), (64, 0), (300, 2), (333, 0)])
+def test_leading_keys_with_logits_of_minus_infinity(dtype, d, masked, splits):
+    """Keys switched off by an infinite component: whole tiles, key groups, splits, all of the prefix."""
+    q, k, v = _draw(masked + d, 9, 8, 2, 333, d)
+    q[:, :, 0] = q[:, :, 0].abs() + 0.1
+    k[:, :masked] = 0
+    k[:, :masked, 0] = -math.inf
+    if masked == 333:
+        got, want = _run(dtype, q, k, v, splits=splits)
+        assert (got[0] == 0).all() and (got[2] == 0).all()     # the tree's zero values are all there is
+        assert (got[1] - want[1]).abs().max() <= TOL
+    else:
+        _check(*_run(dtype, q, k, v, splits=splits))
