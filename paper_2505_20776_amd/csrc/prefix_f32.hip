@@ -148,14 +148,13 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
   for (int s = 0; s < NSUB; ++s)
 #pragma unroll
     for (int b = 0; b < kOBlocks; ++b) acc[s][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float ref[NSUB], run_sum[NSUB];      // reference logit (raw units) the exponentials are taken against; lane-partial sum
+  float ref[NSUB], run_sum[NSUB];      // reference (scaled logit, base 2) the exponentials are taken against; lane-partial sum
 #pragma unroll
   for (int s = 0; s < NSUB; ++s) {
     ref[s] = -INFINITY;
     run_sum[s] = 0.f;
   }
   const float c = p.scale_log2;
-  const float lazy_raw = kLazyLog2 / c;
   const int gran_log2 = __builtin_ctz(p.score_gran);
 
   // A tile in three parts: the logits (and the V fragments: all that reads the ring), the softmax, the second product (from
@@ -250,14 +249,15 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
 #pragma unroll
       for (int u = 0; u < kSubTiles; ++u)
         mx[s] = fmaxf(mx[s], fmaxf(fmaxf(s_acc[s][u][0], s_acc[s][u][1]), fmaxf(s_acc[s][u][2], s_acc[s][u][3])));
-      grow |= mx[s] > ref[s] + lazy_raw;
+      mx[s] *= c;
+      grow |= mx[s] > ref[s] + kLazyLog2;
     }
     if (__any(grow)) {                 // some row of this wave outgrew its reference: move every reference up
 #pragma unroll
       for (int s = 0; s < NSUB; ++s) {
         const float new_ref = fmaxf(ref[s], halves_max(rows16_max(mx[s])));
         // 0 on the first tile; a row may have seen nothing but logits of minus infinity yet
-        const float alpha = new_ref > -INFINITY ? fast_exp2((ref[s] - new_ref) * c) : 1.f;
+        const float alpha = new_ref > -INFINITY ? fast_exp2(ref[s] - new_ref) : 1.f;
         ref[s] = new_ref;
         run_sum[s] *= alpha;
 #pragma unroll
@@ -266,8 +266,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
     }
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) {
-      const float mc = ref[s] * c;
-      const float base = mc > -INFINITY ? mc : 0.f;
+      const float base = ref[s] > -INFINITY ? ref[s] : 0.f;
 #pragma unroll
       for (int u = 0; u < kSubTiles; ++u) {
 #pragma unroll
@@ -282,7 +281,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
           const int m = row0 + 16 * s + li;
           if (((4 * qt) & (p.score_gran - 1)) == 0 && key < key_hi && m < p.M)
             *reinterpret_cast<floatx2*>(p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + (key >> gran_log2)) * p.M + m) * 2) =
-                floatx2{part, mc};
+                floatx2{part, ref[s]};
         }
       }
     }
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
     for (int b = 0; b < kOBlocks; ++b)
       if (b / kShare != kg) *reinterpret_cast<floatx4*>(dump + (s * kOBlocks + b) * 1024) = columns(s, b);
     if (qt == 0) {
-      ml[(wave * 2 + 0) * kRows + 16 * s + li] = ref[s] * c;
+      ml[(wave * 2 + 0) * kRows + 16 * s + li] = ref[s];
       ml[(wave * 2 + 1) * kRows + 16 * s + li] = sum;
     }
   }

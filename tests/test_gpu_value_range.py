@@ -85,3 +85,13 @@ def test_leading_keys_with_logits_of_minus_infinity(dtype, d, masked, splits):
         assert (got[1] - want[1]).abs().max() <= TOL
     else:
         _check(*_run(dtype, q, k, v, splits=splits))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("scale", [1e-42, 1e-38, 3e-38, 1e-3, 4.0])
+def test_softmax_scales(dtype, d, scale):
+    """Down to the smallest scales (an even softmax).  A logit's error grows with the scale: at 4.0 its sum of d products of
+    unit variance is off by up to d * 2^-24 * 4 * 0.64 * d = 2.5e-3."""
+    q, k, v = _draw(d, 7, 8, 2, 200, d)
+    _check(*_run(dtype, q, k, v, scale=scale), tol=TOL if scale < 1 else 2.5e-3)
