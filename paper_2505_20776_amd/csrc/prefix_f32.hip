@@ -59,6 +59,12 @@ struct Tile {
   }
 };
 
+// The exponent is one fused multiply-add, logit * c - reference, with the reference the rounded product for the row's largest
+// logit: the rounding is left in every exponent alike, up to 2^-24 of the reference, and cancels in the row's sum.  From
+// references of 2^24 on it could no longer be left in; there the product is rounded before the subtraction, as it was for the
+// reference, and the largest logit's exponent is zero again.
+constexpr float kFarLog2 = 16777216.f;
+
 constexpr int stages_of(int stage_bytes) { return kRingBytes / stage_bytes < 4 ? kRingBytes / stage_bytes : 4; }
 
 // value + the value of the lane 16 away (within a pair of 16-lane rows)
@@ -123,7 +129,6 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
       load_to_lds_16(dst + T::kBytes + u * 1024, off + ((ld_piece ^ T::v_swz(r)) << 4), vsrc);
     }
   };
-  issue_stage(0);
 
   // queries (B operand of S^T); rows past the last one repeat it and are never stored
   uintx4 qf[NSUB][kQRegs];
@@ -136,12 +141,32 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
 #pragma unroll
     for (int j = 0; j < kQRegs; ++j) qf[s][j] = *reinterpret_cast<const uintx4*>(src + 64 * j);
   }
-  // All query loads have landed before the loop starts; said through the builtin so that the compiler's own wait
+  issue_stage(0);
+  // All query loads have landed before they are used; said through the builtin so that the compiler's own wait
   // bookkeeping sees it and adds no vmcnt(0) inside the loop, which would wait for the stage just requested
-  // (0x0F70 = vmcnt(0), other counters untouched).
-  __builtin_amdgcn_s_waitcnt(0x0F70);
+  // (the loads of stage 0 stay in flight; 0x0F70: other counters untouched).
+  constexpr int kInFlight = kLoadsPerStage;
+  if (my_tiles > 0) __builtin_amdgcn_s_waitcnt((kInFlight & 15) | (kInFlight >> 4 << 14) | 0x0F70);
+  else __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll
   for (int st = 1; st < kStages - 1; ++st) issue_stage(st);
+  // The scale's power of two goes into the queries (exact), so that a logit that is finite scaled is finite as the product
+  // leaves it: 1 / sqrt(d) and the factor of base 2 make it a sixth to an eighth.
+  const int scale_exp = max(-16, min(0, static_cast<int>(__float_as_uint(p.scale_log2) >> 23) - 127));
+  const float q_scale = __uint_as_float(static_cast<uint32_t>(127 + scale_exp) << 23);
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+    for (int j = 0; j < kQRegs; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t w = qf[s][j][e];
+        if constexpr (BF16)
+          qf[s][j][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{__uint_as_float(w << 16) * q_scale,
+                                                                                     __uint_as_float(w & 0xffff0000u) * q_scale}, bf16x2));
+        else
+          qf[s][j][e] = __float_as_uint(__uint_as_float(w) * q_scale);
+      }
 
   floatx4 acc[NSUB][kOBlocks];
 #pragma unroll
@@ -154,8 +179,9 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
     ref[s] = -INFINITY;
     run_sum[s] = 0.f;
   }
-  const float c = p.scale_log2;
+  const float c = p.scale_log2 * __uint_as_float(static_cast<uint32_t>(127 - scale_exp) << 23);      // what is left of the scale
   const int gran_log2 = __builtin_ctz(p.score_gran);
+  bool far = false;                    // some reference of this wave is beyond kFarLog2
 
   // A tile in three parts: the logits (and the V fragments: all that reads the ring), the softmax, the second product (from
   // registers).  With every wave in the same order both waves of a SIMD would be in their softmax at the same time and the
@@ -262,15 +288,37 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
         run_sum[s] *= alpha;
 #pragma unroll
         for (int b = 0; b < kOBlocks; ++b) acc[s][b] *= alpha;
+        far |= __any(new_ref > kFarLog2 || (new_ref < -kFarLog2 && new_ref > -INFINITY));
       }
+    }
+    float base[NSUB];
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s) base[s] = ref[s] > -INFINITY ? ref[s] : 0.f;
+    if (far) {
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+        for (int u = 0; u < kSubTiles; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float scaled = s_acc[s][u][i] * c;
+            asm volatile("" : "+v"(scaled));               // rounded before the subtraction
+            s_acc[s][u][i] = scaled - base[s];
+          }
+    } else {
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+        for (int u = 0; u < kSubTiles; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fmaf(s_acc[s][u][i], c, -base[s]);
     }
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) {
-      const float base = ref[s] > -INFINITY ? ref[s] : 0.f;
 #pragma unroll
       for (int u = 0; u < kSubTiles; ++u) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(fmaf(s_acc[s][u][i], c, -base));
+        for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(s_acc[s][u][i]);
         float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
         run_sum[s] += part;
         if (SCORES) {
