@@ -188,7 +188,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
   // matrix pipe idle; so the upper half of a workgroup of eight waves (wave w + 4 shares wave w's SIMD) starts a stage with
   // the second product of the tile before (bf16 inputs, 4109 keys: 18.7 instead of 19.9 us; fp32 inputs: equal).
   floatx4 s_acc[NSUB][kSubTiles];      // the tile's logits, then its probabilities
-  bf16x8 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
+  uintx4 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
   uintx4 vf[kOBlocks];                 // fp32: [key i of the quarter][64-column block]; bf16: [16-column block]
   auto tile_logits = [&](int st) __attribute__((always_inline)) {
     const unsigned char* ktile = lds + (st % kStages) * kStageBytes + kg * (2 * T::kBytes);
@@ -334,17 +334,20 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
       }
     }
     if constexpr (BF16) {
-      // P as three bf16 terms: the rounded value, the rounded rest and the rest of that (each subtraction is exact)
+      // P as three bf16 terms, each the leading eight bits of what is just below the rest: their sum is P exactly and none is
+      // zero or negative while P is not zero, so an infinite V gives that infinity as in one product.
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float x = s_acc[s][e >> 2][e & 3];
+        for (int e = 0; e < 8; e += 2) {
+          float x0 = s_acc[s][e >> 2][e & 3], x1 = s_acc[s][e >> 2][(e & 3) + 1];
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
-            const __bf16 b = static_cast<__bf16>(x);
-            pf[s][k][e] = b;
-            x -= static_cast<float>(b);
+            const uint32_t b0 = k < 2 ? __builtin_elementwise_sub_sat(__float_as_uint(x0), 1u) : __float_as_uint(x0);
+            const uint32_t b1 = k < 2 ? __builtin_elementwise_sub_sat(__float_as_uint(x1), 1u) : __float_as_uint(x1);
+            pf[s][k][e / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302);          // the upper halves
+            x0 -= __uint_as_float(b0 & 0xffff0000u);
+            x1 -= __uint_as_float(b1 & 0xffff0000u);
           }
         }
     }
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
         for (int k = 2; k >= 0; --k)                        // smallest terms first
 #pragma unroll
           for (int s = 0; s < NSUB; ++s)
-            acc[s][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[b]), pf[s][k], acc[s][b], 0, 0, 0);
+            acc[s][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[b]), __builtin_bit_cast(bf16x8, pf[s][k]), acc[s][b], 0, 0, 0);
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)

@@ -109,3 +109,12 @@ def test_large_logits(dtype, d, scale, q0, k0):
     q[:], k[:] = 0, 0
     q[:, :, 0], k[:, ::7, 0] = q0, k0
     _check(*_run(dtype, q, k, v, scale=scale), check_scores=False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype,L,splits", [("f32", 333, 0), ("f32", 320, 5), ("bf16", 333, 0), ("bf16", 640, 5)])
+def test_infinite_values(dtype, d, L, splits):
+    """An infinite component of a value that has weight is the output's."""
+    q, k, v = _draw(L + d, 9, 8, 2, L, d)
+    v[:, 3, 1], v[:, 15, 5], v[:, L // 2, d - 1] = math.inf, -math.inf, math.inf
+    _check(*_run(dtype, q, k, v, splits=splits))
