@@ -525,21 +525,27 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
     q[e] *= p.scale_log2;
     o[e] = 0.f;
   }
+  auto add_splits = [&](auto all_there) __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const float w = lane_read(wgt, grp0 + u);
+    for (int u = 0; u < PER; ++u) {
+      const float w = lane_read(wgt, grp0 + u);
+      const bool there = decltype(all_there)::value || s_lo + u <= s_last;
 #pragma unroll
-    for (int e = 0; e < PW; ++e) {
-      const uint32_t word = raw[u][e];
-      if constexpr (PART_F16) {
-        const halfx2 hh = __builtin_bit_cast(halfx2, word);
-        o[2 * e] = fmaf(static_cast<float>(hh[0]), w, o[2 * e]);
-        o[2 * e + 1] = fmaf(static_cast<float>(hh[1]), w, o[2 * e + 1]);
-      } else {
-        o[e] = fmaf(__uint_as_float(word), w, o[e]);
+      for (int e = 0; e < PW; ++e) {
+        const uint32_t word = there ? raw[u][e] : 0u;
+        if constexpr (PART_F16) {
+          const halfx2 hh = __builtin_bit_cast(halfx2, word);
+          o[2 * e] = fmaf(static_cast<float>(hh[0]), w, o[2 * e]);
+          o[2 * e + 1] = fmaf(static_cast<float>(hh[1]), w, o[2 * e + 1]);
+        } else {
+          o[e] = fmaf(__uint_as_float(word), w, o[e]);
+        }
       }
     }
-  }
+  };
+  // the last split read again in place of one that there is not may be infinite, and its weight of zero would make it NaN
+  if (PART_F16 || s_lo + PER - 1 <= s_last) add_splits(std::integral_constant<bool, true>{});
+  else add_splits(std::integral_constant<bool, false>{});
 
   // the wave's share of the tree part, one online-softmax step per batch
   while (true) {
@@ -565,6 +571,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #pragma unroll
     for (int u = 0; u < kAnc; ++u) {
       const float pr = anc[u] >= 0 ? fast_exp2(sc[u] - new_max) : 0.f;
+      if (anc[u] < 0) vraw[u] = RowWords{};        // the row read in place of an ancestor that there is not may be infinite
 #pragma unroll
       for (int e = 0; e < E; ++e) o[e] = fmaf(pr, row_element<IN_BF16>(vraw[u], e), o[e]);
       run_sum += pr;

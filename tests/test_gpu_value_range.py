@@ -118,3 +118,15 @@ def test_infinite_values(dtype, d, L, splits):
     q, k, v = _draw(L + d, 9, 8, 2, L, d)
     v[:, 3, 1], v[:, 15, 5], v[:, L // 2, d - 1] = math.inf, -math.inf, math.inf
     _check(*_run(dtype, q, k, v, splits=splits))
+
+
+@pytest.mark.parametrize("dtype,d,L,splits", [("f32", 64, 64, 1), ("f32", 128, 320, 5), ("f32", 64, 600, 9), ("bf16", 128, 20, 0),
+                                              ("bf16", 64, 640, 5)])
+def test_infinite_values_in_the_last_split_and_in_the_tree(dtype, d, L, splits):
+    """The merge reads the last split and the first node again in place of those that a wave does not have."""
+    q, k, v = _draw(L * d, 9, 8, 2, L, d)
+    v[:, L - 2, 1] = math.inf
+    v_tree = torch.randn((2, 9, d), generator=torch.Generator().manual_seed(L))
+    v_tree[:, 0, 2], v_tree[:, 4, 3] = -math.inf, math.inf
+    # two roots; nodes 1, 3, 5, 6 do not see node 0
+    _check(*_run(dtype, q, k, v, splits=splits, v_tree=v_tree, parent=[-1, -1, 0, 1, 2, 3, 5, 4, 0]))
