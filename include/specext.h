@@ -160,6 +160,12 @@ int specext_workspace_init(void* workspace, size_t workspace_bytes, void* stream
  * rescale exponent travels in the split's softmax reference, so the magnitudes of V
  * must stay within 2^-100 ... 2^100 and those of two splits of one row within a factor
  * of about 2^100 of each other, or a split's weight underflows.
+ * The matrix-core kernels let a row's softmax reference lag behind its largest logit by up
+ * to 2^10 before they rescale, so their unnormalised sums reach 2^10 times |V| times the
+ * keys of a split: with the kernel with fp32 probabilities, whose partial outputs are fp32,
+ * magnitudes of V up to 2^100 stay finite whatever the logits (the vector-ALU kernel: up
+ * to 2^110).  The matrix-core kernels with bf16 probabilities form q k before the scale:
+ * that product has to be finite in fp32, and with the scale below 2^24 in magnitude.
  * The first int32 of the workspace is a status word: 0 after a good call,
  * 1 if some parent[i] was >= i or < -1 (that node is then treated as a root),
  * 2 if SPECEXT_FLAG_FUSED_MERGE was set and the workspace was never initialised

@@ -130,3 +130,13 @@ def test_infinite_values_in_the_last_split_and_in_the_tree(dtype, d, L, splits):
     v_tree[:, 0, 2], v_tree[:, 4, 3] = -math.inf, math.inf
     # two roots; nodes 1, 3, 5, 6 do not see node 0
     _check(*_run(dtype, q, k, v, splits=splits, v_tree=v_tree, parent=[-1, -1, 0, 1, 2, 3, 5, 4, 0]))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("size", [2.0 ** 100, 2.0 ** -100])
+def test_range_of_values(dtype, d, size):
+    """The magnitudes of V that the header promises, behind logits that grow from tile to tile (the reference lags by up to 2^10)."""
+    q, k, v = _draw(d, 9, 8, 2, 600, d)
+    k *= torch.linspace(0.2, 3, 600)[None, :, None]
+    _check(*_run(dtype, q, k, v * size))
