@@ -15,18 +15,43 @@ namespace {
 // scores[r][c] = (1/Hq) * sum_h  sum_blocks  blocksum(h, t) * exp2(ref - lse2(h, t)) / |c|
 // The prefix pass leaves one (sum, ref) pair per score block (score_gran keys;
 // a chunk is a whole number of blocks).  The heads of a chunk are dealt to the four lanes of a
-// quad (head h to lane h mod 4: with four heads per group a quad's load is 32 consecutive bytes),
-// each adds its heads in ascending order, block by block, and the four sums are combined in a fixed
-// order: a deterministic fp32 sum.
+// quad (head h to lane h mod 4: with four heads per group a quad's load is 32 consecutive bytes);
+// each adds its heads in ascending order, and the four sums are combined in a fixed order: a
+// deterministic fp32 sum.  The blocks of a longer chunk are dealt to 4, 16 or 64 quads, whose sums
+// are combined in a fixed order too.
 //
 // What bounds it: every pair group is a 32-byte piece of a line of its own (the pairs of a block are
 // [rows], as the prefix kernels write them), fetched from behind another XCD's L2, so the kernel is one
 // trip to memory if all of a thread's loads are in flight together and enough compute units ask.  Hence
 // one wavefront and 16 chunks per workgroup; 64 chunks per workgroup with a head's loads one after the
 // other took 5.5 us for 512 chunks of one block and 7.9 us for 512 of two (32 heads in 8 groups), this
-// 4.6 us for either.
-constexpr int kScoreChunks = 16;               // chunks per workgroup
+// 2.5 and 2.9 us.
 constexpr int kHeadsAtOnce = 8;                // heads of one thread whose loads are in flight together
+
+// NSUB score blocks per lane and step, QUADS quads per chunk: the smallest pair whose product covers a chunk's blocks
+// (chunks beyond 256 blocks take several steps).
+template <int NSUB, int QUADS>
+struct ScoreShape {
+  static constexpr int kBlocks = NSUB;
+  static constexpr int kQuads = QUADS;
+  static constexpr int kLanes = 4 * QUADS;                         // per chunk
+  static constexpr int kThreads = kLanes > 64 ? kLanes : 64;       // of a workgroup of chunk_scores_kernel
+  static constexpr int kChunks = kThreads / kLanes;
+};
+// Measured, us for the scores of one row over 8K fp32 keys (32 heads in 8 groups) in chunks of 16, 64 and 512 blocks: 17, 66
+// and 490 with one quad per chunk, whose blocks beyond the first four come one after the other; 4.1, 4.0 and 5.7 so.
+template <class F>
+__host__ void with_score_shape(int blocks, F&& f) {
+  if (blocks <= 1) f(ScoreShape<1, 1>{});
+  else if (blocks <= 2) f(ScoreShape<2, 1>{});
+  else if (blocks <= 4) f(ScoreShape<4, 1>{});
+  else if (blocks <= 8) f(ScoreShape<2, 4>{});
+  else if (blocks <= 16) f(ScoreShape<4, 4>{});
+  else if (blocks <= 32) f(ScoreShape<2, 16>{});
+  else if (blocks <= 64) f(ScoreShape<4, 16>{});
+  else if (blocks <= 128) f(ScoreShape<2, 64>{});
+  else f(ScoreShape<4, 64>{});
+}
 
 // the tree row to score: given, or the acceptance walk's last accepted node read on the device
 __device__ __forceinline__ int scored_row(const AttnParams& p, int first_row, const int* row_path, const int* row_count) {
@@ -42,39 +67,42 @@ __device__ __forceinline__ float quad_lane(float v) {
   return SPECEXT_DPP(v, I * 0x55);
 }
 
-// Sum over the heads `part`, part + 4, ... of one chunk's blocks [sub_lo, sub_hi), at most NSUB of them in flight per head.
-template <int NSUB>
-__device__ __forceinline__ float chunk_head_sum(const AttnParams& p, int t, int part, int sub_lo, int sub_hi) {
+// The four partial sums of chunk c that chunk_score adds, by the chunk's lanes; `lane` = number among them.  QUADS = 1: lane
+// p returns the p-th.  4 or 16: every lane returns the first, the others are zero.  64: the lanes of wave p return the p-th.
+template <class Shape>
+__device__ __forceinline__ float chunk_partial(const AttnParams& p, int t, int c, int lane) {
+  constexpr int kBlocks = Shape::kBlocks;
+  const int part = lane & 3;
+  const int per_chunk = p.B / p.score_gran;
+  const int sub_lo = min(c, p.C - 1) * per_chunk;               // chunks past the end re-read the last one, unused
+  const int sub_hi = min(sub_lo + per_chunk, p.n_sub);
   float acc = 0.f;
-  for (int hb = part; hb < p.Hq; hb += 4 * kHeadsAtOnce) {
-    float l2[kHeadsAtOnce];
-    float2 pair[kHeadsAtOnce][NSUB];
-    const float* src[kHeadsAtOnce];
+  for (int sb0 = sub_lo + (lane >> 2); sb0 < sub_hi; sb0 += kBlocks * Shape::kQuads) {
+    for (int hb = part; hb < p.Hq; hb += 4 * kHeadsAtOnce) {
+      float l2[kHeadsAtOnce];
+      float2 pair[kHeadsAtOnce][kBlocks];
 #pragma unroll
-    for (int u = 0; u < kHeadsAtOnce; ++u) {
-      const int h = min(hb + 4 * u, p.Hq - 1);                 // heads past the end re-read the last one, unused
-      const int g = h / p.G;
-      const int m = t * p.G + (h - g * p.G);
-      l2[u] = p.lse2[g * p.M + m];
-      src[u] = p.chunk_part + (static_cast<int64_t>(g) * p.n_sub * p.M + m) * 2;
+      for (int u = 0; u < kHeadsAtOnce; ++u) {
+        const int h = min(hb + 4 * u, p.Hq - 1);                 // heads past the end re-read the last one, unused
+        const int g = h / p.G;
+        const int m = t * p.G + (h - g * p.G);
+        l2[u] = p.lse2[g * p.M + m];
+        const float* src = p.chunk_part + (static_cast<int64_t>(g) * p.n_sub * p.M + m) * 2;
 #pragma unroll
-      for (int b = 0; b < NSUB; ++b)                            // blocks past the chunk's end re-read its last one, unused
-        pair[u][b] = *reinterpret_cast<const float2*>(src[u] + static_cast<int64_t>(min(sub_lo + b, sub_hi - 1)) * p.M * 2);
-    }
+        for (int b = 0; b < kBlocks; ++b)                         // blocks past the chunk's end re-read its last one, unused
+          pair[u][b] = *reinterpret_cast<const float2*>(src + static_cast<int64_t>(min(sb0 + b * Shape::kQuads, sub_hi - 1)) * p.M * 2);
+      }
 #pragma unroll
-    for (int u = 0; u < kHeadsAtOnce; ++u) {
-      if (hb + 4 * u < p.Hq) {
+      for (int u = 0; u < kHeadsAtOnce; ++u) {
+        if (hb + 4 * u < p.Hq) {
 #pragma unroll
-        for (int b = 0; b < NSUB; ++b)
-          if (sub_lo + b < sub_hi) acc += pair[u][b].x * exp2f(pair[u][b].y - l2[u]);
-        for (int sb = sub_lo + NSUB; sb < sub_hi; ++sb) {
-          const float2 cp = *reinterpret_cast<const float2*>(src[u] + static_cast<int64_t>(sb) * p.M * 2);
-          acc += cp.x * exp2f(cp.y - l2[u]);
+          for (int b = 0; b < kBlocks; ++b)
+            if (sb0 + b * Shape::kQuads < sub_hi) acc += pair[u][b].x * exp2f(pair[u][b].y - l2[u]);
         }
       }
     }
   }
-  return acc;
+  return Shape::kQuads == 1 ? acc : Shape::kQuads == 4 ? row16_sum(acc) : wave_sum(acc);
 }
 
 __device__ __forceinline__ float chunk_score(const AttnParams& p, int c, float p0, float p1, float p2, float p3) {
@@ -82,17 +110,23 @@ __device__ __forceinline__ float chunk_score(const AttnParams& p, int c, float p
   return (((p0 + p1) + p2) + p3) / (static_cast<float>(size) * static_cast<float>(p.Hq));
 }
 
-template <int NSUB>
-__global__ __launch_bounds__(4 * kScoreChunks) void chunk_scores_kernel(AttnParams p, int first_row, const int* row_path,
+template <class Shape>
+__global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(AttnParams p, int first_row, const int* row_path,
                                                                        const int* row_count, float* scores) {
   const int t = scored_row(p, first_row + blockIdx.y, row_path, row_count);
-  const int c = blockIdx.x * kScoreChunks + (threadIdx.x >> 2);
-  const int part = threadIdx.x & 3;
-  const int per_chunk = p.B / p.score_gran;
-  const int sub_lo = min(c, p.C - 1) * per_chunk;               // chunks past the end re-read the last one, unused
-  const float acc = chunk_head_sum<NSUB>(p, t, part, sub_lo, min(sub_lo + per_chunk, p.n_sub));
-  const float score = chunk_score(p, c, quad_lane<0>(acc), quad_lane<1>(acc), quad_lane<2>(acc), quad_lane<3>(acc));
-  if (part == 0 && c < p.C) scores[static_cast<int64_t>(blockIdx.y) * p.C + c] = score;
+  const int c = blockIdx.x * Shape::kChunks + threadIdx.x / Shape::kLanes;
+  const int lane = threadIdx.x % Shape::kLanes;
+  const float acc = chunk_partial<Shape>(p, t, c, lane);
+  float parts[4] = {acc, 0.f, 0.f, 0.f};
+  if constexpr (Shape::kQuads == 1) {
+    parts[0] = quad_lane<0>(acc), parts[1] = quad_lane<1>(acc), parts[2] = quad_lane<2>(acc), parts[3] = quad_lane<3>(acc);
+  } else if constexpr (Shape::kQuads == 64) {
+    __shared__ float of_wave[4];
+    if ((lane & 63) == 0) of_wave[lane >> 6] = acc;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) parts[w] = of_wave[w];
+  }
+  if (lane == 0 && c < p.C) scores[static_cast<int64_t>(blockIdx.y) * p.C + c] = chunk_score(p, c, parts[0], parts[1], parts[2], parts[3]);
 }
 
 // --------------------------------------------------------------------------
@@ -333,17 +367,19 @@ __global__ __launch_bounds__(kSelThreads) void select_radix_kernel(const float* 
 // Chunk scores of one tree row and the top-k over them in one launch (at most kRankMax
 // chunks, up to 1024 threads), for problems whose pairs one compute unit takes in faster than a second launch
 // costs.  Scores with the arithmetic of chunk_scores_kernel: the same bits.  scores may be null.
+template <class Shape>
 __global__ __launch_bounds__(kRankMax) void score_select_kernel(AttnParams p, int score_row, const int* row_path,
                                                                const int* row_count, int k, float* scores,
                                                                int* __restrict__ idx_out, int* __restrict__ n_out) {
   __shared__ RadixLds<1> radix;
   __shared__ float partial[kRankMax][4];
   const int t = scored_row(p, score_row, row_path, row_count);
-  const int part = threadIdx.x & 3;
-  const int per_chunk = p.B / p.score_gran;
-  for (int c = threadIdx.x >> 2; c < p.C; c += blockDim.x / 4) {
-    const int sub_lo = c * per_chunk;
-    partial[c][part] = chunk_head_sum<2>(p, t, part, sub_lo, min(sub_lo + per_chunk, p.n_sub));
+  const int lane = threadIdx.x % Shape::kLanes;
+  for (int c = threadIdx.x / Shape::kLanes; c < p.C; c += blockDim.x / Shape::kLanes) {
+    const float acc = chunk_partial<Shape>(p, t, c, lane);
+    if constexpr (Shape::kQuads == 1) partial[c][lane] = acc;
+    else if constexpr (Shape::kQuads == 64) partial[c][lane >> 6] = acc;
+    else if (lane < 4) partial[c][lane] = lane == 0 ? acc : 0.f;
   }
   __syncthreads();
   const int c = threadIdx.x;
@@ -450,11 +486,11 @@ hipError_t launch_chunk_scores(const AttnParams& p, int32_t score_row, const int
                                const int32_t* row_count, float* scores, hipStream_t stream) {
   const int rows = (score_row < 0 && !row_path) ? p.T : 1;
   const int first = score_row < 0 ? 0 : score_row;
-  dim3 grid((p.C + kScoreChunks - 1) / kScoreChunks, rows), block(4 * kScoreChunks);
-  const int per_chunk = p.B / p.score_gran;
-  if (per_chunk <= 1) chunk_scores_kernel<1><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
-  else if (per_chunk <= 2) chunk_scores_kernel<2><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
-  else chunk_scores_kernel<4><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
+  with_score_shape(p.B / p.score_gran, [&](auto shape) {
+    using Shape = decltype(shape);
+    const dim3 grid((p.C + Shape::kChunks - 1) / Shape::kChunks, rows), block(Shape::kThreads);
+    chunk_scores_kernel<Shape><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
+  });
   return hipGetLastError();
 }
 
@@ -463,15 +499,19 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
                                hipStream_t stream) {
   if (p.C > kRankMax) return hipErrorInvalidValue;
   // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 3000 on, a launch of its
-  // own for the scores, which every compute unit shares, is the shorter way.  Measured in one launch / in two, without
-  // the 1 - 2 us between two launches: 512 groups 4.6 / 6.0 us, 2056 8.0 / 8.4, 4096 12.0 / 9.1, 8192 13.4 - 16.7 / 9.1.
+  // own for the scores, which every compute unit shares, is the shorter way also for a caller whom the host bounds and a second
+  // launch costs 1.5 - 2 us.  Measured on the device, us in one launch / in two: 512 groups 4.2 / 5.9, 2048 6.7 / 5.8, 3000
+  // 7.7 / 6.1, 4096 9.2 / 6.2, 8192 14.7 / 7.3 (32-key chunks; 10.6 / 6.6 in 64-key chunks).
   if (scores && static_cast<int64_t>(p.Hkv) * p.n_sub > kScoreGroupsOneLaunch) {
     const hipError_t e = launch_chunk_scores(p, score_row, row_path, row_count, scores, stream);
     return e != hipSuccess ? e : launch_select_chunks(scores, p.C, k, idx_out, n_out, stream);
   }
-  // at least one thread per chunk (selection), up to four (scores: four threads per chunk)
-  const int threads = p.C <= 64 ? 256 : p.C <= 128 ? 512 : 1024;
-  score_select_kernel<<<dim3(1), dim3(threads), 0, stream>>>(p, score_row, row_path, row_count, k, scores, idx_out, n_out);
+  // at least one thread per chunk (selection), four or more for the scores as far as 1024 go
+  with_score_shape(p.B / p.score_gran, [&](auto shape) {
+    using Shape = decltype(shape);
+    const int threads = Shape::kQuads > 1 ? 1024 : p.C <= 64 ? 256 : p.C <= 128 ? 512 : 1024;
+    score_select_kernel<Shape><<<dim3(1), dim3(threads), 0, stream>>>(p, score_row, row_path, row_count, k, scores, idx_out, n_out);
+  });
   return hipGetLastError();
 }
 

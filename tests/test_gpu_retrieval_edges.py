@@ -61,3 +61,40 @@ def test_scores_of_blocks_and_heads(Hq, Hkv, L, B):
         assert int(n_out) == k and list(idx.cpu().numpy()) == list(orc.select_chunks(got, k))
     buf.check_guards()
     check_scores(buf.scores.cpu().numpy(), ref, "all rows")
+
+
+@pytest.mark.parametrize("dtype,B,L", [
+    ("f32", 80, 700),             # five blocks of 16: the first length dealt to four quads; a last chunk of four blocks
+    ("f32", 128, 1024), ("f32", 144, 1000), ("f32", 256, 1030),             # 8, 9, 16 blocks; a last chunk of one block
+    ("f32", 272, 600), ("f32", 512, 1500), ("f32", 528, 1100), ("f32", 1024, 2050),     # 17, 32, 33, 64
+    ("f32", 1040, 2100), ("f32", 8192, 5000), ("f32", 4100, 4200),         # 65; one chunk of 313; 1025 blocks of four keys
+    ("bf16", 1024, 4100), ("bf16", 16384, 9000),                           # 32 blocks of 32 keys; one chunk of 282
+])
+def test_chunks_of_many_score_blocks(dtype, B, L):
+    """Every split of a chunk's blocks over quads, against the oracle, and the one-launch form against the two calls."""
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    T, Hq, Hkv = 3, 6, 2
+    wl = make_workload("blocks", seed=B + L, dtype=dtype, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, prefix_len=L,
+                       parent=chain_tree(T), chunk_size=B, top_k=2, n_needles=0, value_std=1.0)
+    print(f"[case] chunk scores {dtype} B={B} L={L}", flush=True)
+    ref = orc.chunk_scores(wl.q, wl.k_prefix, wl.v_prefix, wl.k_tree, wl.v_tree, wl.parent, B)
+    buf = hx.make_buffers(dtype=dtype, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, prefix_len=L, n_tree=T, chunk_size=B,
+                          want_scores=True)
+    to = lambda a: hx.to_device(a, dtype)  # noqa: E731
+    sx.verify_attn(buf.desc, to(wl.q), to(wl.k_prefix), to(wl.v_prefix), to(wl.k_tree), to(wl.v_tree),
+                   torch.from_numpy(wl.parent).cuda(), buf.out, buf.lse, buf.workspace)
+    sx.chunk_scores(buf.desc, buf.workspace, -1, buf.scores)
+    check_scores(buf.scores.cpu().numpy(), ref, f"B={B}")
+    C = buf.scores.shape[1]
+    for row in range(T):
+        one, one_base = hx.guarded((C,), torch.float32)
+        idx, n_out = torch.empty(2, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+        sx.chunk_scores_select(buf.desc, buf.workspace, row, 2, idx, n_out, scores=one)
+        again = torch.empty_like(idx)
+        sx.chunk_scores_select(buf.desc, buf.workspace, row, 2, again, n_out, scores=None)
+        assert torch.equal(one, buf.scores[row]) and hx.guards_intact(one_base)
+        assert torch.equal(idx, again) and int(n_out) == min(2, C)
+        assert list(idx[:int(n_out)].cpu().numpy()) == list(orc.select_chunks(one.cpu().numpy(), 2))
+    torch.cuda.synchronize()
+    buf.check_guards()
