@@ -414,8 +414,8 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #ifdef SPECEXT_TAIL_STAMPS
   // profiling build: 100 MHz wall-clock stamps of this workgroup's phases (0 start, 1 parent array there, 2 the
   // partials requested up front and the query there, 3 tree K/V rows and the other partials there, 4 stores issued,
-  // 5 stores acknowledged), left in the unused upper half of the partial-output region, 2 MiB in; the waits that
-  // separate 2 and 3 are extra
+  // 5 stores acknowledged), left in the upper half of the partial-output region, which fp16 partials do not use, 2 MiB
+  // in (fp32 partials fill it, so there are no stamps then); the waits that separate 2 and 3 are extra
   unsigned long long phase_stamp[6];
   phase_stamp[0] = wall_clock64();
 #endif
@@ -509,10 +509,12 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
   for (int u = kFirst; u < PER; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
 
 #ifdef SPECEXT_TAIL_STAMPS
-  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kAnc + PER - kFirst) : "memory");      // the loads requested up front
-  phase_stamp[2] = wall_clock64();
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  phase_stamp[3] = wall_clock64();
+  if constexpr (PART_F16) {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kAnc + PER - kFirst) : "memory");      // the loads requested up front
+    phase_stamp[2] = wall_clock64();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    phase_stamp[3] = wall_clock64();
+  }
 #endif
   // the wave's prefix splits: lane i of a group holds (max, sum) of split s_lo + i
   if (!ml_valid || !(ml.y > 0.f)) ml = make_float2(-INFINITY, 0.f);        // an empty split contributes nothing
@@ -632,6 +634,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
     if (p.lse) p.lse[fh * p.T + ft] = l2 * kLn2;
   }
 #ifdef SPECEXT_TAIL_STAMPS
+  if constexpr (!PART_F16) return;
   phase_stamp[4] = wall_clock64();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   phase_stamp[5] = wall_clock64();
