@@ -19,8 +19,8 @@ CASES = [
     (600, 600, 8, 4, "bf16"),        # several row groups per head
     (40, 2000, 16, 2, "f32"),        # a short piece, long context
     (300, 4100, 32, 8, "bf16"),      # 1200 rows per KV head behind 3800 tokens: four key groups
-    (1000, 4133, 32, 8, "bf16"),     # twice to four times the chip's workgroups: two key groups
-    (2048, 2048, 8, 8, "bf16"),      # whole prompt, two or four key groups, G = 1
+    (1000, 4133, 32, 8, "bf16"),     # fewer, longer workgroups for the chip: two key groups
+    (2048, 2048, 8, 8, "bf16"),      # whole prompt, G = 1
 ]
 
 
