@@ -543,6 +543,7 @@ int specext_prefill_attn(const void* q, const void* k, const void* v, void* out,
   p.out_dtype = out_dtype;
   if (static_cast<int64_t>(q_len) * p.G > (1 << 24)) return SPECEXT_ERR_UNSUPPORTED;
   p.M = q_len * p.G;
+  p.n_cus = device_cu_count();
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt(static_cast<float>(head_dim));
   p.scale_log2 = scale * kLog2e;
   p.q_st = q_stride_t ? q_stride_t : static_cast<int64_t>(n_q_heads) * head_dim;

@@ -86,6 +86,7 @@ struct PrefillParams {
   void* out;
   float* lse;                 // natural log, [Hq][Tq]; may be null
   int32_t Hq, Hkv, G, Tq, N, M, q_off, out_dtype;
+  int32_t n_cus;              // compute units of the device (the launch rule's)
   float scale_log2;
   int64_t q_st, q_sh, k_sh, k_sl, o_st, o_sh;
 };

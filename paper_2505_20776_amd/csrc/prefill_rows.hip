@@ -477,12 +477,11 @@ hipError_t launch_key_groups(const PrefillParams& p, hipStream_t stream) {
 // KV heads: 512 new tokens behind 15851 374 / 206 / 156; 1024 behind 7168 191 / 129 / 146; 2048 behind 6144 225 / 229 /
 // 272; whole prompts of 512 18.3 / 13.4 / 9.8, of 1024 30.5 / 21.2 / 20.2, of 2048 56 / 45 / 54, of 4096 133 / 147 / 174.
 hipError_t launch_prefill_rows(const PrefillParams& p, hipStream_t stream) {
-  constexpr int kCus = 256;
   const int rows = kWaves * 32;
   const int groups = (p.M + rows - 1) / rows;
   const float longest = static_cast<float>((p.N + kTile - 1) / kTile);
   const float shortest = static_cast<float>((p.q_off + (rows + p.G - 1) / p.G + kTile - 1) / kTile);
-  const float share = static_cast<float>(p.Hkv) * groups * 0.5f * (longest + (shortest < longest ? shortest : longest)) / kCus;
+  const float share = static_cast<float>(p.Hkv) * groups * 0.5f * (longest + (shortest < longest ? shortest : longest)) / p.n_cus;
   auto periods = [&](int kg) { return longest / kg > share ? longest / kg : share; };
   if (1.15f * periods(2) >= periods(1)) return launch_key_groups<1>(p, stream);
   return 1.2f * periods(4) >= periods(2) ? launch_key_groups<2>(p, stream) : launch_key_groups<4>(p, stream);
