@@ -573,7 +573,8 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 #pragma unroll
     for (int u = 0; u < kAnc; ++u) {
       const float pr = anc[u] >= 0 ? fast_exp2(sc[u] - new_max) : 0.f;
-      if (anc[u] < 0) vraw[u] = RowWords{};        // the row read in place of an ancestor that there is not may be infinite
+      // the row read in place of an ancestor that there is not may be infinite (fp16 partials hold no infinite V anyway)
+      if (!PART_F16 && anc[u] < 0) vraw[u] = RowWords{};
 #pragma unroll
       for (int e = 0; e < E; ++e) o[e] = fmaf(pr, row_element<IN_BF16>(vraw[u], e), o[e]);
       run_sum += pr;
