@@ -118,7 +118,9 @@ const char* specext_strerror(int status);
 /*
  * Upper bound, in bytes, of the workspace specext_verify_attn needs for this
  * descriptor (split partials, final log-sum-exp, chunk partial sums when
- * want_scores, and the status word).  Returns 0 for an invalid descriptor.
+ * want_scores, and the status word).  Returns 0 for an invalid descriptor.  The size
+ * follows from the kernels that this build of the library chooses (8 bytes per query row
+ * and score block, for one): ask for it, rather than keep one from another build.
  * Host-only; needs a visible GPU only when num_splits == 0 (to read the
  * compute-unit count).
  */
@@ -154,8 +156,8 @@ int specext_workspace_init(void* workspace, size_t workspace_bytes, void* stream
  * Pointers must be 16-byte aligned and strides multiples of 8 elements.
  * Arithmetic: logits, softmax statistics and the P V sums are fp32 (P and V enter the
  * matrix cores as bf16; as fp32 with fp32 inputs, and P as an exact sum of three bf16
- * terms where bf16 inputs take the kernel with fp32 probabilities).  With bf16 inputs, head_dim 128 and more than 32 rows per KV
- * head the per-split partial outputs cross memory as fp16 after a per-row power-of-two
+ * terms where bf16 inputs take the kernel with fp32 probabilities).  With bf16 inputs,
+ * head_dim 128 and more than 32 rows per KV head the per-split partial outputs cross memory as fp16 after a per-row power-of-two
  * rescale (11 bits against the row's largest element, whatever the scale of V); the
  * rescale exponent travels in the split's softmax reference, so the magnitudes of V
  * must stay within 2^-100 ... 2^100 and those of two splits of one row within a factor
@@ -326,9 +328,11 @@ int specext_chunk_scores_accepted(const specext_desc* desc, const void* workspac
 
 /*
  * specext_chunk_scores for one tree row followed by specext_select_chunks over that
- * row's scores (Sec. 3.2.1; SelectChunks of Alg. 1), in one launch when there are at most
- * 1024 chunks (two launches beyond that).  Same scores and the same selection, bit for
- * bit, as the two calls.
+ * row's scores (Sec. 3.2.1; SelectChunks of Alg. 1): in one launch while one compute unit
+ * takes in the row's partial sums faster than a second launch costs (n_kv_heads times the
+ * score blocks up to 3000; a block is 32 keys for the kernels with bf16 probabilities, else
+ * 4, 8 or 16) and there are at most 1024 chunks, and always when scores is NULL; else in two.
+ * Same scores and the same selection, bit for bit, as the two calls.
  *
  *   desc, workspace   as for specext_chunk_scores
  *   score_row         the tree row when path is NULL (0 <= score_row < n_tree); else the

@@ -116,7 +116,7 @@ int resolve(const specext_desc* d, AttnParams* p) {
   // keys of a head contiguous in memory and at least one 64-key tile
   const bool mfma64_ok = mfma_common && p->d == 64 && p->kp_sl == 64 && p->L >= 64;
   // Everything else of bf16 and all of fp32: the matrix-core kernel with fp32 probabilities, unless the chunks are no
-  // whole numbers of its four-key score blocks or a query or key stride leaves its 32-bit offsets within a tile.
+  // whole numbers of its four-key score blocks or a key stride leaves its 32-bit offsets within a tile.
   const bool f32_ok = (!p->want_scores || p->B % 4 == 0) && !(d->flags & SPECEXT_FLAG_VALU_PREFIX) && p->kp_sl <= (1 << 22);
   if (mfma64_ok) {
     p->use_mfma = 2;
@@ -137,9 +137,10 @@ int resolve(const specext_desc* d, AttnParams* p) {
   p->n_sub = p->want_scores ? (p->L + p->score_gran - 1) / p->score_gran : 0;
 
   // Split the prefix.  Every split but the last holds keys_per_split keys: a
-  // multiple of the kernel's key granule (4 waves x 32 keys on the matrix-core
-  // path, 64 otherwise) and, with scores, of the chunk size, so that no chunk
-  // is shared by two splits.
+  // multiple of the kernel's key granule (128: 4 waves x 32 keys in the key-split
+  // kernel, a stage of bf16 keys in the fp32-probability one; else 64) and, with
+  // scores, of the chunk size, so that no chunk is shared by two splits (except
+  // in the fp32-probability kernel, below).
   if (p->L == 0) {
     p->S = 0;
     p->keys_per_split = 128;
@@ -436,7 +437,7 @@ int specext_chunk_scores_select(const specext_desc* desc, const void* workspace,
       (reinterpret_cast<uintptr_t>(path) & 3u) || (reinterpret_cast<uintptr_t>(n_accept) & 3u) ||
       (reinterpret_cast<uintptr_t>(idx_out) & 3u) || (reinterpret_cast<uintptr_t>(n_out) & 3u))
     return SPECEXT_ERR_UNSUPPORTED;
-  // beyond what one workgroup ranks, the two steps run as two launches and need the scores in memory
+  // beyond what one workgroup ranks with a key per thread, the two steps run as two launches and need the scores in memory
   if (p.C > 1024 && !scores) return SPECEXT_ERR_INVALID_ARG;
   const WorkspaceLayout w = layout_of(p);
   if (workspace_bytes < w.total) return SPECEXT_ERR_WORKSPACE_TOO_SMALL;

@@ -105,7 +105,7 @@ hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream);
 // row_path[*row_count - 1] (row 0 when *row_count <= 0)
 hipError_t launch_chunk_scores(const AttnParams& p, int32_t score_row, const int32_t* row_path,
                                const int32_t* row_count, float* scores, hipStream_t stream);
-// chunk scores of one row and their top-k in one launch; needs p.C <= 1024
+// chunk scores of one row and their top-k, in one launch or (scores given, many score blocks) in two; needs p.C <= 1024
 hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int32_t* row_path,
                                const int32_t* row_count, int32_t k, float* scores, int32_t* idx_out, int32_t* n_out,
                                hipStream_t stream);

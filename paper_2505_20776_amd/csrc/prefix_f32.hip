@@ -8,13 +8,17 @@
 // heads per group is matrix-bound (0.12 us of K/V traffic per us of matrix work), everything
 // else - softmax, LDS reads, loads - fits beside it.  One thread per query row on the vector
 // ALUs, which this replaces, left three of a compute unit's four SIMDs idle and read every K/V
-// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 29 us
-// (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first tile, 4.3 us, the
-// workgroup's own merge and stores, 4 us, and 20 % of the loop).
+// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 27 us, 30
+// under the profiler (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first
+// tile, 4.3 us, the workgroup's own merge and stores, 4 us, and 20 % of the loop).
 // With bf16 inputs Q K^T is exact in bf16 products, and the probabilities go into P V as three
 // bf16 terms whose sum is the fp32 value (8 + 8 + 8 mantissa bits), so that nothing is rounded
 // and the product runs at a third of the bf16 rate instead of the fp32 one's sixteenth (4109
-// keys, 60 nodes: 6250 us before, 19 us here).
+// keys, 60 nodes: 6250 us before, 18 us here, 21 under the profiler).
+// The range is that of plain fp32 attention but for |V| near its end (the lagging reference lets
+// P reach 2^10: an exact running maximum takes 28.4 instead of 27.1 us at 2K and 86 instead of
+// 79.5 at 8K): infinite V, logits of minus infinity, of any finite size and scales of any size
+// are answered; scaling the queries for that costs 0.2 - 0.5 us of prologue.
 //
 // Shape.  A workgroup owns 16 * NSUB * RB query rows of one KV head and one split of the keys.
 // Its waves form RB row groups x KG key groups: the key groups take the split's tiles in turns
@@ -24,7 +28,8 @@
 //   stage   KG tiles, one workgroup barrier; the ring in LDS holds 128 KB of stages (two of
 //           64 KB, four for head_dim 64), requested ahead by direct global->LDS loads
 // Workgroups of 128 rows with two key groups (half as many reads of every key, twice the partial
-// outputs) measured slower: 32 against 29 us (fp32, 2K), 20.0 against 18.7 us (bf16, 4109).
+// outputs) measured slower under the profiler: 32 against 29 us (fp32, 2K), 20.0 against 18.7 us
+// (bf16, 4109).
 // Matrix-core mapping, transposed so that a lane owns one query row (l & 15) in both products:
 //   S^T[key][row]   = K Q^T     A = K rows from LDS, B = Q in registers.  The contraction index
 //                               is permuted alike on both sides: a lane quarter (l >> 4) takes
