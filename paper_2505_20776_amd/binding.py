@@ -68,6 +68,12 @@ def load_library() -> ctypes.CDLL:
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2505_20776_amd.build` "
                           "(there is no fallback implementation)")
+    # torch may bring a HIP runtime of its own.  Loaded first, it is the one that the library binds to; behind the library there
+    # would be two runtimes in the process, and a stream or tensor of one is no object of the other (a crash in the first call).
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        pass
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     dp = ctypes.POINTER(specext_desc)

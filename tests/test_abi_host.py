@@ -199,3 +199,14 @@ def test_calibration_argument_checks(sx):
     assert lib.specext_calib_mfma(0, 32, 1, None, None) == invalid
     assert lib.specext_calib_mfma(10, 24, 1, None, None) == invalid
     assert lib.specext_calib_stream_read(None, 32768, None, None) == invalid
+
+
+def test_one_hip_runtime_whatever_is_loaded_first():
+    """The library loaded before torch: both use the same HIP runtime."""
+    import subprocess
+    import sys
+    code = ("import paper_2505_20776_amd as sx; sx.load_library(); import torch; "
+            "print(len({l.split()[-1] for l in open('/proc/self/maps') if 'libamdhip64' in l}))")
+    run = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                         stdout=subprocess.PIPE, text=True, timeout=250)
+    assert run.returncode == 0 and run.stdout.split()[-1] == "1"
