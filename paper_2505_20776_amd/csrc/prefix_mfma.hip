@@ -89,11 +89,6 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(AttnParams p) 
       qf[rb][ks] = __builtin_bit_cast(bf16x8, w);
     }
   }
-  // All query loads have landed before the main loop starts; said through the builtin
-  // so that the compiler's own wait bookkeeping sees it and adds no vmcnt wait of its
-  // own inside the loop (0x0F70 = vmcnt(0), other counters untouched).
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-
   // ---- per-wave LDS staging: a ring of 3 K tiles and a ring of 2 V tiles, each
   // tile 32 rows x 256 B, filled by direct global->LDS loads: one load instruction
   // writes 1 KB = 4 consecutive rows, lane i landing at byte 16*i.  The 16-byte
@@ -287,6 +282,13 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(AttnParams p) 
       issue_v(1);
     }
     if (n > 2) issue_k(2);
+    // The queries, requested before all these, have landed when no more than these are pending: they and the first keys
+    // share one trip to memory (2048 keys, 8 nodes: 7.2 us with a wait of their own before the first key is requested, 6.9 so;
+    // 65536 keys 49.9 and 49.1, 8192 keys 11.6 and 11.8).  Said through the builtin so that the compiler's own wait bookkeeping sees it and adds no
+    // vmcnt wait of its own inside the loop (vmcnt(16), (32), (40); other counters untouched).
+    if (n > 2) __builtin_amdgcn_s_waitcnt(0x8F78);
+    else if (n > 1) __builtin_amdgcn_s_waitcnt(0x8F70);
+    else __builtin_amdgcn_s_waitcnt(0x4F70);
     wait_vm_groups(1 + (n > 1 ? 2 : 0) + (n > 2 ? 1 : 0));     // K0 landed
     read_k(0);
     qk(s_v);
