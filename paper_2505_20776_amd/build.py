@@ -1,4 +1,4 @@
-"""Build libspecext.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Build libspecext.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python side's argument marshalling, in-tree."""
 from __future__ import annotations
 
 import os
@@ -32,6 +32,29 @@ def hipcc_path() -> str:
 STAMPS_LIB_PATH = os.path.join(PKG_DIR, "libspecext_stamps.so")
 
 
+MARSHAL_PATH = os.path.join(PKG_DIR, "_marshal.so")
+
+
+def _marshal_command(out: str):
+    """Host code only: the host compiler, against Python's and torch's headers; torch's libraries are those already loaded."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    cxx = next((c for c in (os.environ.get("CXX"), shutil.which("g++"), shutil.which("c++"), "/opt/rocm/llvm/bin/clang++")
+                if c and (os.path.exists(c) or shutil.which(c))), None)
+    if cxx is None:
+        raise RuntimeError("no C++ compiler found (set CXX)")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+    includes = include_paths() + [sysconfig.get_paths()["include"], os.path.join(rocm, "include"), "/opt/rocm/include"]
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return ([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w", "-D__HIP_PLATFORM_AMD__=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            + [a for i in includes if os.path.isdir(i) for a in ("-isystem", i)]
+            + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10",
+               "-lc10_hip"])
+
+
 def build_library(verbose: bool = True, stamps: bool = False) -> str:
     """Compile every HIP source for gfx950 and link libspecext.so next to this file.
     stamps=True builds the profiling variant libspecext_stamps.so instead (-DSPECEXT_TAIL_STAMPS: the row-split
@@ -52,6 +75,10 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
         objs.append(obj)
         procs.append((src, subprocess.Popen(common + EXTRA_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj],
                                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    marshal_tmp = MARSHAL_PATH + ".tmp"
+    if not stamps:
+        procs.append(("marshal.cpp", subprocess.Popen(_marshal_command(marshal_tmp), stdout=subprocess.PIPE,
+                                                      stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, pr in procs:
         out, _ = pr.communicate()
@@ -66,6 +93,8 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
     tmp = lib_path + ".tmp"
     subprocess.run([hipcc_path(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, lib_path)
+    if not stamps:
+        os.replace(marshal_tmp, MARSHAL_PATH)
     return lib_path
 
 
