@@ -146,6 +146,18 @@ int resolve(const specext_desc* d, AttnParams* p) {
     p->keys_per_split = 128;
     return SPECEXT_OK;
   }
+  // Automatic split count of a short prefix in the bf16 kernels: eight key tiles per split, four while that keeps the count
+  // at 16 or below (measured at 1K - 8K tokens: more splits shorten the prefix kernel by less than they add to the merge,
+  // fewer leave most compute units idle).
+  const int by_256 = static_cast<int>((p->L + 255) / 256), by_128 = static_cast<int>((p->L + 127) / 128);
+  const int by_len = by_256 > (by_128 < 16 ? by_128 : 16) ? by_256 : (by_128 < 16 ? by_128 : 16);
+  // With so few splits that workgroups of 128 rows still fit the device at once, the row-split kernel takes those: twice as
+  // many compute units, and a wave has its SIMD to itself.  Every K/V byte then enters two compute units, of one XCD where
+  // the KV head is the fastest grid index.  Prefix launch with 256 / with 128 rows, 60 nodes, 32 heads in 8 groups, us:
+  // 1K keys 7.5 / 6.75, 2K 7.8 / 7.1, 3K 9.2 / 8.3, 4K 11.5 / 10.3.
+  if (p->use_mfma == 2 && p->rows_per_group == 256 && d->num_splits == 0 &&
+      static_cast<int64_t>(by_len) * p->Hkv * ((p->M + 127) / 128) <= device_cu_count())
+    p->rows_per_group = 128;
   // (the fp32-probability kernel keeps the reference of every score block beside its sum, so a chunk may lie in two splits
   // and a split is cut at whole stages of its four key groups)
   int64_t unit = p->use_mfma == 1 ? 128 : 64;
@@ -157,11 +169,6 @@ int resolve(const specext_desc* d, AttnParams* p) {
     const int cus = device_cu_count();
     const int row_groups = (p->M + p->rows_per_group - 1) / p->rows_per_group;
     want = cus / (p->Hkv * row_groups);
-    // short prefixes: eight key tiles per split, four while that keeps the split count at 16 or
-    // below (measured at 1K - 8K tokens: more splits shorten the prefix kernel by less than they
-    // add to the merge, fewer leave most compute units idle)
-    const int by_256 = static_cast<int>((p->L + 255) / 256), by_128 = static_cast<int>((p->L + 127) / 128);
-    const int by_len = by_256 > (by_128 < 16 ? by_128 : 16) ? by_256 : (by_128 < 16 ? by_128 : 16);
     // fp32-probability kernel: its matrix work per key is many times the merge's, so one stage per split is enough
     const int by_stage = static_cast<int>((p->L + unit - 1) / unit);
     const int most = p->use_mfma != 3 ? by_len : by_stage < 64 ? by_stage : 64;
