@@ -24,6 +24,27 @@ def test_selection_lengths(n):
             assert n_out == k and list(sel) == list(orc.select_chunks(s, k)), f"n={n} k={k}"
 
 
+@pytest.mark.parametrize("n_list,n_idx", [(1, 1), (63, 63), (64, 64), (65, 65), (65, 64), (130, 129), (64, 0), (64, 70)])
+def test_gather_lists_around_a_wave(n_list, n_idx):
+    """List entries from the 65th on are read in a second step; entries that contribute fewer or no tokens before and behind."""
+    from paper_2505_20776_amd import harness as hx
+    B, H, d = 9, 2, 64                      # 72 vectors of 16 bytes per chunk
+    C = 140
+    L = C * B - 4                           # the last chunk has five tokens
+    g = torch.Generator(device="cuda").manual_seed(n_list)
+    k = torch.randn((1, H, L, d), device="cuda", generator=g).to(torch.bfloat16)
+    v = torch.randn((1, H, L, d), device="cuda", generator=g).to(torch.bfloat16)
+    idx = np.random.default_rng(n_list).permutation(C)[:n_list].astype(np.int32)
+    idx[0] = C - 1
+    idx[n_list // 2] = -1 if n_list > 1 else C - 1
+    idx[-1] = C if n_list > 2 else idx[-1]
+    used = [int(c) for c in idx[:n_idx] if 0 <= c < C]
+    kd, vd, pos, length = hx.run_gather(k, v, idx, B, n_idx=n_idx)
+    rk, rv, rpos = orc.gather_draft_kv(k.float().cpu().numpy(), v.float().cpu().numpy(), np.array(used, dtype=np.int32), B)
+    assert length == len(rpos) and list(pos[:length]) == list(rpos) and (pos[length:] == -1).all()
+    assert (kd[:, :, :length].float().cpu().numpy() == rk).all() and (vd[:, :, :length].float().cpu().numpy() == rv).all()
+
+
 @pytest.mark.parametrize("Hq,Hkv,L,B", [
     (6, 3, 500, 32),          # 6 heads: two of four lanes have one head more; 16 chunks
     (36, 12, 545, 32),        # 36 heads: nine per lane, one past a round of eight; 18 chunks, the last of one token
