@@ -252,7 +252,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
 // kRadixMax with four (4096 scores of a 128K prefix: 25 us bit by bit as below, 8.2 us so).
 constexpr int kRankMax = 1024;
 constexpr int kRadixMax = 4 * kSelThreads;
-constexpr int kScoreGroupsOneLaunch = 3000;
+constexpr int kScoreGroupsOneLaunch = 1200;
+constexpr int kScoreChunksOneLaunch = 128;
 
 // One workgroup (blockDim.x a multiple of 64), thread i holding the scores of chunks i, i + blockDim.x, ... (KPT of
 // them).  The key of the k-th largest score is found a byte at a time from the top:
@@ -287,6 +288,30 @@ __device__ __forceinline__ void radix_select_and_write(const float (&score)[KPT]
   for (int v = 0; v < KPT; ++v) {
     live[v] = i + v * static_cast<int>(blockDim.x) < n;
     key[v] = live[v] ? orderable(score[v]) : 0u;
+  }
+  // Up to a wave of scores: every lane counts the keys above its own, no barrier and no LDS.  Scores and selection of one row
+  // in one launch, 16 chunks 4.3 us with the rounds below, 2.9 so; 64 chunks 4.4 and 3.4.
+  if (KPT == 1 && n <= 64) {
+    if (wave > 0) return;
+    int above = 0;                       // keys larger than this lane's
+#pragma unroll
+    for (int q = 0; q < 64; q += 16)
+      if (q < n) {                       // lanes behind the last score hold zero, which is above nothing
+#pragma unroll
+        for (int j = q; j < q + 16; ++j) above += static_cast<uint32_t>(__builtin_amdgcn_readlane(key[0], j)) > key[0] ? 1 : 0;
+      }
+    bool take = live[0] && above < k_eff;
+    const uint64_t most = __ballot(take);
+    if (__popcll(most) > k_eff) {
+      // the smallest keys of these are equal, and not all of them fit: the lowest-indexed ones do
+      int last = -1;
+      for (uint64_t rest = most; rest; rest &= rest - 1) last = max(last, __builtin_amdgcn_readlane(above, __builtin_ctzll(rest)));
+      const uint64_t ties = __ballot(take && above == last);
+      if (above == last) take = take && __popcll(ties & ((uint64_t{1} << lane) - 1)) < k_eff - last;
+    }
+    const uint64_t taken = __ballot(take);
+    if (take) idx_out[__popcll(taken & ((uint64_t{1} << lane) - 1))] = lane;
+    return;
   }
   for (int u = i; u < 4 * 256; u += blockDim.x) (&sh.hist[0][0])[u] = 0;
   __syncthreads();
@@ -520,11 +545,12 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
                                const int32_t* row_count, int32_t k, float* scores, int32_t* idx_out, int32_t* n_out,
                                hipStream_t stream) {
   if (p.C > kRankMax) return hipErrorInvalidValue;
-  // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 3000 on, a launch of its
-  // own for the scores, which every compute unit shares, is the shorter way also for a caller whom the host bounds and a second
-  // launch costs 1.5 - 2 us.  Measured on the device, us in one launch / in two: 512 groups 4.2 / 5.9, 2048 6.7 / 5.8, 3000
-  // 7.7 / 6.1, 4096 9.2 / 6.2, 8192 14.7 / 7.3 (32-key chunks; 10.6 / 6.6 in 64-key chunks).
-  if (scores && static_cast<int64_t>(p.Hkv) * p.n_sub > kScoreGroupsOneLaunch) {
+  // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 1200 on, and from 128 chunks
+  // on, a launch of its own for the scores, which every compute unit shares, is the shorter way.  Measured on the device, us
+  // in one launch / in two: 8 KV heads, 32-key chunks, 64 chunks 3.3 / 4.6, 65 4.9 / 5.8, 128 5.3 / 5.9, 150 6.6 / 6.0, 256
+  // 7.4 / 5.9; 64 chunks of two blocks 4.0 / 5.0, 100 6.3 / 6.3; 2 KV heads, 512 chunks 9.4 / 6.2; 32 KV heads, 32 chunks
+  // 3.5 / 4.3, 64 5.4 / 4.6.
+  if (scores && (p.C > kScoreChunksOneLaunch || static_cast<int64_t>(p.Hkv) * p.n_sub > kScoreGroupsOneLaunch)) {
     const hipError_t e = launch_chunk_scores(p, score_row, row_path, row_count, scores, stream);
     return e != hipSuccess ? e : launch_select_chunks(scores, p.C, k, idx_out, n_out, stream);
   }

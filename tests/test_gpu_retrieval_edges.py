@@ -24,6 +24,21 @@ def test_selection_lengths(n):
             assert n_out == k and list(sel) == list(orc.select_chunks(s, k)), f"n={n} k={k}"
 
 
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 32, 48, 49, 63, 64, 65])
+def test_selection_within_one_wave(n):
+    """Up to 64 scores are ranked all against all in steps of 16; ties that fit whole, in part and not at all."""
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(n)
+    two = np.where(rng.random(n) < 0.5, np.float32(0.25), np.float32(0.75)).astype(np.float32)
+    mixed = np.where(rng.random(n) < 0.3, rng.random(n), 0.5).astype(np.float32)
+    for s in (rng.standard_normal(n).astype(np.float32), two, mixed, np.zeros(n, np.float32), -np.abs(rng.standard_normal(n)).astype(np.float32),
+              np.arange(n, dtype=np.float32), np.arange(n, dtype=np.float32)[::-1].copy()):
+        for k in range(0, n + 3):
+            sel, n_out, raw = hx.run_select(s, k)
+            assert n_out == min(k, n) and list(sel) == list(orc.select_chunks(s, k)), f"n={n} k={k}"
+            assert (raw[n_out:] == -1).all()
+
+
 @pytest.mark.parametrize("n_list,n_idx", [(1, 1), (63, 63), (64, 64), (65, 65), (65, 64), (130, 129), (64, 0), (64, 70)])
 def test_gather_lists_around_a_wave(n_list, n_idx):
     """List entries from the 65th on are read in a second step; entries that contribute fewer or no tokens before and behind."""
@@ -46,6 +61,9 @@ def test_gather_lists_around_a_wave(n_list, n_idx):
 
 
 @pytest.mark.parametrize("Hq,Hkv,L,B", [
+    (32, 8, 4096, 32),        # 128 chunks, 1024 groups: one launch
+    (32, 8, 4097, 32),        # 129 chunks: two
+    (32, 8, 4864, 64),        # 76 chunks, 1216 groups: two
     (6, 3, 500, 32),          # 6 heads: two of four lanes have one head more; 16 chunks
     (36, 12, 545, 32),        # 36 heads: nine per lane, one past a round of eight; 18 chunks, the last of one token
     (8, 2, 3000, 96),         # three blocks per chunk
