@@ -82,7 +82,7 @@ __device__ __forceinline__ float rows16_max(float v) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-template <int D, bool BF16, int NSUB, int RB, bool SCORES>
+template <int D, bool BF16, int NSUB, int RB, int SCORES>
 __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) {
   using T = Tile<D, BF16>;
   constexpr int kStageBytes = KG * 2 * T::kBytes;
@@ -186,6 +186,8 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
   }
   const float c = p.scale_log2 * __uint_as_float(static_cast<uint32_t>(127 - scale_exp) << 23);      // what is left of the scale
   const int gran_log2 = __builtin_ctz(p.score_gran);
+  // of block 0 and this lane's first row
+  float* score_row = SCORES == 2 ? p.chunk_part + (static_cast<int64_t>(g) * p.n_sub * p.M + row0 + li) * 2 : nullptr;
   bool far = false;                    // some reference of this wave is beyond kFarLog2
 
   // A tile in three parts: the logits (and the V fragments: all that reads the ring), the softmax, the second product (from
@@ -326,7 +328,12 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
         for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(s_acc[s][u][i]);
         float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
         run_sum[s] += part;
-        if (SCORES) {
+        if constexpr (SCORES == 2) {
+          // blocks of 16 keys, the usual case: no choices
+          part = halves_sum(rows16_sum(part));
+          if (16 * u < left && qt == 0 && row0 + 16 * s + li < p.M)
+            *reinterpret_cast<floatx2*>(score_row + (static_cast<int64_t>(key0 / 16 + u) * p.M + 16 * s) * 2) = floatx2{part, ref[s]};
+        } else if constexpr (SCORES == 1) {
           // one (sum, reference) pair per score_gran keys: 4 (a lane quarter), 8 or 16
           if (p.score_gran >= 8) part = rows16_sum(part);
           if (p.score_gran >= 16) part = halves_sum(part);
@@ -465,7 +472,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) 
   }
 }
 
-template <int D, bool BF16, int NSUB, int RB, bool SCORES>
+template <int D, bool BF16, int NSUB, int RB, int SCORES>
 hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   using T = Tile<D, BF16>;
   constexpr int kWaves = RB * KG;
@@ -495,7 +502,13 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
 
 template <int D, bool BF16, int NSUB, int RB>
 hipError_t launch_shape(const AttnParams& p, hipStream_t stream) {
-  return p.want_scores ? launch_one<D, BF16, NSUB, RB, true>(p, stream) : launch_one<D, BF16, NSUB, RB, false>(p, stream);
+  if (!p.want_scores) return launch_one<D, BF16, NSUB, RB, 0>(p, stream);
+  // 64-row workgroups have a form for 16-key score blocks (chunks that are a multiple of 16 keys) without the run-time choices
+  // and the 64-bit address of every pair: bf16 8K in 32 rows x 2, chunks of 16, 28.4 -> 27.6 us, fp32 8K 80.4 -> 79.7; with
+  // fewer rows there are too few tiles to pay for its prologue (toy 5.5 -> 5.6).
+  if constexpr (RB == 2)
+    if (p.score_gran == 16) return launch_one<D, BF16, NSUB, RB, 2>(p, stream);
+  return launch_one<D, BF16, NSUB, RB, 1>(p, stream);
 }
 
 template <int D, bool BF16>
