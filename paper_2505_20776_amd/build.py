@@ -65,6 +65,7 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
     common = [
         hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+        "-mllvm", "-amdgpu-kernarg-preload-count=14",        # a kernel's first arguments in registers at its start (csrc/common.h)
         "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
     ] + (["-DSPECEXT_TAIL_STAMPS"] if stamps else [])
     lib_path = STAMPS_LIB_PATH if stamps else LIB_PATH

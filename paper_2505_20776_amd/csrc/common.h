@@ -125,6 +125,17 @@ hipError_t launch_gather(const void* k_src, const void* v_src, void* k_dst, void
                          int32_t src_len, int32_t src_cap, int32_t dst_cap, int32_t row_bytes,
                          int32_t chunk_size, int32_t* pos_out, int32_t* len_out, hipStream_t stream);
 
+// Kernel arguments.  The first 14 dwords of a kernel's scalar arguments are in registers when a wave starts (the build asks for
+// it, -amdgpu-kernarg-preload-count); what lies behind them, every struct, and the launch's dimensions take a scalar load
+// first, 0.2 us of a launch that waits for it.  So what a kernel needs for its first trip to memory comes first, as scalars,
+// and a problem's other parameters behind in AttnParams.  Where nothing is lost by it, addresses are passed as integers: the
+// runtime looks every pointer argument up in its list of allocations (0.03 - 0.1 us of host time each).
+inline uint64_t address_of(const void* p) { return reinterpret_cast<uintptr_t>(p); }
+template <class T>
+__device__ __forceinline__ T* in_global(uint64_t address) {
+  return (T*)(__attribute__((address_space(1))) T*)address;
+}
+
 // bf16 helpers (bit-level; round to nearest even on the way down)
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) {
   return __uint_as_float(static_cast<uint32_t>(b) << 16);

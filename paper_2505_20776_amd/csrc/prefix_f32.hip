@@ -83,7 +83,12 @@ __device__ __forceinline__ float rows16_max(float v) {
 }
 
 template <int D, bool BF16, int NSUB, int RB, int SCORES>
-__global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(AttnParams p) {
+__global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at, uint64_t v_at, uint64_t q_at, int64_t kp_sh, int L, int keys_per_split, int M, int G,
+                                                            int kp_sl, int head_fastest, AttnParams p) {
+  p.kp = in_global<const void>(k_at);
+  p.vp = in_global<const void>(v_at);
+  p.q = in_global<const void>(q_at);
+  p.kp_sh = kp_sh, p.L = L, p.keys_per_split = keys_per_split, p.M = M, p.G = G, p.kp_sl = kp_sl, p.head_fastest = head_fastest;
   using T = Tile<D, BF16>;
   constexpr int kStageBytes = KG * 2 * T::kBytes;
   constexpr int kStages = stages_of(kStageBytes);
@@ -496,7 +501,8 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   }
   const int rows_per_wg = 16 * NSUB * RB;
   dim3 grid(p.head_fastest ? p.Hkv : p.S, p.head_fastest ? p.S : p.Hkv, (p.M + rows_per_wg - 1) / rows_per_wg);
-  kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(p);
+  kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L, p.keys_per_split, p.M, p.G,
+                                                             static_cast<int>(p.kp_sl), p.head_fastest, p);
   return hipGetLastError();
 }
 

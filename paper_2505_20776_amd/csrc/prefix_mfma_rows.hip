@@ -80,7 +80,12 @@ __device__ __forceinline__ void static_for(F&& f) {
 // K fragments against the same four query fragments, and the even / odd probabilities
 // meet V^T's first / second pair of 32-column blocks in the same two output blocks.
 template <int WAVES, bool SCORES, int KPR, int STAGES>
-__global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(AttnParams p) {
+__global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, uint64_t v_at, uint64_t q_at, int64_t kp_sh, int L, int keys_per_split, int M, int G,
+                                                            int kp_sl, int head_fastest, AttnParams p) {
+  p.kp = in_global<const void>(k_at);
+  p.vp = in_global<const void>(v_at);
+  p.q = in_global<const void>(q_at);
+  p.kp_sh = kp_sh, p.L = L, p.keys_per_split = keys_per_split, p.M = M, p.G = G, p.kp_sl = kp_sl, p.head_fastest = head_fastest;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int kStages = STAGES;
   constexpr int kRing = kStageTiles * kStages;            // tiles per ring (K ring and V ring)
@@ -619,7 +624,8 @@ hipError_t launch_rows(const AttnParams& p, hipStream_t stream) {
   }
   const int rows_per_wg = WAVES * 32;
   dim3 grid(p.head_fastest ? p.Hkv : p.S, p.head_fastest ? p.S : p.Hkv, (p.M + rows_per_wg - 1) / rows_per_wg);
-  kernel<<<grid, dim3(WAVES * 64), kLdsBytes, stream>>>(p);
+  kernel<<<grid, dim3(WAVES * 64), kLdsBytes, stream>>>(address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L, p.keys_per_split, p.M, p.G,
+                                                             static_cast<int>(p.kp_sl), p.head_fastest, p);
   return hipGetLastError();
 }
 

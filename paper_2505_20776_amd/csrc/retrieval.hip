@@ -435,12 +435,12 @@ __device__ __forceinline__ int chunk_tokens(int c, int n_chunks, int src_len, in
 // behind one another and a workgroup-wide sum, 32 chunks of 32 tokens of 8 heads (4 MB of cold bf16 rows) took 4.7 us, this 4.2;
 // of 32 heads 7.2 and 6.6; four chunks of one fp32 head 2.8 and 2.5.
 constexpr int kGatherAtOnce = 4;
-__global__ __launch_bounds__(256) void gather_copy_kernel(const uint4* __restrict__ k_src, const uint4* __restrict__ v_src,
+constexpr int kGatherThreads = 256;
+__global__ __launch_bounds__(kGatherThreads) void gather_copy_kernel(const int* __restrict__ idx, const int* __restrict__ n_idx, int max_idx,
+                                                         int src_len, int chunk_size, int row_vecs, int src_cap, int dst_cap,
+                                                         const uint4* __restrict__ k_src, const uint4* __restrict__ v_src,
                                                          uint4* __restrict__ k_dst, uint4* __restrict__ v_dst,
-                                                         const int* __restrict__ idx, const int* __restrict__ n_idx,
-                                                         int max_idx, int src_len, int src_cap, int dst_cap,
-                                                         int row_vecs, int chunk_size, int* __restrict__ pos_out,
-                                                         int* __restrict__ len_out) {
+                                                         int* __restrict__ pos_out, int* __restrict__ len_out) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x;
   int c = idx[r], first = idx[min(lane, max_idx - 1)];
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void gather_copy_kernel(const uint4* __restric
   if (book && r == 0) {
     const int total = tokens_of(n_used);
     if (pos_out)
-      for (int i = total + threadIdx.x; i < dst_cap; i += blockDim.x) pos_out[i] = -1;
+      for (int i = total + threadIdx.x; i < dst_cap; i += kGatherThreads) pos_out[i] = -1;
     if (len_out && threadIdx.x == 0) *len_out = total;
   }
   if (r >= n_used) return;
@@ -470,16 +470,16 @@ __global__ __launch_bounds__(256) void gather_copy_kernel(const uint4* __restric
   const uint4* src = (blockIdx.z == 0 ? k_src : v_src) + (lh * src_cap + static_cast<int64_t>(c) * chunk_size) * row_vecs;
   uint4* dst = (blockIdx.z == 0 ? k_dst : v_dst) + (lh * dst_cap + dst_tok) * row_vecs;
   const int n_vecs = tokens * row_vecs;
-  for (int i0 = threadIdx.x; i0 < n_vecs; i0 += kGatherAtOnce * 256) {
+  for (int i0 = threadIdx.x; i0 < n_vecs; i0 += kGatherAtOnce * kGatherThreads) {
     uint4 v[kGatherAtOnce];
 #pragma unroll
-    for (int u = 0; u < kGatherAtOnce; ++u) v[u] = src[min(i0 + u * 256, n_vecs - 1)];      // past the end: the last one again, unused
+    for (int u = 0; u < kGatherAtOnce; ++u) v[u] = src[min(i0 + u * kGatherThreads, n_vecs - 1)];      // past the end: the last one again, unused
 #pragma unroll
     for (int u = 0; u < kGatherAtOnce; ++u)
-      if (i0 + u * 256 < n_vecs) dst[i0 + u * 256] = v[u];
+      if (i0 + u * kGatherThreads < n_vecs) dst[i0 + u * kGatherThreads] = v[u];
   }
   if (book && pos_out)
-    for (int tk = threadIdx.x; tk < tokens; tk += blockDim.x) pos_out[dst_tok + tk] = c * chunk_size + tk;
+    for (int tk = threadIdx.x; tk < tokens; tk += kGatherThreads) pos_out[dst_tok + tk] = c * chunk_size + tk;
 }
 
 // The bookkeeping alone (an empty list or no (layer, head) to copy): original positions of
@@ -569,10 +569,9 @@ hipError_t launch_gather(const void* k_src, const void* v_src, void* k_dst, void
                          int32_t chunk_size, int32_t* pos_out, int32_t* len_out, hipStream_t stream) {
   if (max_idx > 0 && n_lh > 0) {
     dim3 grid(max_idx, n_lh, 2);
-    gather_copy_kernel<<<grid, dim3(256), 0, stream>>>(
-        static_cast<const uint4*>(k_src), static_cast<const uint4*>(v_src), static_cast<uint4*>(k_dst),
-        static_cast<uint4*>(v_dst), idx, n_idx, max_idx, src_len, src_cap, dst_cap, row_bytes / 16, chunk_size,
-        pos_out, len_out);
+    gather_copy_kernel<<<grid, dim3(kGatherThreads), 0, stream>>>(
+        idx, n_idx, max_idx, src_len, chunk_size, row_bytes / 16, src_cap, dst_cap, static_cast<const uint4*>(k_src),
+        static_cast<const uint4*>(v_src), static_cast<uint4*>(k_dst), static_cast<uint4*>(v_dst), pos_out, len_out);
     return hipGetLastError();
   }
   if (pos_out || len_out) {

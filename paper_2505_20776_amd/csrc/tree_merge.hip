@@ -395,7 +395,14 @@ __device__ __forceinline__ float row_element(const W& w, int e) {
 }
 
 template <int D, bool IN_BF16, bool PART_F16, int PER>
-__global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(AttnParams p) {
+__global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uint64_t parent_at, uint64_t ml_at, uint64_t o_at,
+                                                                             uint64_t q_at, int T, int Hq, int M, int G, int S,
+                                                                             AttnParams p) {
+  p.parent = in_global<const int32_t>(parent_at);
+  p.part_ml = in_global<float>(ml_at);
+  p.part_o = in_global<float>(o_at);
+  p.q = in_global<const void>(q_at);
+  p.T = T, p.Hq = Hq, p.M = M, p.G = G, p.S = S;
   constexpr int E = D / 16;                      // elements per lane: 8 or 4
   constexpr int PW = PART_F16 ? E / 2 : E;       // 32-bit words a lane holds per partial
   constexpr int RW = IN_BF16 ? E / 2 : E;        // and per K or V row
@@ -652,12 +659,14 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(Att
 template <int D, bool IN_BF16, bool PART_F16>
 void launch_shared(const AttnParams& p, dim3 grid, hipStream_t stream) {
   const dim3 block(kShareWaves * 64);
+#define SPECEXT_MERGE_ARGS address_of(p.parent), address_of(p.part_ml), address_of(p.part_o), address_of(p.q), p.T, p.Hq, p.M, p.G, p.S, p
   const int per = (p.S + kShareWaves - 1) / kShareWaves;       // splits per wave, rounded up to a power of two
-  if (per <= 1) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 1><<<grid, block, 0, stream>>>(p);
-  else if (per <= 2) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 2><<<grid, block, 0, stream>>>(p);
-  else if (per <= 4) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 4><<<grid, block, 0, stream>>>(p);
-  else if (per <= 8) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 8><<<grid, block, 0, stream>>>(p);
-  else tree_merge_shared_kernel<D, IN_BF16, PART_F16, 16><<<grid, block, 0, stream>>>(p);
+  if (per <= 1) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 1><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
+  else if (per <= 2) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 2><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
+  else if (per <= 4) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 4><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
+  else if (per <= 8) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 8><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
+  else tree_merge_shared_kernel<D, IN_BF16, PART_F16, 16><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
+#undef SPECEXT_MERGE_ARGS
 }
 
 }  // namespace
