@@ -82,17 +82,12 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
   bf16x8 qf[RB][8];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    const int m = row0 + 32 * rb + c32;
-    const bool ok = m < p.M;
-    const int t = ok ? m / p.G : 0;
-    const int h = g * p.G + (ok ? m % p.G : 0);
+    const int m = min(row0 + 32 * rb + c32, p.M - 1);           // padding rows repeat the last real row
+    const int t = m / p.G;
+    const int h = g * p.G + (m - t * p.G);
     const uint16_t* qp = static_cast<const uint16_t*>(p.q) + t * p.q_st + h * p.q_sh + 8 * hf;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      uintx4 w = {0u, 0u, 0u, 0u};
-      if (ok) w = *reinterpret_cast<const uintx4*>(qp + 16 * ks);
-      qf[rb][ks] = __builtin_bit_cast(bf16x8, w);
-    }
+    for (int ks = 0; ks < 8; ++ks) qf[rb][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(qp + 16 * ks));
   }
   // ---- per-wave LDS staging: a ring of 3 K tiles and a ring of 2 V tiles, each
   // tile 32 rows x 256 B, filled by direct global->LDS loads: one load instruction
@@ -245,12 +240,10 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
       }
       run_sum[rb] += part;
       if (SCORES) {
-        const float tot = part + __shfl_xor(part, 32, 64);
-        const int m = row0 + 32 * rb + c32;
-        if (hf == 0 && m < p.M) {
-          float* cp = p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + tile_key0(j) / kTile) * p.M + m) * 2;
-          *reinterpret_cast<floatx2*>(cp) = floatx2{tot, mc};
-        }
+        // every lane stores: the two lanes of a row hold the same pair, and so do padding rows
+        const float tot = halves_sum(part);
+        unsigned char* block = reinterpret_cast<unsigned char*>(p.chunk_part) + (static_cast<int64_t>(g) * p.n_sub + tile_key0(j) / kTile) * p.M * 8;
+        *reinterpret_cast<floatx2*>(block + static_cast<unsigned>(min(row0 + 32 * rb + c32, p.M - 1)) * 8u) = floatx2{tot, mc};
       }
       pf[rb][0] = pack8(s_v[rb], 0);
       pf[rb][1] = pack8(s_v[rb], 8);

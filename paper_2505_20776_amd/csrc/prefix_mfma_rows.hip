@@ -287,10 +287,15 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
   const float lazy_raw = kLazyLog2 / c;      // the lazy margin in raw-logit units
   const floatx16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // where this lane's (sum, reference) pair of tile j goes: score_base + j * score_step
-  float* score_base = nullptr;
-  const int score_step = p.M * 2;
-  if (SCORES) score_base = p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + key_lo / kTile) * p.M + min(m, p.M - 1)) * 2;
+  // Where a row's (sum, reference) pair of score block b of the split goes: score_base + b * score_step + score_off bytes.
+  // Every lane stores its pair, without a mask: the two lanes of a row hold the same one, and so do padding rows, which
+  // repeat the last real row.  A uniform base, a lane's fixed offset and no predicate leave one store and two scalar
+  // additions per tile; with a 64-bit address and three conditions per lane a launch took 26.2 instead of 24.7 us (32731
+  // keys, 16 nodes), 26.4 instead of 25.4 (8155 keys, 32 KV heads), 74 instead of 71 (32731 keys, 128 nodes), 10.3 instead of 9.7 (4K).
+  unsigned char* score_base = nullptr;
+  const int64_t score_step = static_cast<int64_t>(p.M) * 8;
+  const unsigned score_off = static_cast<unsigned>(min(m, p.M - 1)) * 8u;
+  if (SCORES) score_base = reinterpret_cast<unsigned char*>(p.chunk_part) + (static_cast<int64_t>(g) * p.n_sub + key_lo / kTile) * score_step;
 
   // One tile in two parts.  Front: the logits (matrix pipe) and the V^T fragments, everything
   // the tile needs from its ring slot SLOT.  Back: online softmax (vector ALU; one query row
@@ -392,9 +397,8 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
 #pragma unroll
       for (int b = 0; b < KPR; ++b) {
         const float tot = halves_sum(part[b]);
-        if (hf == 0 && m < p.M && key0 + b * kTile < key_hi) {
-          *reinterpret_cast<floatx2*>(score_base + (j * KPR + b) * score_step) = floatx2{tot, mc};
-        }
+        if (KPR == 1 || key0 + b * kTile < key_hi)
+          *reinterpret_cast<floatx2*>(score_base + (j * KPR + b) * score_step + score_off) = floatx2{tot, mc};
       }
     }
 #pragma unroll
