@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_rows_kernel(PrefillParams
     float mx = fmaxf(s[0], s[1]);
 #pragma unroll
     for (int r = 2; r < 16; r += 2) mx = fmaxf(mx, fmaxf(s[r], s[r + 1]));
-    if (__any(mx > ref + lazy_raw)) {     // some row of this wave outgrew its reference: move every reference up
+    if (__builtin_expect(__any(mx > ref + lazy_raw), 0)) {     // some row of this wave outgrew its reference: move every reference up
       mx = halves_max(mx);
       const float new_ref = fmaxf(ref, mx);
       // 0 on the first tile; with several key groups a row may not have seen any key yet
@@ -270,8 +270,8 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_rows_kernel(PrefillParams
       static_for<0, kStages>([&](auto u_c) {
         constexpr int u = decltype(u_c)::value;
         const int st = s0 + u;
-        if (st < n_stages) {
-          if (st > 0 && st + kStages - 2 < my_tiles) {
+        if (__builtin_expect(st < n_stages, 1)) {
+          if (__builtin_expect(st > 0 && st + kStages - 2 < my_tiles, 1)) {
             asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoadsPerStage * (kStages - 2)) : "memory");
           } else {
             wait_vmcnt_even(kLoadsPerStage * max(0, min(my_tiles - 1 - st, kStages - 2)));   // also covers the queries
@@ -291,20 +291,20 @@ __global__ __launch_bounds__(kWaves * 64) void prefill_rows_kernel(PrefillParams
             }
           };
           if ((KG == 1 || st == 0 || st > live_tiles) && more) issue_stage(ic<(u + kStages - 1) % kStages>{}, st + kStages - 1);
-          if (st == 0) {
+          if (__builtin_expect(st == 0, 0)) {
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks)
               qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const lds_uintx4*>(static_cast<uintptr_t>(q_lds + k_rd[ks])));
           }
           if constexpr (kUpper) {
-            if (st > 0 && st <= live_tiles) {
+            if (__builtin_expect(st > 0 && st <= live_tiles, 1)) {
               tile_softmax(st - 1);
               second_product(next);
             }
-            if (st < live_tiles) tile_front(ic<u>{});
+            if (__builtin_expect(st < live_tiles, 1)) tile_front(ic<u>{});
           } else {
-            if (st > 0 && st <= live_tiles) second_product(next);
-            if (st < live_tiles) {
+            if (__builtin_expect(st > 0 && st <= live_tiles, 1)) second_product(next);
+            if (__builtin_expect(st < live_tiles, 1)) {
               tile_front(ic<u>{});
               tile_softmax(st);
             }

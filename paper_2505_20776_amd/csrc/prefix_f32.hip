@@ -269,7 +269,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
     // online softmax; lane quarter qt holds keys 16 u + 4 qt + i of the tile
     const int key0 = key_lo + (st * KG + kg) * T::kKeys;
     const int left = key_hi - key0;
-    if (left < T::kKeys) {
+    if (__builtin_expect(left < T::kKeys, 0)) {
 #pragma unroll
       for (int u = 0; u < kSubTiles; ++u)
 #pragma unroll
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
       mx[s] *= c;
       grow |= mx[s] > ref[s] + kLazyLog2;
     }
-    if (__any(grow)) {                 // some row of this wave outgrew its reference: move every reference up
+    if (__builtin_expect(__any(grow), 0)) {                 // some row of this wave outgrew its reference: move every reference up
 #pragma unroll
       for (int s = 0; s < NSUB; ++s) {
         const float new_ref = fmaxf(ref[s], halves_max(rows16_max(mx[s])));
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
     float base[NSUB];
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) base[s] = ref[s] > -INFINITY ? ref[s] : 0.f;
-    if (far) {
+    if (__builtin_expect(far, 0)) {
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
 #pragma unroll

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
     bool grow = false;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) grow |= tile_max[rb] > ref[rb] + lazy_raw;
-    if (__any(grow)) {
+    if (__builtin_expect(__any(grow), 0)) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         const float mx = fmaxf(tile_max[rb], __shfl_xor(tile_max[rb], 32, 64));

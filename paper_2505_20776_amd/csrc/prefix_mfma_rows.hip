@@ -342,7 +342,7 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
     const int first_key = tile_first_row(j);
     // register r of s[kp] holds key first_key + KPR * (4*hf + 8*(r/4) + r%4) + kp
     const int skip = key0 - first_key - KPR * 4 * hf;     // > 0 only in a shifted last tile: keys of the tile before
-    if (first_key < key0) {
+    if (__builtin_expect(first_key < key0, 0)) {
 #pragma unroll
       for (int kp = 0; kp < KPR; ++kp)
 #pragma unroll
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
     for (int kp = 0; kp < KPR; ++kp)
 #pragma unroll
       for (int r = 0; r < 16; r += 2) mx = fmaxf(mx, fmaxf(s[kp][r], s[kp][r + 1]));
-    if (__any(mx > ref + lazy_raw)) {     // some row of this wave outgrew its reference: move every reference up
+    if (__builtin_expect(__any(mx > ref + lazy_raw), 0)) {     // some row of this wave outgrew its reference: move every reference up
       mx = halves_max(mx);
       const float new_ref = fmaxf(ref, mx);
       const float alpha = fast_exp2((ref - new_ref) * c);     // 0 on the first tile
@@ -436,13 +436,13 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
       static_for<0, kStages>([&](auto u_c) {
         constexpr int u = decltype(u_c)::value;
         const int s = s0 + u;
-        if (s < n_stages) {
-          if (s == 0) {
+        if (__builtin_expect(s < n_stages, 1)) {
+          if (__builtin_expect(s == 0, 0)) {
             wait_vmcnt_even(younger_than_stage(0));        // also covers the wave's own queries
 #pragma unroll
             for (int ks = 0; ks < kQSteps; ++ks)
               qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(priv + k_rd[ks]));
-          } else if ((s + kStages - 1) * kStageTiles <= n) {
+          } else if (__builtin_expect((s + kStages - 1) * kStageTiles <= n, 1)) {
             asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoadsPerTile * kStageTiles * (kStages - 2)) : "memory");
           } else {
             wait_vmcnt_even(younger_than_stage(s));
@@ -453,20 +453,20 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
 #ifdef SPECEXT_TAIL_STAMPS
           if (s == 0) stamp_first = wall_clock64();
 #endif
-          if (s + kStages - 1 < n_stages) issue_stage(ic<(u + kStages - 1) % kStages>{}, s + kStages - 1);
+          if (__builtin_expect(s + kStages - 1 < n_stages, 1)) issue_stage(ic<(u + kStages - 1) % kStages>{}, s + kStages - 1);
           static_for<0, kStageTiles>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value;
             const int j = s * kStageTiles + i;
-            if (j < n && wave_live) {
+            if (__builtin_expect(j < n && wave_live, 1)) {
               if constexpr (kOrder == 2) {
-                if (j > 0) tile_second_product();
+                if (__builtin_expect(j > 0, 1)) tile_second_product();
                 tile_front(ic<u * kStageTiles + i>{});
                 SPECEXT_LOOP_STAMP(ls_half);
                 tile_softmax(j);
               } else if constexpr (kRot) {
-                if (j > 0) tile_softmax(j - 1);
+                if (__builtin_expect(j > 0, 1)) tile_softmax(j - 1);
                 SPECEXT_LOOP_STAMP(ls_half);
-                if (j > 0) tile_second_product();
+                if (__builtin_expect(j > 0, 1)) tile_second_product();
                 tile_front(ic<u * kStageTiles + i>{});
               } else {
                 tile_front(ic<u * kStageTiles + i>{});

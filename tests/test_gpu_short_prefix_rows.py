@@ -29,3 +29,22 @@ def test_128_row_workgroups_give_the_bits_of_256(Hq, Hkv, d, L, T):
     ref_out, ref_lse, ref_scores = oracle_all(wl)
     check_attention(wl, auto, ref_out, ref_lse, "short prefix")
     check_scores(auto["scores"], ref_scores, "short prefix")
+
+
+# rows per KV head: one past the key-split kernel's 32, odd counts that leave padding rows in the last wave, whole waves of padding
+@pytest.mark.parametrize("Hq,Hkv,L,T", [(1, 1, 4096, 33), (3, 1, 2000, 15), (4, 4, 9000, 65), (3, 1, 9000, 43), (5, 1, 9000, 51), (1, 1, 1000, 5),
+                                        (6, 2, 700, 7)])
+def test_score_pairs_beside_padding_rows(Hq, Hkv, L, T):
+    """Every lane of a wave stores its row's score pair, padding rows that of the last real row: the same bits in every pass, and
+    nothing outside of the pairs."""
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(L + T)
+    wl = make_workload("pairs", seed=L + T, dtype="bf16", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, prefix_len=L,
+                       parent=random_parent_tree(T, 7, rng), chunk_size=32, top_k=4, n_needles=0, value_std=1.0)
+    print(f"[case] Hq={Hq} Hkv={Hkv} L={L} T={T}", flush=True)
+    first = hx.run_verify(wl)
+    for _ in range(3):
+        again = hx.run_verify(wl)
+        assert np.array_equal(again["scores"], first["scores"]) and np.array_equal(again["out"], first["out"])
+    _, _, ref_scores = oracle_all(wl)
+    check_scores(first["scores"], ref_scores, "pairs")
