@@ -68,3 +68,22 @@ def test_strided_keys_of_64(dtype):
     torch.cuda.synchronize()
     buf.check_guards()
     assert np.abs(buf.out.cpu().numpy() - ref_out).max() <= TOL_F32 * np.abs(ref_out).max()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,L,T,B", [
+    ("bf16", 32, 8, 128, 4109, 60, 16),       # eight splits of 17 tiles, the last of ten: key groups of five and four tiles
+    ("bf16", 32, 8, 128, 3000, 40, 16), ("bf16", 8, 2, 64, 1000, 20, 12), ("f32", 32, 8, 128, 3333, 25, 64),
+    ("f32", 16, 8, 128, 1100, 40, 32), ("f32", 4, 1, 64, 300, 12, 8)])
+def test_splits_cut_at_tiles(dtype, Hq, Hkv, d, L, T, B):
+    """Automatic split counts cut the prefix at whole tiles of a key group, requested ones at stages of all four."""
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(L)
+    wl = make_workload("tiles", seed=L, dtype=dtype, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, prefix_len=L,
+                       parent=random_parent_tree(T, 9, rng), chunk_size=B, top_k=4, n_needles=0, value_std=1.0)
+    print(f"[case] {dtype} Hq={Hq} Hkv={Hkv} d={d} L={L} T={T} B={B}", flush=True)
+    ref_out, ref_lse, ref_scores = oracle_all(wl)
+    for splits in (0, 6):
+        res = hx.run_verify(wl, num_splits=splits, out_dtype="f32")
+        assert np.abs(res["out"] - ref_out).max() <= TOL_F32 * np.abs(ref_out).max()
+        assert np.abs(res["lse"] - ref_lse).max() <= TOL_F32
+        check_scores(res["scores"], ref_scores, "tiles")
