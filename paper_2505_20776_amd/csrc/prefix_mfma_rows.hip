@@ -52,6 +52,12 @@ constexpr int kStageTiles = SPECEXT_ROWS_STAGE_TILES;   // tiles between two wor
 constexpr int kDeepStages = SPECEXT_ROWS_STAGES;
 constexpr int kShortStages = 2;
 constexpr int kShortSplitTiles = 24;                    // splits of at most this many tiles take the short ring
+// Four waves: three stages for short splits where more than two of the waves have rows.  Measured with four / three stages, us
+// per launch: 32 nodes of 4 heads 8K 10.6 / 10.3, 16K 16.1 / 15.3, 24K 22.7 / 22.6; 120 nodes of 32 KV heads 4K 16.0 / 15.3; 60
+// nodes of 4 heads in two row groups 3K 8.05 / 7.9; with up to 64 rows 8K 9.4 / 9.5, 16K 14.0 / 13.7, 50 nodes of 32 KV heads
+// 2K 9.9 / 10.3.
+constexpr int kShortStages4 = 3;
+constexpr int kShortSplitTiles4 = 16;
 constexpr int ring_bytes(int stages) { return 2 * kStageTiles * stages * kTileBytes; }
 // Behind the rings every wave has a private area: first the staging of its 32 query
 // rows (32 x 256 B), at the end the staging of its 32 partial output rows as fp16
@@ -642,12 +648,14 @@ hipError_t launch_prefix_mfma_rows(const AttnParams& p, hipStream_t stream) {
     if (big) return p.want_scores ? launch_rows<8, true, 2>(p, stream) : launch_rows<8, false, 2>(p, stream);
     return p.want_scores ? launch_rows<4, true, 2>(p, stream) : launch_rows<4, false, 2>(p, stream);
   }
+  const int split_tiles = (p.keys_per_split + kTile - 1) / kTile;
   if (big) {
-    const int split_tiles = (p.keys_per_split + kTile - 1) / kTile;
     if (split_tiles <= kShortSplitTiles)
       return p.want_scores ? launch_rows<8, true, 1, kShortStages>(p, stream) : launch_rows<8, false, 1, kShortStages>(p, stream);
     return p.want_scores ? launch_rows<8, true, 1>(p, stream) : launch_rows<8, false, 1>(p, stream);
   }
+  if (split_tiles <= kShortSplitTiles4 && p.M > 64)
+    return p.want_scores ? launch_rows<4, true, 1, kShortStages4>(p, stream) : launch_rows<4, false, 1, kShortStages4>(p, stream);
   return p.want_scores ? launch_rows<4, true, 1>(p, stream) : launch_rows<4, false, 1>(p, stream);
 }
 

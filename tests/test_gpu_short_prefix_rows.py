@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 # M = T * Hq / Hkv query rows per KV head: one past 128, the middle, one short of and exactly 256, and past it
 @pytest.mark.parametrize("Hq,Hkv,d,L,T", [
     (3, 1, 128, 1024, 43), (32, 8, 128, 2048, 60), (15, 3, 128, 2048, 51), (8, 2, 128, 4096, 64), (4, 1, 128, 1024, 65),
+    (4, 1, 128, 2048, 33),
     (8, 2, 64, 2048, 60), (4, 4, 64, 1024, 128), (4, 2, 64, 1024, 128)])
 def test_128_row_workgroups_give_the_bits_of_256(Hq, Hkv, d, L, T):
     import paper_2505_20776_amd as sx
@@ -48,3 +49,19 @@ def test_score_pairs_beside_padding_rows(Hq, Hkv, L, T):
         assert np.array_equal(again["scores"], first["scores"]) and np.array_equal(again["out"], first["out"])
     _, _, ref_scores = oracle_all(wl)
     check_scores(first["scores"], ref_scores, "pairs")
+
+
+@pytest.mark.parametrize("L,splits,T", [(97, 1, 17), (128, 1, 20), (16 * 32, 1, 32), (16 * 32 + 1, 1, 32), (17 * 32, 1, 18), (1000, 2, 25)])
+def test_ring_depths_of_four_waves(L, splits, T):
+    """65 to 128 rows: a ring of three stages up to 16 tiles per split, of four beyond; split lengths around both."""
+    from paper_2505_20776_amd import harness as hx
+    rng = np.random.default_rng(L)
+    wl = make_workload("ring", seed=L, dtype="bf16", n_q_heads=4, n_kv_heads=1, head_dim=128, prefix_len=L,
+                       parent=random_parent_tree(T, 7, rng), chunk_size=32, top_k=4, n_needles=0, value_std=1.0)
+    print(f"[case] L={L} splits={splits} T={T}", flush=True)
+    ref_out, ref_lse, ref_scores = oracle_all(wl)
+    for want_scores in (True, False):
+        res = hx.run_verify(wl, num_splits=splits, want_scores=want_scores)
+        check_attention(wl, res, ref_out, ref_lse, "ring")
+        if want_scores:
+            check_scores(res["scores"], ref_scores, "ring")
