@@ -3,7 +3,7 @@
 //
 // A verification step of one layer is five calls of this library behind one another, and on short prefixes the host is
 // what bounds it.  Marshalled in Python through ctypes, a call costs 1.5 - 2.2 us beside its launches (10 - 14 method calls
-// on tensors, a conversion of every argument); here 0.2.
+// on tensors, a conversion of every argument); here 0.25 - 0.3.
 //
 // Only the plain case is taken: exact torch.Tensor, int, float, bool and None arguments and the library's own descriptor.
 // Whatever else arrives - subclasses, numpy numbers, stream objects, a wrong or missing argument, a tensor without
