@@ -3,6 +3,7 @@ same for every kind of argument, given by position, by name or left out, and wha
 points are replaced by recorders, so nothing here needs a GPU."""
 import ctypes
 import inspect
+import os
 import random
 
 import numpy as np
@@ -12,6 +13,9 @@ import torch
 import paper_2505_20776_amd as sx
 from paper_2505_20776_amd import binding
 
+if not (os.path.exists(binding._LIB_PATH) and os.path.exists(binding._MARSHAL_PATH)):
+    from paper_2505_20776_amd.build import build_library
+    build_library(verbose=False)
 sx.load_library()
 pytestmark = pytest.mark.skipif(binding._marshal is None, reason="package imported before it was built")
 NAMES = binding._marshal.FUNCTIONS if binding._marshal is not None else ()
