@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 # SPECEXT_LIBRARY may name another build of the same library (e.g. one compiled with other flags)
@@ -64,6 +65,7 @@ class specext_desc(ctypes.Structure):
 
 _lib = None
 _marshal = None         # the native marshalling; None where this module was imported before it was built
+_marshal_error = None   # why it did not load
 
 
 def load_library() -> ctypes.CDLL:
@@ -133,6 +135,9 @@ def load_library() -> ctypes.CDLL:
     if _marshal is not None:
         for name in _marshal.FUNCTIONS:
             _marshal.bind(name, ctypes.cast(getattr(lib, "specext_" + name), ctypes.c_void_p).value)
+    elif _marshal_error is not None:
+        warnings.warn(f"{_MARSHAL_PATH} does not load ({_marshal_error}): calls are marshalled through ctypes, 2 us more each, "
+                      "until it is built again with `python -m paper_2505_20776_amd.build`", RuntimeWarning, stacklevel=2)
     return lib
 
 
@@ -392,15 +397,20 @@ def chunk_scores_select(desc, workspace, score_row: int, k: int, idx_out, n_out,
 
 
 def _take_over() -> None:
-    """Put the native callables in the place of the functions above that they take over."""
-    global _marshal
+    """Put the native callables in the place of the functions above that they take over.  One that does not load (damaged, or
+    built for another torch or Python) leaves those functions where they are: the build imports this package, too."""
+    global _marshal, _marshal_error
     if not os.path.exists(_MARSHAL_PATH):
         return          # not built yet: load_library says so, and the build itself imports this package
     try:
         import torch  # noqa: F401
     except ImportError:
         return          # addresses instead of tensors: the functions above
-    from . import _marshal as native
+    try:
+        from . import _marshal as native
+    except Exception as e:
+        _marshal_error = f"{type(e).__name__}: {e}"
+        return
     _marshal = native
     for name in native.FUNCTIONS:
         globals()[name] = native.wrap(name, globals()[name], specext_desc, _check)

@@ -1,0 +1,48 @@
+"""The package around its native argument marshalling: what works where that is damaged, missing or built later.  Each case is a
+copy of the package in a process of its own; nothing here needs a GPU."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PACKAGE = "paper_2505_20776_amd"
+LIBRARY = os.path.join(ROOT, PACKAGE, "libspecext.so")
+MARSHAL = os.path.join(ROOT, PACKAGE, "_marshal.so")
+SPLITS = ("sx.num_splits(sx.make_desc(dtype=1, n_q_heads=8, n_kv_heads=2, head_dim=128, prefix_len=300, n_tree=8, num_splits=200))")
+
+
+@pytest.fixture
+def copy(tmp_path):
+    """The package's Python files and the built library, without the marshalling."""
+    if not (os.path.exists(LIBRARY) and os.path.exists(MARSHAL)):
+        from paper_2505_20776_amd.build import build_library
+        build_library(verbose=False)
+    package = tmp_path / PACKAGE
+    package.mkdir()
+    for name in os.listdir(os.path.join(ROOT, PACKAGE)):
+        if name.endswith(".py"):
+            shutil.copy(os.path.join(ROOT, PACKAGE, name), package)
+    os.symlink(LIBRARY, package / "libspecext.so")
+    return package
+
+
+def _run(copy, code, *options, **env):
+    env = {k: v for k, v in dict(os.environ, **env).items() if k not in ("SPECEXT_LIBRARY", "PYTHONPATH")}
+    run = subprocess.run([sys.executable, *options, "-c", code], cwd=copy.parent, env=env, stdout=subprocess.PIPE,
+                         stderr=subprocess.STDOUT, text=True, timeout=250)
+    assert run.returncode == 0, run.stdout[-3000:]
+    return run.stdout
+
+
+@pytest.mark.parametrize("what", ["empty", "text", "another library"])
+def test_marshalling_that_does_not_load(copy, what):
+    """The package imports, its functions and its build work, and loading the library says what to do."""
+    if what == "another library":
+        shutil.copy(LIBRARY, copy / "_marshal.so")
+    else:
+        (copy / "_marshal.so").write_bytes(b"" if what == "empty" else b"no shared object" * 400)
+    out = _run(copy, f"import {PACKAGE} as sx, {PACKAGE}.build, types; print({SPLITS}); print(type(sx.verify_attn) is types.FunctionType)")
+    assert "3\nTrue" in out and "RuntimeWarning" in out and f"python -m {PACKAGE}.build" in out
