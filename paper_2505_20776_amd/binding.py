@@ -65,7 +65,7 @@ class specext_desc(ctypes.Structure):
 
 _lib = None
 _marshal = None         # the native marshalling; None where this module was imported before it was built
-_marshal_error = None   # why it did not load
+_marshal_error = None   # why it does not serve, where torch is there and it could
 
 
 def load_library() -> ctypes.CDLL:
@@ -73,9 +73,8 @@ def load_library() -> ctypes.CDLL:
     global _lib
     if _lib is not None:
         return _lib
-    missing = [p for p in (_LIB_PATH, _MARSHAL_PATH) if not os.path.exists(p)]
-    if missing:
-        raise ImportError(f"{missing[0]} is missing: build it with `python -m paper_2505_20776_amd.build` "
+    if not os.path.exists(_LIB_PATH):
+        raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2505_20776_amd.build` "
                           "(there is no fallback implementation)")
     # torch may bring a HIP runtime of its own.  Loaded first, it is the one that the library binds to; behind the library there
     # would be two runtimes in the process, and a stream or tensor of one is no object of the other (a crash in the first call).
@@ -136,8 +135,8 @@ def load_library() -> ctypes.CDLL:
         for name in _marshal.FUNCTIONS:
             _marshal.bind(name, ctypes.cast(getattr(lib, "specext_" + name), ctypes.c_void_p).value)
     elif _marshal_error is not None:
-        warnings.warn(f"{_MARSHAL_PATH} does not load ({_marshal_error}): calls are marshalled through ctypes, 2 us more each, "
-                      "until it is built again with `python -m paper_2505_20776_amd.build`", RuntimeWarning, stacklevel=2)
+        warnings.warn(f"{_MARSHAL_PATH} {_marshal_error}: calls are marshalled through ctypes, 2 us more each, "
+                      "until it is built with `python -m paper_2505_20776_amd.build`", RuntimeWarning, stacklevel=2)
     return lib
 
 
@@ -400,16 +399,17 @@ def _take_over() -> None:
     """Put the native callables in the place of the functions above that they take over.  One that does not load (damaged, or
     built for another torch or Python) leaves those functions where they are: the build imports this package, too."""
     global _marshal, _marshal_error
-    if not os.path.exists(_MARSHAL_PATH):
-        return          # not built yet: load_library says so, and the build itself imports this package
     try:
         import torch  # noqa: F401
     except ImportError:
         return          # addresses instead of tensors: the functions above
+    if not os.path.exists(_MARSHAL_PATH):
+        _marshal_error = "is missing"
+        return
     try:
         from . import _marshal as native
     except Exception as e:
-        _marshal_error = f"{type(e).__name__}: {e}"
+        _marshal_error = f"does not load ({type(e).__name__}: {e})"
         return
     _marshal = native
     for name in native.FUNCTIONS:

@@ -46,3 +46,17 @@ def test_marshalling_that_does_not_load(copy, what):
         (copy / "_marshal.so").write_bytes(b"" if what == "empty" else b"no shared object" * 400)
     out = _run(copy, f"import {PACKAGE} as sx, {PACKAGE}.build, types; print({SPLITS}); print(type(sx.verify_attn) is types.FunctionType)")
     assert "3\nTrue" in out and "RuntimeWarning" in out and f"python -m {PACKAGE}.build" in out
+
+
+def test_without_marshalling(copy):
+    out = _run(copy, f"import {PACKAGE} as sx; print({SPLITS})")
+    assert out.endswith("3\n") and "RuntimeWarning" in out and "_marshal.so is missing" in out
+
+
+def test_without_torch(copy):
+    """Addresses instead of tensors: nothing of the marshalling is asked for."""
+    for _ in range(2):
+        out = _run(copy, f"import sys; sys.modules['torch'] = None; import {PACKAGE} as sx; print({SPLITS}); "
+                         "print(sx.select_chunks(4096, 0, 2, 4096, 4096, stream=0, check=False))")
+        assert out == "3\n-1\n"
+        os.path.exists(copy / "_marshal.so") or os.symlink(MARSHAL, copy / "_marshal.so")
