@@ -13,7 +13,9 @@ ten tensors 1.9 -> 0.3 us); everything else comes back to the functions here.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import sys
 import warnings
 from typing import Optional
 
@@ -64,7 +66,7 @@ class specext_desc(ctypes.Structure):
 
 
 _lib = None
-_marshal = None         # the native marshalling; None where this module was imported before it was built
+_marshal = None         # the native marshalling, once it serves
 _marshal_error = None   # why it does not serve, where torch is there and it could
 
 
@@ -131,6 +133,7 @@ def load_library() -> ctypes.CDLL:
     lib.specext_calib_issue_mix.restype = ctypes.c_int
     lib.specext_calib_issue_mix.argtypes = [i32, i32, i32, i32, vp, vp]
     _lib = lib
+    _take_over()            # built since this module was imported
     if _marshal is not None:
         for name in _marshal.FUNCTIONS:
             _marshal.bind(name, ctypes.cast(getattr(lib, "specext_" + name), ctypes.c_void_p).value)
@@ -399,6 +402,8 @@ def _take_over() -> None:
     """Put the native callables in the place of the functions above that they take over.  One that does not load (damaged, or
     built for another torch or Python) leaves those functions where they are: the build imports this package, too."""
     global _marshal, _marshal_error
+    if _marshal is not None:
+        return
     try:
         import torch  # noqa: F401
     except ImportError:
@@ -406,14 +411,21 @@ def _take_over() -> None:
     if not os.path.exists(_MARSHAL_PATH):
         _marshal_error = "is missing"
         return
+    importlib.invalidate_caches()
     try:
         from . import _marshal as native
     except Exception as e:
         _marshal_error = f"does not load ({type(e).__name__}: {e})"
         return
-    _marshal = native
+    _marshal, _marshal_error = native, None
+    if _raw_stream is not None:
+        native.set_stream_ready()
+    package = sys.modules[__package__]
     for name in native.FUNCTIONS:
-        globals()[name] = native.wrap(name, globals()[name], specext_desc, _check)
+        plain = globals()[name]
+        globals()[name] = native.wrap(name, plain, specext_desc, _check)
+        if getattr(package, name, None) is plain:           # the package has imported its names by now
+            setattr(package, name, globals()[name])
 
 
 _take_over()

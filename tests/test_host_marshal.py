@@ -17,8 +17,8 @@ if not (os.path.exists(binding._LIB_PATH) and os.path.exists(binding._MARSHAL_PA
     from paper_2505_20776_amd.build import build_library
     build_library(verbose=False)
 sx.load_library()
-pytestmark = pytest.mark.skipif(binding._marshal is None, reason="package imported before it was built")
-NAMES = binding._marshal.FUNCTIONS if binding._marshal is not None else ()
+assert binding._marshal is not None, binding._marshal_error
+NAMES = binding._marshal.FUNCTIONS
 
 
 class _Recorder:

@@ -60,3 +60,12 @@ def test_without_torch(copy):
                          "print(sx.select_chunks(4096, 0, 2, 4096, 4096, stream=0, check=False))")
         assert out == "3\n-1\n"
         os.path.exists(copy / "_marshal.so") or os.symlink(MARSHAL, copy / "_marshal.so")
+
+
+def test_built_after_the_import(copy):
+    """Loading the library takes the marshalling over that was built since the package was imported."""
+    out = _run(copy, f"import os, {PACKAGE} as sx; from {PACKAGE} import binding; os.symlink({MARSHAL!r}, {str(copy / '_marshal.so')!r}); "
+                     "sx.load_library(); print(len(binding._marshal.FUNCTIONS)); "
+                     "print(all(type(getattr(m, n)).__name__ == 'Call' for m in (sx, binding) for n in binding._marshal.FUNCTIONS)); "
+                     "print(sx.select_chunks(4096, 0, 2, 4096, 4096, stream=0, check=False))")
+    assert out == "10\nTrue\n-1\n"
