@@ -36,15 +36,19 @@ MARSHAL_PATH = os.path.join(PKG_DIR, "_marshal.so")
 
 
 def _marshal_command(out: str):
-    """Host code only: the host compiler, against Python's and torch's headers; torch's libraries are those already loaded."""
+    """(command, reason why there is none).  Host code only: the host compiler, against Python's and torch's headers; torch's
+    libraries are those already loaded."""
     import sysconfig
 
-    import torch
-    from torch.utils.cpp_extension import include_paths
+    try:
+        import torch
+        from torch.utils.cpp_extension import include_paths
+    except ImportError as e:
+        return None, f"torch: {e}"
     cxx = next((c for c in (os.environ.get("CXX"), shutil.which("g++"), shutil.which("c++"), "/opt/rocm/llvm/bin/clang++")
                 if c and (os.path.exists(c) or shutil.which(c))), None)
     if cxx is None:
-        raise RuntimeError("no C++ compiler found (set CXX)")
+        return None, "no C++ compiler found (set CXX)"
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
     includes = include_paths() + [sysconfig.get_paths()["include"], os.path.join(rocm, "include"), "/opt/rocm/include"]
     lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
@@ -52,14 +56,16 @@ def _marshal_command(out: str):
              f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
             + [a for i in includes if os.path.isdir(i) for a in ("-isystem", i)]
             + [os.path.join(CSRC, "marshal.cpp"), "-o", out, "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10",
-               "-lc10_hip"])
+               "-lc10_hip"]), None
 
 
 def build_library(verbose: bool = True, stamps: bool = False) -> str:
     """Compile every HIP source for gfx950 and link libspecext.so next to this file.
     stamps=True builds the profiling variant libspecext_stamps.so instead (-DSPECEXT_TAIL_STAMPS: the row-split
     prefix kernel and the fused merge tail leave wall-clock stamps of their phases in the workspace; see
-    paper_2505_20776_amd/phase_stamps.py)."""
+    paper_2505_20776_amd/phase_stamps.py).
+    The marshalling beside it needs torch and a host compiler.  Where it cannot be built the library still is; an older
+    _marshal.so, which may not fit it, goes."""
     obj_dir = os.path.join(PKG_DIR, "_build_stamps" if stamps else "_build")
     os.makedirs(obj_dir, exist_ok=True)
     common = [
@@ -77,9 +83,8 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
         procs.append((src, subprocess.Popen(common + EXTRA_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj],
                                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     marshal_tmp = MARSHAL_PATH + ".tmp"
-    if not stamps:
-        procs.append(("marshal.cpp", subprocess.Popen(_marshal_command(marshal_tmp), stdout=subprocess.PIPE,
-                                                      stderr=subprocess.STDOUT, text=True)))
+    marshal_cmd, marshal_error = _marshal_command(marshal_tmp) if not stamps else (None, None)
+    marshal = marshal_cmd and subprocess.Popen(marshal_cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     failed = False
     for src, pr in procs:
         out, _ = pr.communicate()
@@ -89,12 +94,20 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
             sys.stderr.write(f"[specext build] {src} failed:\n{out}\n")
         elif verbose and out.strip():
             sys.stderr.write(f"[specext build] {src}:\n{out}\n")
+    if marshal:
+        out, _ = marshal.communicate()
+        if marshal.returncode != 0:
+            marshal_error = out
     if failed:
         raise RuntimeError("hipcc failed")
     tmp = lib_path + ".tmp"
     subprocess.run([hipcc_path(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, lib_path)
-    if not stamps:
+    if marshal_error is not None:
+        sys.stderr.write(f"[specext build] {lib_path} is built, _marshal.so is not:\n{marshal_error}\n")
+        if os.path.exists(MARSHAL_PATH):
+            os.remove(MARSHAL_PATH)
+    elif not stamps:
         os.replace(marshal_tmp, MARSHAL_PATH)
     return lib_path
 

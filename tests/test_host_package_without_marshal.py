@@ -69,3 +69,20 @@ def test_built_after_the_import(copy):
                      "print(all(type(getattr(m, n)).__name__ == 'Call' for m in (sx, binding) for n in binding._marshal.FUNCTIONS)); "
                      "print(sx.select_chunks(4096, 0, 2, 4096, 4096, stream=0, check=False))")
     assert out == "10\nTrue\n-1\n"
+
+
+@pytest.mark.parametrize("missing", ["torch", "headers"])
+def test_build_without_what_the_marshalling_needs(copy, tmp_path, missing):
+    """The library is built, the build says what is not, and an older _marshal.so does not stay beside a newer library.  A script
+    stands in for hipcc: it notes each call and writes the output file."""
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text('#!/bin/sh\necho "$@" >> calls\nwhile [ "$1" != -o ]; do shift; done; echo built > "$2"\n')
+    hipcc.chmod(0o755)
+    os.remove(copy / "libspecext.so")
+    os.symlink(MARSHAL, copy / "_marshal.so")
+    hide = "sys.modules['torch'] = None; " if missing == "torch" else ""
+    out = _run(copy, f"import sys; {hide}from {PACKAGE}.build import build_library, SOURCES; build_library(); print(len(SOURCES))",
+               HIPCC=str(hipcc), CXX="false")
+    assert "_marshal.so is not" in out and not os.path.lexists(copy / "_marshal.so")
+    assert (copy / "libspecext.so").read_text() == "built\n"
+    assert len(open(tmp_path / "calls").readlines()) == int(out.splitlines()[-1]) + 1
