@@ -8,7 +8,9 @@ is missing, loading raises: there is no fallback path.
 
 The functions that a decoding step calls are taken over, for plain arguments, by
 callables of the same signature that marshal natively (csrc/marshal.cpp; a call of
-ten tensors 1.9 -> 0.3 us); everything else comes back to the functions here.
+ten tensors 1.9 -> 0.3 us); everything else comes back to the functions here.  They
+are copied, pickled, weakly referenced, given attributes and bound as functions are,
+but they are no function objects: inspect.isfunction is false, isroutine is true.
 """
 from __future__ import annotations
 

@@ -174,6 +174,7 @@ struct Call {
   PyObject* slow;        // the Python function
   PyTypeObject* desc;    // type of the descriptor
   PyObject* raise;       // (status, name of the C entry point) -> raises
+  PyObject* weak;        // weak references to this
 };
 
 // int within 64 bits
@@ -309,11 +310,13 @@ int call_clear(PyObject* self) {
 
 void call_dealloc(PyObject* self) {
   PyObject_GC_UnTrack(self);
+  if (reinterpret_cast<Call*>(self)->weak) PyObject_ClearWeakRefs(self);
   call_clear(self);
   Py_TYPE(self)->tp_free(self);
 }
 
-// name, docstring, signature and the like are the Python function's
+// In everything but the call and its type this is the Python function: its attributes are that one's, to read and to write, as
+// a class attribute it binds, and copy and pickle refer to it by its name.
 PyObject* call_getattro(PyObject* self, PyObject* name) {
   PyObject* slow = reinterpret_cast<Call*>(self)->slow;
   if (PyUnicode_Check(name)) {
@@ -321,12 +324,31 @@ PyObject* call_getattro(PyObject* self, PyObject* name) {
       Py_INCREF(slow);
       return slow;
     }
-    for (const char* of_function : {"__name__", "__qualname__", "__doc__", "__module__", "__defaults__", "__kwdefaults__", "__code__",
-                                    "__annotations__"})
-      if (PyUnicode_CompareWithASCIIString(name, of_function) == 0) return PyObject_GetAttr(slow, name);
+    for (const char* of_type : {"__class__", "__call__", "__get__", "__reduce__", "__reduce_ex__"})
+      if (PyUnicode_CompareWithASCIIString(name, of_type) == 0) return PyObject_GenericGetAttr(self, name);
   }
-  return PyObject_GenericGetAttr(self, name);
+  return PyObject_GetAttr(slow, name);
 }
+
+int call_setattro(PyObject* self, PyObject* name, PyObject* value) {      // value NULL: deleted
+  return PyObject_SetAttr(reinterpret_cast<Call*>(self)->slow, name, value);
+}
+
+PyObject* call_repr(PyObject* self) { return PyObject_Repr(reinterpret_cast<Call*>(self)->slow); }
+
+PyObject* call_descr_get(PyObject* self, PyObject* object, PyObject*) {
+  if (object && object != Py_None) return PyMethod_New(self, object);
+  Py_INCREF(self);
+  return self;
+}
+
+PyObject* call_reduce(PyObject* self, PyObject*) {
+  return PyObject_GetAttrString(reinterpret_cast<Call*>(self)->slow, "__qualname__");
+}
+
+PyMethodDef call_methods[] = {{"__reduce__", call_reduce, METH_NOARGS, nullptr},
+                              {"__reduce_ex__", call_reduce, METH_O, nullptr},
+                              {nullptr, nullptr, 0, nullptr}};
 
 PyTypeObject call_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
@@ -346,6 +368,7 @@ PyObject* py_wrap(PyObject*, PyObject* args) {
     c->desc = reinterpret_cast<PyTypeObject*>(desc);
     Py_INCREF(raise);
     c->raise = raise;
+    c->weak = nullptr;
     PyObject_GC_Track(c);
     return reinterpret_cast<PyObject*>(c);
   }
@@ -397,6 +420,11 @@ PyMODINIT_FUNC PyInit__marshal() {
   call_type.tp_clear = call_clear;
   call_type.tp_dealloc = call_dealloc;
   call_type.tp_getattro = call_getattro;
+  call_type.tp_setattro = call_setattro;
+  call_type.tp_repr = call_repr;
+  call_type.tp_descr_get = call_descr_get;
+  call_type.tp_methods = call_methods;
+  call_type.tp_weaklistoffset = offsetof(Call, weak);
   if (PyType_Ready(&call_type) < 0) return nullptr;
   PyObject* m = PyModule_Create(&module);
   if (!m) return nullptr;

@@ -1,10 +1,14 @@
 """The native argument marshalling against the Python functions that it takes over: what reaches the C entry point is the
 same for every kind of argument, given by position, by name or left out, and what is refused is refused alike.  The entry
 points are replaced by recorders, so nothing here needs a GPU."""
+import copy
 import ctypes
+import functools
 import inspect
 import os
+import pickle
 import random
+import weakref
 
 import numpy as np
 import pytest
@@ -143,3 +147,33 @@ def test_tensors_without_storage_and_subclasses(recorded):
     assert recorded["select_chunks"].calls[0] == recorded["select_chunks"].calls[1]
     with pytest.raises((RuntimeError, NotImplementedError, ValueError)):
         sx.select_chunks(torch.sparse_coo_tensor(torch.zeros((1, 1), dtype=torch.long), torch.ones(1), (8,)), 8, 2, plain, plain, stream=0)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_used_as_a_function_is(name):
+    """What a program may do with a module's function beside calling it."""
+    f = getattr(sx, name)
+    assert pickle.loads(pickle.dumps(f)) is f and copy.copy(f) is f and copy.deepcopy({"f": f})["f"] is f
+    assert weakref.ref(f)() is f and len({f, f}) == 1 and f == f
+    assert inspect.isroutine(f) and callable(f) and inspect.unwrap(f) is f.__wrapped__ and "def " + name in inspect.getsource(f)
+    assert f.__module__ == binding.__name__ and f.__qualname__ == name and f.__globals__ is vars(binding) and repr(f).startswith("<function " + name)
+    with pytest.raises(AttributeError, match="no_such"):
+        f.no_such
+    f.note = 1
+    assert f.note == 1 and vars(f) == {"note": 1} and "note" in dir(f)
+    del f.note
+    assert not hasattr(f, "note") and not vars(f)
+    holder = type("Holder", (), {"call": f})()
+    assert holder.call.__self__ is holder and holder.call.__func__ is f and type(holder).call is f
+    assert functools.wraps(f)(lambda: None).__name__ == name
+
+
+def test_weak_reference_outlived():
+    def plain():
+        pass
+
+    f = binding._marshal.wrap(NAMES[0], plain, sx.specext_desc, binding._check)
+    gone = []
+    ref = weakref.ref(f, gone.append)
+    del f
+    assert ref() is None and gone == [ref]
