@@ -192,7 +192,9 @@ int specext_verify_attn(const specext_desc* desc, const void* q, const void* k_p
  *               malformed parent index); may be NULL
  *
  * Limits: a descriptor whose specext_workspace_bytes exceeds the scratch array is
- * rejected with SPECEXT_ERR_WORKSPACE_TOO_SMALL before anything is launched (the
+ * rejected with SPECEXT_ERR_WORKSPACE_TOO_SMALL before anything is launched (unless, in the
+ * kernel with fp32 probabilities, a requested num_splits fits when it is cut into fewer
+ * splits at 64 fp32 or 128 bf16 keys: then it is cut so; the
  * Llama-3.1-8B layer shape fits at every prefix length with a 60-node tree at up to
  * 48 splits and with a 128-node tree at up to 22, the automatic split counts
  * included); want_scores != 0 is SPECEXT_ERR_UNSUPPORTED, because the
@@ -410,9 +412,11 @@ int specext_chunk_scores_materialized(const specext_desc* desc, const void* work
                                       float* scores, void* stream);
 
 /*
- * Number of prefix splits specext_verify_attn uses for this descriptor when
- * desc->num_splits == 0 (else returns desc->num_splits clamped to what is
- * valid).  Returns a negative specext_status on an invalid descriptor.
+ * Number of prefix splits specext_verify_attn uses for this descriptor: the automatic
+ * choice when desc->num_splits == 0, else at most desc->num_splits (splits are cut at
+ * whole key granules of the kernel, and of chunks where the kernel needs that).  Asking
+ * for the number of the automatic choice gives as many splits again.  Returns a negative
+ * specext_status on an invalid descriptor.
  */
 int specext_num_splits(const specext_desc* desc);
 

@@ -56,7 +56,7 @@ int64_t gcd64(int64_t a, int64_t b) {
 }
 
 // Validate the descriptor and resolve every default.  Pointers are not looked at here.
-int resolve(const specext_desc* d, AttnParams* p) {
+int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   if (!d || d->struct_size != sizeof(specext_desc)) return SPECEXT_ERR_INVALID_ARG;
   if (d->n_q_heads <= 0 || d->n_kv_heads <= 0 || d->prefix_len < 0 || d->n_tree <= 0 || d->num_splits < 0)
     return SPECEXT_ERR_INVALID_ARG;
@@ -136,11 +136,13 @@ int resolve(const specext_desc* d, AttnParams* p) {
   p->score_gran = p->use_mfma == 3 ? (p->B % 16 == 0 ? 16 : p->B % 8 == 0 ? 8 : 4) : p->use_mfma ? 32 : p->B;
   p->n_sub = p->want_scores ? (p->L + p->score_gran - 1) / p->score_gran : 0;
 
-  // Split the prefix.  Every split but the last holds keys_per_split keys: a
-  // multiple of the kernel's key granule (128: 4 waves x 32 keys in the key-split
-  // kernel, a stage of bf16 keys in the fp32-probability one; else 64) and, with
-  // scores, of the chunk size, so that no chunk is shared by two splits (except
-  // in the fp32-probability kernel, below).
+  // Split the prefix.  Every split but the last holds keys_per_split keys, a multiple of the kernel's key granule:
+  //   key-split kernel                 128 (4 waves x 32 keys)
+  //   row-split, vector-ALU kernel     64
+  //   fp32-probability kernel          a tile of a key group, 32 bf16 or 16 fp32 keys (with stage_cut a stage of all four)
+  // and, with scores, of the chunk size, so that no chunk is shared by two splits.  The fp32-probability kernel keeps the
+  // reference of every score block beside its sum, so there a chunk may lie in two splits; a score block (4, 8 or 16 keys) may
+  // not, and as it divides the tile it does not.
   if (p->L == 0) {
     p->S = 0;
     p->keys_per_split = 128;
@@ -158,13 +160,13 @@ int resolve(const specext_desc* d, AttnParams* p) {
   if (p->use_mfma == 2 && p->rows_per_group == 256 && d->num_splits == 0 &&
       static_cast<int64_t>(by_len) * p->Hkv * ((p->M + 127) / 128) <= device_cu_count())
     p->rows_per_group = 128;
-  // (the fp32-probability kernel keeps the reference of every score block beside its sum, so a chunk may lie in two splits.
-  // An automatic split is cut at whole tiles of a key group: at whole stages of the four, 4109 bf16 keys made seven splits of
-  // five stages where eight of four and a bit fit, 19.1 instead of 18.1 us; 3333 fp32 keys 26.4 and 24.6; 1100 17.5 and 17.7.
-  // A requested count is cut at stages, as the static scratch's size allows for.)
+  // The fp32-probability kernel's splits end at whole tiles of a key group: at whole stages of the four, 4109 bf16 keys made
+  // seven splits of five stages where eight of four and a bit fit, 19.1 instead of 18.1 us; 3333 fp32 keys 26.4 and 24.6; 1100
+  // 17.5 and 17.7.  A requested count is cut the same way, so that the one that an automatic call reports gives its problem
+  // again; only where the static scratch array cannot hold a requested count is that cut at stages, which makes fewer splits.
   int64_t unit = p->use_mfma == 1 ? 128 : 64;
   const int stage = p->in_dtype == SPECEXT_BF16 ? 128 : 64;
-  if (p->use_mfma == 3) unit = d->num_splits == 0 ? stage / 4 : stage;
+  if (p->use_mfma == 3) unit = stage_cut && d->num_splits != 0 ? stage : stage / 4;
   if (p->want_scores && p->use_mfma != 3) unit = unit / gcd64(unit, p->B) * p->B;
   int want = d->num_splits;
   if (want == 0) {
@@ -290,9 +292,10 @@ void* static_scratch_of_current_device() {
 // specext_verify_attn on an explicit workspace; status_word != nullptr redirects the status word
 int verify_attn_on(const specext_desc* desc, const void* q, const void* k_prefix, const void* v_prefix,
                    const void* k_tree, const void* v_tree, const int32_t* parent, void* out, float* lse,
-                   void* workspace, size_t workspace_bytes, int32_t* status_word, bool library_memory, void* stream) {
+                   void* workspace, size_t workspace_bytes, int32_t* status_word, bool library_memory, bool stage_cut,
+                   void* stream) {
   AttnParams p;
-  const int rc = resolve(desc, &p);
+  const int rc = resolve(desc, &p, stage_cut);
   if (rc != SPECEXT_OK) return rc;
   if (!q || !k_tree || !v_tree || !parent || !out || !workspace) return SPECEXT_ERR_INVALID_ARG;
   if (p.L > 0 && (!k_prefix || !v_prefix)) return SPECEXT_ERR_INVALID_ARG;
@@ -379,7 +382,7 @@ int specext_verify_attn(const specext_desc* desc, const void* q, const void* k_p
                         const void* k_tree, const void* v_tree, const int32_t* parent, void* out, float* lse,
                         void* workspace, size_t workspace_bytes, void* stream) {
   return verify_attn_on(desc, q, k_prefix, v_prefix, k_tree, v_tree, parent, out, lse, workspace, workspace_bytes,
-                        nullptr, false, stream);
+                        nullptr, false, false, stream);
 }
 
 int specext_verify_attn_static(const specext_desc* desc, const void* q, const void* k_prefix, const void* v_prefix,
@@ -392,11 +395,16 @@ int specext_verify_attn_static(const specext_desc* desc, const void* q, const vo
   // takes the caller's workspace: the layer that feeds the retrieval uses specext_verify_attn
   if (p.want_scores) return SPECEXT_ERR_UNSUPPORTED;
   if (reinterpret_cast<uintptr_t>(status_out) & 3u) return SPECEXT_ERR_UNSUPPORTED;
-  if (layout_of(p).total > kStaticScratchBytes) return SPECEXT_ERR_WORKSPACE_TOO_SMALL;
+  bool stage_cut = false;
+  if (layout_of(p).total > kStaticScratchBytes) {
+    stage_cut = true;
+    resolve(desc, &p, stage_cut);
+    if (layout_of(p).total > kStaticScratchBytes) return SPECEXT_ERR_WORKSPACE_TOO_SMALL;
+  }
   void* ws = static_scratch_of_current_device();
   if (!ws) return SPECEXT_ERR_LAUNCH_FAILED;
   return verify_attn_on(desc, q, k_prefix, v_prefix, k_tree, v_tree, parent, out, lse, ws, kStaticScratchBytes,
-                        status_out, true, stream);
+                        status_out, true, stage_cut, stream);
 }
 
 int specext_chunk_scores(const specext_desc* desc, const void* workspace, size_t workspace_bytes,

@@ -99,6 +99,22 @@ int main() {
     EXPECT(specext_verify_attn_static(&x, ok, ok, ok, ok, ok, iok, ok, fok, iok, nullptr) == -3);   // too large for the scratch
   }
 
+  // kernel with fp32 probabilities: twelve splits of 112 keys are too large for the static scratch, ten of 128 are not
+  {
+    specext_desc x = good_desc();
+    x.dtype = x.out_dtype = SPECEXT_F32;
+    x.want_scores = 0;
+    x.n_q_heads = 64;
+    x.n_tree = 128;
+    x.prefix_len = 1280;
+    x.num_splits = 12;
+    EXPECT(specext_num_splits(&x) == 12);
+    EXPECT(specext_workspace_bytes(&x) > (size_t{SPECEXT_STATIC_SCRATCH_MIB} << 20));
+    EXPECT(specext_verify_attn_static(&x, ok, ok, ok, ok, ok, iok, ok, fok, iok, nullptr) != SPECEXT_ERR_WORKSPACE_TOO_SMALL);
+    x.num_splits = 40;
+    EXPECT(specext_verify_attn_static(&x, ok, ok, ok, ok, ok, iok, ok, fok, iok, nullptr) == SPECEXT_ERR_WORKSPACE_TOO_SMALL);
+  }
+
   // pointers and sizes of verify_attn
   EXPECT(specext_verify_attn(&d, nullptr, ok, ok, ok, ok, iok, ok, fok, ok, ws, nullptr) == -1);
   EXPECT(specext_verify_attn(&d, ok, nullptr, ok, ok, ok, iok, ok, fok, ok, ws, nullptr) == -1);

@@ -66,6 +66,19 @@ def test_workspace_and_splits(sx):
     assert sx.num_splits(d) == 2                        # vector-ALU kernel: 64-key granule
 
 
+@pytest.mark.parametrize("dtype,d,hq,hkv,T,L,B", [
+    ("bf16", 128, 32, 8, 60, 4109, 16), ("f32", 128, 32, 8, 60, 1100, 32), ("f32", 128, 32, 8, 60, 3333, 64),
+    ("f32", 64, 4, 1, 8, 512, 32), ("f32", 64, 4, 1, 8, 300, 8), ("bf16", 64, 8, 2, 20, 1000, 12), ("bf16", 128, 32, 8, 8, 8155, 32),
+    ("bf16", 128, 32, 8, 60, 2048, 32), ("bf16", 64, 12, 12, 60, 1024, 32), ("bf16", 128, 32, 8, 128, 32731, 32), ("f32", 128, 8, 8, 1, 70001, 16)])
+def test_the_reported_split_count_gives_the_automatic_problem(sx, dtype, d, hq, hkv, T, L, B):
+    for want_scores in (True, False):
+        kw = dict(dtype=sx.SPECEXT_BF16 if dtype == "bf16" else sx.SPECEXT_F32, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=L,
+                  n_tree=T, chunk_size=B, want_scores=want_scores)
+        auto = sx.make_desc(**kw)
+        asked = sx.make_desc(num_splits=sx.num_splits(auto), **kw)
+        assert sx.num_splits(asked) == sx.num_splits(auto) and sx.workspace_bytes(asked) == sx.workspace_bytes(auto)
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("struct_size", 4, -1), ("n_q_heads", 0, -1), ("n_kv_heads", 5, -1), ("prefix_len", -1, -1),
     ("n_tree", 0, -1), ("chunk_size", 0, -1), ("num_splits", -2, -1), ("softmax_scale", -1.0, -1),

@@ -94,3 +94,23 @@ def test_static_entry_rejects_what_it_cannot_hold():
                           chunk_size=32, want_scores=True)
     rc = sx.verify_attn_static(scored, dummy, dummy, dummy, dummy, dummy, par, dummy, None, None, check=False)
     assert rc == -2
+
+
+def test_static_entry_cuts_a_requested_count_coarser():
+    """Twelve splits of 112 fp32 keys do not fit the scratch array; cut at stages the request makes ten of 128, as ten asked for do."""
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness
+
+    Hq, Hkv, d, T, L = 64, 8, 128, 128, 1280
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, kp, vp, kt, vt = rn(T, Hq, d), rn(Hkv, L, d), rn(Hkv, L, d), rn(Hkv, T, d), rn(Hkv, T, d)
+    parent = torch.arange(-1, T - 1, dtype=torch.int32, device="cuda")
+    kw = dict(dtype="f32", n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, prefix_len=L, n_tree=T)
+    ten, twelve = harness.make_buffers(num_splits=10, **kw), harness.make_buffers(num_splits=12, **kw)
+    assert sx.num_splits(twelve.desc) == 12 and sx.workspace_bytes(twelve.desc) > (48 << 20) >= sx.workspace_bytes(ten.desc)
+    sx.verify_attn(ten.desc, q, kp, vp, kt, vt, parent, ten.out, ten.lse, ten.workspace)
+    status = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    sx.verify_attn_static(twelve.desc, q, kp, vp, kt, vt, parent, twelve.out, twelve.lse, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and torch.equal(ten.out, twelve.out) and torch.equal(ten.lse, twelve.lse)
