@@ -247,7 +247,8 @@ int specext_select_chunks(const float* scores, int32_t n_chunks, int32_t k, int3
  *                 idx[r]*chunk_size + t of the source.  A ragged last source
  *                 chunk contributes only its real tokens and later chunks
  *                 follow it without a gap.
- *   idx           device int32 [max_idx]; entries < 0 or >= ceil(src_len/chunk_size) are skipped
+ *   idx           device int32 [max_idx]; entries < 0 or >= ceil(src_len/chunk_size) are skipped.  All
+ *                 max_idx entries may be read, whatever *n_idx; those behind *n_idx have no effect
  *   n_idx         device int32 [1] (how many entries of idx are used, clamped to
  *                 max_idx) or NULL to use all max_idx entries
  *   dst_cap       token capacity of the destination; must be >= max_idx * chunk_size

@@ -131,8 +131,10 @@ def run_gather(k_src: torch.Tensor, v_src: torch.Tensor, idx: np.ndarray, chunk_
     """gather_draft_kv on [Ld,H,L,d] device tensors.  Returns (k_dst, v_dst, pos, length) with the
     destination sized max_idx * chunk_size tokens and pre-filled with a canary pattern."""
     ld, hh, plen, d = k_src.shape
-    idx_t = torch.from_numpy(np.ascontiguousarray(idx, dtype=np.int32)).cuda()
     max_idx = int(len(idx) if max_idx is None else max_idx)
+    idx_t = torch.full((max(max_idx, len(idx), 1),), -1, dtype=torch.int32)       # all max_idx entries may be read
+    idx_t[:len(idx)] = torch.from_numpy(np.ascontiguousarray(idx, dtype=np.int32))
+    idx_t = idx_t.cuda()
     cap = max_idx * chunk_size
     k_dst, k_base = guarded((ld, hh, cap, d), k_src.dtype)
     v_dst, v_base = guarded((ld, hh, cap, d), k_src.dtype)
@@ -143,8 +145,6 @@ def run_gather(k_src: torch.Tensor, v_src: torch.Tensor, idx: np.ndarray, chunk_
     pos.fill_(-5)
     length.fill_(-5)
     n_idx_t = None if n_idx is None else torch.tensor([n_idx], dtype=torch.int32, device="cuda")
-    if idx_t.numel() == 0:
-        idx_t = torch.zeros(1, dtype=torch.int32, device="cuda")
     sx.gather_draft_kv(k_src, v_src, k_dst, v_dst, idx_t, n_idx_t, max_idx, ld, hh, plen, cap, d, chunk_size,
                        k_src.element_size(), pos, length)
     torch.cuda.synchronize()

@@ -60,6 +60,27 @@ def test_gather_lists_around_a_wave(n_list, n_idx):
     assert (kd[:, :, :length].float().cpu().numpy() == rk).all() and (vd[:, :, :length].float().cpu().numpy() == rv).all()
 
 
+def test_gather_list_shorter_than_its_room(monkeypatch):
+    """The kernel may read all max_idx entries: a list of three with room for seventy is handed over with all of them."""
+    from paper_2505_20776_amd import binding, harness as hx
+    handed, gather = [], binding.gather_draft_kv
+
+    def note(*args, **kw):
+        handed.append((args[4].numel(), args[6]))
+        return gather(*args, **kw)
+
+    monkeypatch.setattr(binding, "gather_draft_kv", note)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    k = torch.randn((1, 2, 700, 64), device="cuda", generator=g).to(torch.bfloat16)
+    idx = np.array([5, 0, 21], dtype=np.int32)
+    for n_idx in (3, 2, None):
+        kd, _, pos, length = hx.run_gather(k, k, idx, 32, n_idx=n_idx, max_idx=70)
+        rk, _, rpos = orc.gather_draft_kv(k.float().cpu().numpy(), k.float().cpu().numpy(), idx[:n_idx], 32)
+        assert length == len(rpos) and list(pos[:length]) == list(rpos)
+        assert (kd[:, :, :length].float().cpu().numpy() == rk).all()
+    assert all(size >= max_idx for size, max_idx in handed)
+
+
 @pytest.mark.parametrize("Hq,Hkv,L,B", [
     (32, 8, 4096, 32),        # 128 chunks, 1024 groups: one launch
     (32, 8, 4097, 32),        # 129 chunks: two
