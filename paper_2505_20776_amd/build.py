@@ -59,6 +59,16 @@ def _marshal_command(out: str):
                "-lc10_hip"]), None
 
 
+def compile_command(src: str, stamps: bool = False):
+    """hipcc with the flags of one source, without its input and output."""
+    return [
+        hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+        "-mllvm", "-amdgpu-kernarg-preload-count=14",        # a kernel's first arguments in registers at its start (csrc/common.h)
+        "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
+    ] + (["-DSPECEXT_TAIL_STAMPS"] if stamps else []) + EXTRA_FLAGS.get(src, [])
+
+
 def build_library(verbose: bool = True, stamps: bool = False) -> str:
     """Compile every HIP source for gfx950 and link libspecext.so next to this file.
     stamps=True builds the profiling variant libspecext_stamps.so instead (-DSPECEXT_TAIL_STAMPS: the row-split
@@ -68,19 +78,13 @@ def build_library(verbose: bool = True, stamps: bool = False) -> str:
     _marshal.so, which may not fit it, goes."""
     obj_dir = os.path.join(PKG_DIR, "_build_stamps" if stamps else "_build")
     os.makedirs(obj_dir, exist_ok=True)
-    common = [
-        hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-mllvm", "-amdgpu-kernarg-preload-count=14",        # a kernel's first arguments in registers at its start (csrc/common.h)
-        "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
-    ] + (["-DSPECEXT_TAIL_STAMPS"] if stamps else [])
     lib_path = STAMPS_LIB_PATH if stamps else LIB_PATH
     procs = []
     objs = []
     for src in SOURCES:
         obj = os.path.join(obj_dir, src.replace(".hip", ".o"))
         objs.append(obj)
-        procs.append((src, subprocess.Popen(common + EXTRA_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj],
+        procs.append((src, subprocess.Popen(compile_command(src, stamps) + ["-c", os.path.join(CSRC, src), "-o", obj],
                                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     marshal_tmp = MARSHAL_PATH + ".tmp"
     marshal_cmd, marshal_error = _marshal_command(marshal_tmp) if not stamps else (None, None)

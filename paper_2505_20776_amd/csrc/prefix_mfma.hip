@@ -78,17 +78,6 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
   const unsigned char* kbase = static_cast<const unsigned char*>(p.kp) + static_cast<int64_t>(g) * p.kp_sh * 2;
   const unsigned char* vbase = static_cast<const unsigned char*>(p.vp) + static_cast<int64_t>(g) * p.kp_sh * 2;
 
-  // ---- Q fragments (B operand of S^T): lane = row c32, 8 consecutive d per k-step ----
-  bf16x8 qf[RB][8];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int m = min(row0 + 32 * rb + c32, p.M - 1);           // padding rows repeat the last real row
-    const int t = m / p.G;
-    const int h = g * p.G + (m - t * p.G);
-    const uint16_t* qp = static_cast<const uint16_t*>(p.q) + t * p.q_st + h * p.q_sh + 8 * hf;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[rb][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(qp + 16 * ks));
-  }
   // ---- per-wave LDS staging: a ring of 3 K tiles and a ring of 2 V tiles, each
   // tile 32 rows x 256 B, filled by direct global->LDS loads: one load instruction
   // writes 1 KB = 4 consecutive rows, lane i landing at byte 16*i.  The 16-byte
@@ -153,15 +142,34 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
   auto issue_k = [&](int j) { issue_tile(kbase, j, stage_lds + (j % kKSlots) * kTileBytes, true); };
   auto issue_v = [&](int j) { issue_tile(vbase, j, stage_lds + (kKSlots + j % kVSlots) * kTileBytes, false); };
 
-  bf16x8 kf[8];
-  auto read_k = [&](int j) {
-    const unsigned char* kst = stage + (j % kKSlots) * kTileBytes + k_rd_base;
+  // The queries (B operand of S^T: lane = row c32, 8 consecutive d per k-step) take the same way through LDS, in the K slot
+  // that stays empty longest: with loads into registers the compiler, which counts only those, would wait for them until
+  // nothing at all is in flight.
+  static_assert(RB == 1, "the queries of one block of 32 rows fit a slot");
+  constexpr int kQSlot = kKSlots - 1;
+  auto issue_q = [&]() {
+    const float inv_g = 1.0f / static_cast<float>(p.G);
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int r = 4 * it + ld_row;
+      const int m = min(row0 + r, p.M - 1);                                       // padding rows repeat the last real row
+      const int t = static_cast<int>((static_cast<float>(m) + 0.5f) * inv_g);     // m / G, exact for m < 2^20
+      const int h = g * p.G + (m - t * p.G);
+      const unsigned voff = static_cast<unsigned>((t * p.q_st + h * p.q_sh) * 2) + ((ld_slot ^ (r & 15)) << 4);
+      load_to_lds_16(stage_lds + kQSlot * kTileBytes + it * 1024, voff, static_cast<const unsigned char*>(p.q));
+    }
+  };
+
+  auto read_rows = [&](bf16x8 (&f)[8], int slot) {
+    const unsigned char* kst = stage + slot * kTileBytes + k_rd_base;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       const uintx4 kw = *reinterpret_cast<const uintx4*>(kst + (((2 * ks) ^ k_rd_xor) << 4));
-      kf[ks] = __builtin_bit_cast(bf16x8, kw);
+      f[ks] = __builtin_bit_cast(bf16x8, kw);
     }
   };
+  bf16x8 qf[RB][8], kf[8];
+  auto read_k = [&](int j) { read_rows(kf, j % kKSlots); };
   bf16x8 vf[4][2];
   auto read_v = [&](int j) {
     const unsigned char* vst = stage + (kKSlots + j % kVSlots) * kTileBytes + v_rd_base;
@@ -272,21 +280,26 @@ __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at,
   };
 
   if (n > 0) {
-    // prologue: fill the rings (K0 V0 K1 V1 K2, and K3 once K0 has left its slot), logits of tile 0
+    // prologue: the queries, then fill the rings (K0 V0 K1 V1, K2 once the queries have left its slot, K3 once K0 has), logits
+    // of tile 0.  Queries and first keys share one trip to memory and each wait leaves the younger loads in flight.  Us per
+    // launch, 8 nodes of 32 heads in 8 groups: with query loads into registers, for which the compiler waited until the ring
+    // was drained, 1K keys 6.3, 2K 6.7, 4K 9.1, 8K 11.3, 16K 16.0; so 5.7, 6.1, 8.1, 10.4, 16.0.  Queries behind V0: 6.35,
+    // 6.7, 8.2, 10.4, 15.9 (one tile per wave up to 2K, and its logits then wait for V0, too).
+    issue_q();
     issue_k(0);
     issue_v(0);
     if (n > 1) {
       issue_k(1);
       issue_v(1);
     }
-    if (n > 2) issue_k(2);
-    // The queries, requested before all these, have landed when no more than these are pending: they and the first keys
-    // share one trip to memory (2048 keys, 8 nodes: 7.2 us with a wait of their own before the first key is requested, 6.9 so;
-    // 65536 keys 49.9 and 49.1, 8192 keys 11.6 and 11.8).  Said through the builtin so that the compiler's own wait bookkeeping sees it and adds no
-    // vmcnt wait of its own inside the loop (vmcnt(16), (32), (40); other counters untouched).
-    if (n > 2) __builtin_amdgcn_s_waitcnt(0x8F78);
-    else if (n > 1) __builtin_amdgcn_s_waitcnt(0x8F70);
-    else __builtin_amdgcn_s_waitcnt(0x4F70);
+    wait_vm_groups(n > 1 ? 4 : 2);       // queries landed
+    read_rows(qf[0], kQSlot);
+    if (n > 2) {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      issue_k(2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     wait_vm_groups(1 + (n > 1 ? 2 : 0) + (n > 2 ? 1 : 0));     // K0 landed
     read_k(0);
     qk(s_v);
