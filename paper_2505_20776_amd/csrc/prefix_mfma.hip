@@ -52,11 +52,11 @@ __device__ __forceinline__ void wait_vm_groups(int groups) {
 
 template <int RB, bool SCORES>
 __global__ __launch_bounds__(kWaves * 64) void prefix_mfma_kernel(uint64_t k_at, uint64_t v_at, uint64_t q_at, int64_t kp_sh, int L, int keys_per_split, int M, int G,
-                                                            int kp_sl, int head_fastest, AttnParams p) {
+                                                            int kp_sl, AttnParams p) {
   p.kp = in_global<const void>(k_at);
   p.vp = in_global<const void>(v_at);
   p.q = in_global<const void>(q_at);
-  p.kp_sh = kp_sh, p.L = L, p.keys_per_split = keys_per_split, p.M = M, p.G = G, p.kp_sl = kp_sl, p.head_fastest = head_fastest;
+  p.kp_sh = kp_sh, p.L = L, p.keys_per_split = keys_per_split, p.M = M, p.G = G, p.kp_sl = kp_sl;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
   const int lane = threadIdx.x & 63;
@@ -449,7 +449,7 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   }
   dim3 grid(p.S, p.Hkv, (p.M + 32 * RB - 1) / (32 * RB));
   kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L, p.keys_per_split, p.M, p.G,
-                                                             static_cast<int>(p.kp_sl), p.head_fastest, p);
+                                                             static_cast<int>(p.kp_sl), p);
   return hipGetLastError();
 }
 
