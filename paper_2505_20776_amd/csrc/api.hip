@@ -369,6 +369,11 @@ size_t specext_debug_stamps_offset(const specext_desc* desc) {
   if (resolve(desc, &p) != SPECEXT_OK || p.use_mfma != 2 || !p.part_f16) return 0;
   return layout_of(p).part_o_off + static_cast<size_t>(p.S) * p.Hq * p.T * p.d * 2;
 }
+// Query rows of a workgroup of that kernel, 32 per wave: 128 or 256.  0 as above.
+int specext_debug_rows_per_workgroup(const specext_desc* desc) {
+  AttnParams p;
+  return resolve(desc, &p) != SPECEXT_OK || p.use_mfma != 2 || !p.part_f16 ? 0 : p.rows_per_group;
+}
 #endif
 
 int specext_num_splits(const specext_desc* desc) {

@@ -26,6 +26,18 @@ from paper_2505_20776_amd import harness
 from workloads import config_tree
 
 
+def workgroup_shape(lib, desc, n_rows: int):
+    """(waves of a workgroup, row groups) of the prefix launch for this descriptor, n_rows = query rows per KV head."""
+    rows = int(lib.specext_debug_rows_per_workgroup(ctypes.byref(desc)))
+    return rows // 32, -(-n_rows // rows)
+
+
+def loop_stamps_written(waves: int, n_workgroups: int, spare_bytes: int) -> bool:
+    """Whether the kernel leaves its per-wave loop stamps: eight-wave workgroups only, 4 MiB into the spare half of the partial
+    region, 80 words per wave, where that half holds them."""
+    return waves == 8 and spare_bytes >= (4 << 20) + n_workgroups * waves * 80 * 4
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--prefix", type=int, default=16384)
@@ -38,6 +50,7 @@ def main():
         raise SystemExit("this library was built without -DSPECEXT_TAIL_STAMPS: see the module's docstring")
     lib.specext_debug_stamps_offset.restype = ctypes.c_size_t
     lib.specext_debug_stamps_offset.argtypes = [ctypes.POINTER(sx.specext_desc)]
+    lib.specext_debug_rows_per_workgroup.argtypes = [ctypes.POINTER(sx.specext_desc)]
     dev, Hq, Hkv, d, L, n_layers = "cuda", 32, 8, 128, a.prefix, 8
     parent_np = config_tree(4)
     T = len(parent_np)
@@ -61,39 +74,40 @@ def main():
     n_merge_wg = (Hq * T + 3) // 4
     merge_fits = S * Hq * T * d * 2 >= (2 << 20) + n_merge_wg * 64
     merge_acc = []
-    # the per-wave loop stamps (eight-wave workgroups only) lie 4 MiB into the spare half, 80 words per wave
-    n_rows = Hq // Hkv * T
-    loop_fits = n_rows > 128 and S * Hq * T * d * 2 >= (4 << 20) + Hkv * S * 8 * 80 * 4
+    waves, row_groups = workgroup_shape(lib, buf.desc, Hq // Hkv * T)
+    n_wg = row_groups * Hkv * S
+    loop_fits = loop_stamps_written(waves, n_wg, S * Hq * T * d * 2)
     loop_acc = []
     for it in range(a.passes + 2):
         for l in range(n_layers):
             sx.verify_attn(buf.desc, q[l], kp[l], vp[l], kt[l], vt[l], parent, buf.out, buf.lse, buf.workspace)
         torch.cuda.synchronize()
-        st = buf.workspace[off:off + Hkv * S * 64].view(torch.int64).cpu().numpy().reshape(Hkv, S, 8).astype(np.float64)
+        st = buf.workspace[off:off + n_wg * 64].view(torch.int64).cpu().numpy().reshape(row_groups, Hkv, S, 8).astype(np.float64)
         if it >= 2:
-            acc.append((st[:, :, :n_st] - st[:, :, 0].min()) / 100.0)
+            acc.append((st[..., :n_st] - st[..., 0].min()) / 100.0)
             if loop_fits:
                 lo = off + (4 << 20)
-                loop_acc.append(buf.workspace[lo:lo + Hkv * S * 8 * 80 * 4].view(torch.int32).cpu().numpy()
-                                .reshape(Hkv * S, 8, 80).astype(np.int64) & 0xffffffff)
+                loop_acc.append(buf.workspace[lo:lo + n_wg * 8 * 80 * 4].view(torch.int32).cpu().numpy()
+                                .reshape(n_wg, 8, 80).astype(np.int64) & 0xffffffff)
             if not fused and merge_fits:
                 ms = buf.workspace[off + (2 << 20):off + (2 << 20) + n_merge_wg * 64].view(torch.int64).cpu().numpy()
                 ms = ms.reshape(n_merge_wg, 8)[:, :6].astype(np.float64)
-                merge_acc.append(((ms - ms[:, 0].min()) / 100.0, (ms[:, 0].min() - st[:, :, 3].max()) / 100.0))
+                merge_acc.append(((ms - ms[:, 0].min()) / 100.0, (ms[:, 0].min() - st[..., 3].max()) / 100.0))
     us = np.mean(acc, axis=0)
     names = (["workgroup start", "last key tile done (tail entry)", "own partial acknowledged, flag stored", "tree part done",
               "all flags seen", "own slice merged and written", "done"] if fused else
              ["workgroup start", "first key tile ready", "last key tile done", "partial stores issued"])
     tiles = -(-(-(-L // S)) // 32)
-    print(f"prefix {L}, {S} splits x {Hkv} KV heads = {S * Hkv} workgroups, {tiles} key tiles each, merge: {a.merge}")
+    print(f"prefix {L}, {S} splits x {Hkv} KV heads x {row_groups} row groups = {n_wg} workgroups of {waves} waves, {tiles} key tiles "
+          f"each, merge: {a.merge}")
     print(f"{'phase':42s} {'min':>8s} {'median':>8s} {'max':>8s}   (us after the first workgroup's start)")
     for i, n in enumerate(names):
-        v = us[:, :, i]
+        v = us[..., i]
         print(f"{n:42s} {v.min():8.2f} {np.median(v):8.2f} {v.max():8.2f}")
     last = 1 if fused else 2
-    print("last key tile done, mean per KV head (one head per XCD):", " ".join(f"{us[h, :, last].mean():.2f}" for h in range(Hkv)))
+    print("last key tile done, mean per KV head (one head per XCD):", " ".join(f"{us[:, h, :, last].mean():.2f}" for h in range(Hkv)))
     if not fused:
-        print(f"key-tile loop: {np.median(us[:, :, 2] - us[:, :, 1]) / tiles:.3f} us per tile (median workgroup)")
+        print(f"key-tile loop: {np.median(us[..., 2] - us[..., 1]) / tiles:.3f} us per tile (median workgroup)")
     if loop_acc and tiles > 5:
         n_t = min(16, tiles - 4)            # stamped tiles: 4 .. 4 + n_t - 1
         ticks = np.median([(w[:, :, 65] - w[:, :, 64]) & 0xffffffff for w in loop_acc])
