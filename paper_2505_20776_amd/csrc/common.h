@@ -127,9 +127,11 @@ hipError_t launch_gather(const void* k_src, const void* v_src, void* k_dst, void
 
 // Kernel arguments.  The first 14 dwords of a kernel's scalar arguments are in registers when a wave starts (the build asks for
 // it, -amdgpu-kernarg-preload-count); what lies behind them, every struct, and the launch's dimensions take a scalar load
-// first, 0.2 us of a launch that waits for it.  So what a kernel needs for its first trip to memory comes first, as scalars,
-// and a problem's other parameters behind in AttnParams.  Where nothing is lost by it, addresses are passed as integers: the
-// runtime looks every pointer argument up in its list of allocations (0.03 - 0.1 us of host time each).
+// first, 0.2 us of a launch that waits for it.  So what a kernel needs to request its first keys, partials or list entries
+// comes first, as scalars, and a problem's other parameters behind in AttnParams.  (The query strides are among those: the
+// row-split kernel requests keys before its queries, the other two wait for the strides.)  Where nothing is lost by it,
+// addresses are passed as integers: the runtime looks every pointer argument up in its list of allocations (0.03 - 0.1 us of
+// host time each).
 inline uint64_t address_of(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 template <class T>
 __device__ __forceinline__ T* in_global(uint64_t address) {

@@ -152,9 +152,10 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
     for (int j = 0; j < kQRegs; ++j) qf[s][j] = *reinterpret_cast<const uintx4*>(src + 64 * j);
   }
   issue_stage(0);
-  // All query loads have landed before they are used; said through the builtin so that the compiler's own wait
-  // bookkeeping sees it and adds no vmcnt(0) inside the loop, which would wait for the stage just requested
-  // (the loads of stage 0 stay in flight; 0x0F70: other counters untouched).
+  // All query loads have landed, stage 0 may still be in flight (0x0F70: other counters untouched).  The compiler counts only
+  // the query loads, the tiles being requested by inline assembly, and waits for each of them once more where the scaling below
+  // uses it: down to vmcnt(0), which is stage 0, and for head_dim 64 the later stages requested by then.  So the scaling follows
+  // the first stage's landing; inside the loop there is no such wait.
   constexpr int kInFlight = kLoadsPerStage;
   if (my_tiles > 0) __builtin_amdgcn_s_waitcnt((kInFlight & 15) | (kInFlight >> 4 << 14) | 0x0F70);
   else __builtin_amdgcn_s_waitcnt(0x0F70);
