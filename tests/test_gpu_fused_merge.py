@@ -51,7 +51,8 @@ def _wl(L, tree, seed, Hq=32, Hkv=8):
 
 CASES = [  # L, tree, splits, Hq, Hkv
     (16384 - 37, "eagle60", 0, 32, 8),      # 32 splits, 8 rows per slice, four groups share a row's splits
-    (2048, "eagle60", 0, 32, 8),            # 8 splits, 30 rows per slice
+    (2048, "eagle60", 0, 32, 8),            # 16 splits in two row groups of 128 rows, 8 rows per slice
+    (2048, "eagle60", 8, 32, 8),            # 8 splits of 256 rows, 30 rows per slice
     (1000, "eagle26", 0, 8, 2),             # 4-wave kernel, 26 rows per slice in two passes
     (1000, "eagle26", 1, 8, 2),             # one split: the workgroup merges alone
     (4096 + 13, "wide128", 0, 32, 8),       # two row groups per KV head
