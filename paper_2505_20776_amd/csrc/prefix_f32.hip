@@ -480,6 +480,8 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
 
 template <int D, bool BF16, int NSUB, int RB, int SCORES>
 hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
+  // a split begins with a score block: the kernel stores a block's pair from one tile of one split
+  if (SCORES && p.keys_per_split % p.score_gran != 0) return hipErrorInvalidValue;
   using T = Tile<D, BF16>;
   constexpr int kWaves = RB * KG;
   constexpr int kStageBytes = KG * 2 * T::kBytes;
