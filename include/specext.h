@@ -333,7 +333,7 @@ int specext_chunk_scores_accepted(const specext_desc* desc, const void* workspac
  * specext_chunk_scores for one tree row followed by specext_select_chunks over that
  * row's scores (Sec. 3.2.1; SelectChunks of Alg. 1): in one launch while one compute unit
  * takes in the row's partial sums faster than a second launch costs (up to 128 chunks and
- * n_kv_heads times the score blocks up to 1200; a block is 32 keys for the kernels with bf16
+ * n_kv_heads times the score blocks up to 1600; a block is 32 keys for the kernels with bf16
  * probabilities, else 4, 8 or 16), and up to 1024 chunks also when scores is NULL; else in two.
  * Same scores and the same selection, bit for bit, as the two calls.
  *

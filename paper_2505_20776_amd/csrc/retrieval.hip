@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
 // kRadixMax with four (4096 scores of a 128K prefix: 25 us bit by bit as below, 8.2 us so).
 constexpr int kRankMax = 1024;
 constexpr int kRadixMax = 4 * kSelThreads;
-constexpr int kScoreGroupsOneLaunch = 1200;
+constexpr int kScoreGroupsOneLaunch = 1600;
 constexpr int kScoreChunksOneLaunch = 128;
 
 // One workgroup (blockDim.x a multiple of 64), thread i holding the scores of chunks i, i + blockDim.x, ... (KPT of
@@ -545,11 +545,16 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
                                const int32_t* row_count, int32_t k, float* scores, int32_t* idx_out, int32_t* n_out,
                                hipStream_t stream) {
   if (p.C > kRankMax) return hipErrorInvalidValue;
-  // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 1200 on, and from 128 chunks
-  // on, a launch of its own for the scores, which every compute unit shares, is the shorter way.  Measured on the device, us
-  // in one launch / in two: 8 KV heads, 32-key chunks, 64 chunks 3.3 / 4.6, 65 4.9 / 5.8, 128 5.3 / 5.9, 150 6.6 / 6.0, 256
-  // 7.4 / 5.9; 64 chunks of two blocks 4.0 / 5.0, 100 6.3 / 6.3; 2 KV heads, 512 chunks 9.4 / 6.2; 32 KV heads, 32 chunks
-  // 3.5 / 4.3, 64 5.4 / 4.6.
+  // One compute unit takes in the pair groups (KV heads x score blocks) at some 600 per us; from 1600 on, and from 128 chunks
+  // on, where the selection takes sixteen waves, a launch of its own for the scores, which every compute unit shares, is the
+  // shorter way.  Measured with the pairs as the attention left them, us in one launch / in two; whole iterations of one
+  // layer, then of two, launched from Python (the two in turn in one process):
+  //   8 heads, 32-key chunks   100 chunks 28.3 / 29.0, 41.7 / 42.4;  128 28.8 / 29.6, 43.2 / 43.7;  160 31.5 / 31.1, 47.3 / 46.8
+  //   8 heads, 64-key chunks   80 (1280 groups) 32.1 / 32.2, 47.5 / 48.3;  100 (1600) 33.1 / 33.3, 50.3 / 50.3;  113 (1800) 34.9 / 34.6
+  //   32 heads, 32-key chunks  41 (1312) 28.9 / 29.4, 42.1 / 42.8;  50 (1600) 30.3 / 30.5, 44.1 / 44.3;  64 (2048) 31.2 / 30.8, 45.6 / 45.1
+  // and the selection alone in a captured graph: 8 heads 1280 groups 5.8 / 6.2, 1600 6.1 / 6.4, 2048 6.4 / 6.2, 2944 6.2 / 5.1; 2 heads
+  // 129 chunks 5.6 / 5.2, 256 6.5 / 5.5 (with one or two heads and 129 to 192 chunks the iteration is bounded by the host and
+  // equal to 0.3 us either way, with a slow host up to 1 - 2 us longer in two).
   if (scores && (p.C > kScoreChunksOneLaunch || static_cast<int64_t>(p.Hkv) * p.n_sub > kScoreGroupsOneLaunch)) {
     const hipError_t e = launch_chunk_scores(p, score_row, row_path, row_count, scores, stream);
     return e != hipSuccess ? e : launch_select_chunks(scores, p.C, k, idx_out, n_out, stream);

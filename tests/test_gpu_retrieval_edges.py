@@ -1,6 +1,8 @@
 """Edges of the score and selection kernels: lengths around one and four keys per thread of the byte-wise selection, all keys
 in one histogram bin, few distinct keys; scores of chunks of one to five blocks with a remainder of heads and chunks, and
 the one-launch form against the two calls on both sides of the line between one launch and two."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -84,13 +86,15 @@ def test_gather_list_shorter_than_its_room(monkeypatch):
 @pytest.mark.parametrize("Hq,Hkv,L,B", [
     (32, 8, 4096, 32),        # 128 chunks, 1024 groups: one launch
     (32, 8, 4097, 32),        # 129 chunks: two
-    (32, 8, 4864, 64),        # 76 chunks, 1216 groups: two
+    (32, 8, 4864, 64),        # 76 chunks, 1216 groups: one
     (6, 3, 500, 32),          # 6 heads: two of four lanes have one head more; 16 chunks
     (36, 12, 545, 32),        # 36 heads: nine per lane, one past a round of eight; 18 chunks, the last of one token
     (8, 2, 3000, 96),         # three blocks per chunk
     (8, 8, 2222, 160),        # five blocks per chunk
-    (32, 32, 3008, 32),       # 32 groups x 94 blocks = 3008: two launches
-    (32, 32, 2976, 32),       # 2976: one
+    (32, 32, 3008, 32),       # 32 heads x 94 blocks = 3008 groups: two launches
+    (32, 32, 2976, 32),       # 2976: two
+    (8, 8, 6400, 64),         # 100 chunks, 8 x 200 = 1600 groups: one
+    (8, 8, 6401, 64),         # 1608: two
 ])
 def test_scores_of_blocks_and_heads(Hq, Hkv, L, B):
     import paper_2505_20776_amd as sx
@@ -121,6 +125,38 @@ def test_scores_of_blocks_and_heads(Hq, Hkv, L, B):
         assert int(n_out) == k and list(idx.cpu().numpy()) == list(orc.select_chunks(got, k))
     buf.check_guards()
     check_scores(buf.scores.cpu().numpy(), ref, "all rows")
+
+
+def _launches(call):
+    """Kernels that the call launches: the nodes of a captured graph of it."""
+    paths = {line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line}
+    hip = ctypes.CDLL(paths.pop())
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# both sides of the line between one launch and two: 128 chunks, 1600 pair groups
+@pytest.mark.parametrize("Hkv,L,B,with_scores,launches", [
+    (8, 4096, 32, True, 1), (8, 4097, 32, True, 2), (8, 5120, 64, True, 1), (16, 2560, 64, True, 1), (32, 1600, 32, True, 1),
+    (8, 6400, 64, True, 1), (8, 6401, 64, True, 2), (8, 12000, 128, True, 2), (8, 12000, 128, False, 1), (2, 32768, 32, False, 1)])
+def test_launches_of_scores_and_selection(Hkv, L, B, with_scores, launches):
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    T, d, k = 2, 128, 4
+    g = torch.Generator(device="cuda").manual_seed(L)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    buf = hx.make_buffers(dtype="bf16", n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=d, prefix_len=L, n_tree=T, chunk_size=B, want_scores=True)
+    sx.verify_attn(buf.desc, rn(T, Hkv, d), rn(Hkv, L, d), rn(Hkv, L, d), rn(Hkv, T, d), rn(Hkv, T, d),
+                   torch.tensor([-1, 0], dtype=torch.int32, device="cuda"), buf.out, buf.lse, buf.workspace)
+    sc = torch.empty(-(-L // B), dtype=torch.float32, device="cuda") if with_scores else None
+    idx, n_out = torch.empty(k, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    assert _launches(lambda: sx.chunk_scores_select(buf.desc, buf.workspace, 1, k, idx, n_out, scores=sc)) == launches
 
 
 @pytest.mark.parametrize("dtype,B,L", [
