@@ -139,7 +139,7 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   // Split the prefix.  Every split but the last holds keys_per_split keys, a multiple of the kernel's key granule:
   //   key-split kernel                 128 (4 waves x 32 keys)
   //   row-split, vector-ALU kernel     64
-  //   fp32-probability kernel          a tile of a key group, 32 bf16 or 16 fp32 keys (with stage_cut a stage of all four)
+  //   fp32-probability kernel          a tile of a key group, 32 bf16 or 16 fp32 keys, or a stage of all four
   // and, with scores, of the chunk size, so that no chunk is shared by two splits.  The fp32-probability kernel keeps the
   // reference of every score block beside its sum, so there a chunk may lie in two splits; a score block (4, 8 or 16 keys) may
   // not, and as it divides the tile it does not.
@@ -160,10 +160,13 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   if (p->use_mfma == 2 && p->rows_per_group == 256 && d->num_splits == 0 &&
       static_cast<int64_t>(by_len) * p->Hkv * ((p->M + 127) / 128) <= device_cu_count())
     p->rows_per_group = 128;
-  // The fp32-probability kernel's splits end at whole tiles of a key group: at whole stages of the four, 4109 bf16 keys made
-  // seven splits of five stages where eight of four and a bit fit, 19.1 instead of 18.1 us; 3333 fp32 keys 26.4 and 24.6; 1100
-  // 17.5 and 17.7.  A requested count is cut the same way, so that the one that an automatic call reports gives its problem
-  // again; only where the static scratch array cannot hold a requested count is that cut at stages, which makes fewer splits.
+  // The fp32-probability kernel's splits may end at whole tiles of a key group.  An automatic count is cut so where that pays:
+  // a split's last stage is at most half full then, and there are at most a third more splits to merge than with splits of
+  // whole stages.  Attention call, us, cut at tiles / at stages (60 nodes, 32 heads in 8 groups): fp32 1200 keys (8 x 2.5 / 7
+  // x 3 stages) 32.4 / 33.3, 1600 36.7 / 37.3, 2200 41.0 / 42.1, bf16 2500 24.8 / 25.4, 4109 29.1 / 29.3; but fp32 600 (8 x 1.25 / 5
+  // x 2) 28.8 / 28.4, 800 (8 x 1.75 / 7 x 2) 30.6 / 29.5, 1300 (8 x 2.75 / 7 x 3) 34.3 / 33.3, bf16 1200 (8 x 1.25 / 5 x 2) 22.6 / 21.8.
+  // A requested count is always cut at tiles, so that the one that an automatic call reports gives as many splits again; only
+  // where the static scratch array cannot hold a requested count is that cut at stages, which makes fewer splits.
   int64_t unit = p->use_mfma == 1 ? 128 : 64;
   const int stage = p->in_dtype == SPECEXT_BF16 ? 128 : 64;
   if (p->use_mfma == 3) unit = stage_cut && d->num_splits != 0 ? stage : stage / 4;
@@ -181,8 +184,12 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
     if (want < 1) want = 1;
   }
   if (want > SPECEXT_MAX_SPLITS) want = SPECEXT_MAX_SPLITS;
-  int64_t per = (p->L + want - 1) / want;
-  per = (per + unit - 1) / unit * unit;
+  auto keys_of = [&](int64_t u) { return ((p->L + want - 1) / want + u - 1) / u * u; };
+  auto splits_of = [&](int64_t keys) { return (p->L + keys - 1) / keys; };
+  int64_t per = keys_of(unit);
+  if (p->use_mfma == 3 && d->num_splits == 0 &&
+      (per % stage * 2 > stage || splits_of(per) * 3 > splits_of(keys_of(stage)) * 4))
+    per = keys_of(stage);
   p->keys_per_split = static_cast<int32_t>(per);
   p->S = static_cast<int32_t>((p->L + per - 1) / per);
   // Tree pass and merge as the tail of the prefix launch (on request): row-split kernel

@@ -66,6 +66,17 @@ def test_workspace_and_splits(sx):
     assert sx.num_splits(d) == 2                        # vector-ALU kernel: 64-key granule
 
 
+@pytest.mark.parametrize("dtype,L,B,splits", [
+    ("f32", 1200, 32, 8), ("f32", 1600, 32, 8), ("f32", 2200, 32, 8), ("bf16", 2500, 16, 8), ("bf16", 4109, 16, 8),      # cut at tiles
+    ("f32", 600, 32, 5), ("f32", 800, 32, 7), ("f32", 1300, 32, 7), ("bf16", 1200, 16, 5), ("bf16", 1600, 16, 7),        # at stages
+    ("f32", 2048, 32, 8), ("f32", 64, 32, 1), ("bf16", 128, 16, 1)])                                                     # equal
+def test_automatic_splits_with_fp32_probabilities(sx, dtype, L, B, splits):
+    """60 nodes, 32 heads in 8 groups, 256 compute units: at most eight splits; the measured sides of the rule between the cuts."""
+    d = sx.make_desc(dtype=sx.SPECEXT_BF16 if dtype == "bf16" else sx.SPECEXT_F32, n_q_heads=32, n_kv_heads=8, head_dim=128, prefix_len=L,
+                     n_tree=60, chunk_size=B, want_scores=True)
+    assert sx.num_splits(d) == splits
+
+
 @pytest.mark.parametrize("dtype,d,hq,hkv,T,L,B", [
     ("bf16", 128, 32, 8, 60, 4109, 16), ("f32", 128, 32, 8, 60, 1100, 32), ("f32", 128, 32, 8, 60, 3333, 64),
     ("f32", 64, 4, 1, 8, 512, 32), ("f32", 64, 4, 1, 8, 300, 8), ("bf16", 64, 8, 2, 20, 1000, 12), ("bf16", 128, 32, 8, 8, 8155, 32),

@@ -75,7 +75,7 @@ def test_strided_keys_of_64(dtype):
     ("bf16", 32, 8, 128, 3000, 40, 16), ("bf16", 8, 2, 64, 1000, 20, 12), ("f32", 32, 8, 128, 3333, 25, 64),
     ("f32", 16, 8, 128, 1100, 40, 32), ("f32", 4, 1, 64, 300, 12, 8)])
 def test_splits_cut_at_tiles(dtype, Hq, Hkv, d, L, T, B):
-    """Automatic and requested split counts cut the prefix at whole tiles of a key group."""
+    """Automatic split counts cut the prefix at whole tiles of a key group or at stages of all four, requested ones at tiles."""
     from paper_2505_20776_amd import harness as hx
     rng = np.random.default_rng(L)
     wl = make_workload("tiles", seed=L, dtype=dtype, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, prefix_len=L,
