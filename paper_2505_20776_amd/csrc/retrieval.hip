@@ -433,9 +433,12 @@ __device__ __forceinline__ int chunk_tokens(int c, int n_chunks, int src_len, in
 // What bounds it: the launch and two trips to memory, the list and then the rows.  So the list's length, the workgroup's
 // entry and the first 64 entries are requested together, and every wave adds up the tokens ahead for itself; with the three
 // behind one another and a workgroup-wide sum, 32 chunks of 32 tokens of 8 heads (4 MB of cold bf16 rows) took 4.7 us, this 4.2;
-// of 32 heads 7.2 and 6.6; four chunks of one fp32 head 2.8 and 2.5.
+// of 32 heads 7.2 and 6.6; four chunks of one fp32 head 2.8 and 2.5.  Behind more than kGatherAlone entries the waves share
+// the sum: each for itself, 256 chunks took 9.85 us as shared, but 1024 chunks of 16 tokens of 8 heads 39 instead of 32 us, 4096 of
+// 4 tokens of 2 heads 53 instead of 27.
 constexpr int kGatherAtOnce = 4;
 constexpr int kGatherThreads = 256;
+constexpr int kGatherAlone = 256;
 __global__ __launch_bounds__(kGatherThreads) void gather_copy_kernel(const int* __restrict__ idx, const int* __restrict__ n_idx, int max_idx,
                                                          int src_len, int chunk_size, int row_vecs, int src_cap, int dst_cap,
                                                          const uint4* __restrict__ k_src, const uint4* __restrict__ v_src,
@@ -448,8 +451,20 @@ __global__ __launch_bounds__(kGatherThreads) void gather_copy_kernel(const int* 
   asm volatile("" : "+s"(c), "+v"(first), "+s"(n_used));        // all three requested before the first is waited for
   n_used = min(max(n_used, 0), max_idx);
   const int n_chunks = (src_len + chunk_size - 1) / chunk_size;
-  // tokens of the first `end` list entries
+  // tokens of the first `end` list entries (the same `end` in the whole workgroup)
+  __shared__ int wave_tokens[kGatherThreads / 64];
   auto tokens_of = [&](int end) {
+    if (__builtin_expect(end > kGatherAlone, 0)) {
+      int part = 0;
+      for (int i = threadIdx.x; i < end; i += kGatherThreads) part += chunk_tokens(idx[i], n_chunks, src_len, chunk_size);
+      part = __builtin_amdgcn_readlane(wave_inclusive_scan(part), 63);
+      __syncthreads();                 // the sum before has been read
+      if (lane == 0) wave_tokens[threadIdx.x >> 6] = part;
+      __syncthreads();
+      int total = 0;
+      for (int w = 0; w < kGatherThreads / 64; ++w) total += wave_tokens[w];
+      return total;
+    }
     int part = lane < end ? chunk_tokens(first, n_chunks, src_len, chunk_size) : 0;
     for (int i = 64 + lane; i < end; i += 64) part += chunk_tokens(idx[i], n_chunks, src_len, chunk_size);
     return __builtin_amdgcn_readlane(wave_inclusive_scan(part), 63);

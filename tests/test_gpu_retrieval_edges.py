@@ -41,12 +41,14 @@ def test_selection_within_one_wave(n):
             assert (raw[n_out:] == -1).all()
 
 
-@pytest.mark.parametrize("n_list,n_idx", [(1, 1), (63, 63), (64, 64), (65, 65), (65, 64), (130, 129), (64, 0), (64, 70)])
+@pytest.mark.parametrize("n_list,n_idx", [(1, 1), (63, 63), (64, 64), (65, 65), (65, 64), (130, 129), (64, 0), (64, 70),
+                                          (256, 256), (257, 257), (258, 258), (600, 600), (600, 300), (1030, 1030)])
 def test_gather_lists_around_a_wave(n_list, n_idx):
-    """List entries from the 65th on are read in a second step; entries that contribute fewer or no tokens before and behind."""
+    """List entries from the 65th on are read in a second step, behind more than 256 of them by the whole workgroup; entries that
+    contribute fewer or no tokens before and behind."""
     from paper_2505_20776_amd import harness as hx
     B, H, d = 9, 2, 64                      # 72 vectors of 16 bytes per chunk
-    C = 140
+    C = max(140, n_list + 10)
     L = C * B - 4                           # the last chunk has five tokens
     g = torch.Generator(device="cuda").manual_seed(n_list)
     k = torch.randn((1, H, L, d), device="cuda", generator=g).to(torch.bfloat16)
