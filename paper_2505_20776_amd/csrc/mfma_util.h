@@ -5,6 +5,17 @@
 
 namespace specext {
 
+template <int I>
+using ic = std::integral_constant<int, I>;
+// f(ic<0>{}), f(ic<1>{}), ..., f(ic<N-1>{})
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(ic<I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float floatx2;
@@ -70,6 +81,11 @@ __device__ __forceinline__ void load_to_lds_16(unsigned lds_dst, unsigned voff, 
 __device__ __forceinline__ void load_to_lds_16_stream(unsigned lds_dst, unsigned voff, const unsigned char* base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                :: "s"(lds_dst), "v"(voff), "s"(base) : "memory", "m0");
+}
+
+// The same from a 64-bit address of each lane.
+__device__ __forceinline__ void load_to_lds_16_at(unsigned lds_dst, const unsigned char* src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_dst), "v"(src) : "memory", "m0");
 }
 
 // s_waitcnt vmcnt(n) for a run-time even n in [0, 24]

@@ -47,16 +47,6 @@ constexpr int kPrivBytes = 32 * kPatchStride;
 constexpr int lds_bytes(int kg) { return ring_bytes(kg) + (kg == 1 ? kWaves * kPrivBytes : kWaves / kg * 32 * kRowBytes); }
 static_assert(lds_bytes(1) <= 160 * 1024 && lds_bytes(2) <= 160 * 1024 && lds_bytes(4) <= 160 * 1024, "must fit the 160 KB of LDS");
 
-template <int I>
-using ic = std::integral_constant<int, I>;
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(ic<I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 template <int KG>
 __global__ __launch_bounds__(kWaves * 64) void prefill_rows_kernel(PrefillParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];

@@ -8,13 +8,15 @@
 // heads per group is matrix-bound (0.12 us of K/V traffic per us of matrix work), everything
 // else - softmax, LDS reads, loads - fits beside it.  One thread per query row on the vector
 // ALUs, which this replaces, left three of a compute unit's four SIMDs idle and read every K/V
-// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 27 us, 30
-// under the profiler (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first
-// tile, 4.3 us, the workgroup's own merge and stores, 4 us, and 20 % of the loop).
+// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 24.7 us
+// (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first tile, 2 us, the
+// workgroup's own merge and stores, 3 us, and the loop's other instructions: products of fp32 run on
+// the vector multipliers, so while one wave of a SIMD issues them the other's vector instructions
+// wait).
 // With bf16 inputs Q K^T is exact in bf16 products, and the probabilities go into P V as three
 // bf16 terms whose sum is the fp32 value (8 + 8 + 8 mantissa bits), so that nothing is rounded
 // and the product runs at a third of the bf16 rate instead of the fp32 one's sixteenth (4109
-// keys, 60 nodes: 6250 us before, 18 us here, 21 under the profiler).
+// keys, 60 nodes: 6250 us before, 16.3 us here).
 // The range is that of plain fp32 attention but for |V| near its end (the lagging reference lets
 // P reach 2^10: an exact running maximum takes 28.4 instead of 27.1 us at 2K and 86 instead of
 // 79.5 at 8K): infinite V, logits of minus infinity, of any finite size and scales of any size
@@ -26,7 +28,10 @@
 // SIMDs busy and the split count - the partial outputs that cross memory - stays low.
 //   tile    one key group's step: 16 keys (fp32) or 32 keys (bf16), the same bytes
 //   stage   KG tiles, one workgroup barrier; the ring in LDS holds 128 KB of stages (two of
-//           64 KB, four for head_dim 64), requested ahead by direct global->LDS loads
+//           64 KB, four for head_dim 64), requested ahead by direct global->LDS loads.  A compute
+//           unit takes in 64 bytes per clock: issuing a stage keeps its waves for 1000 cycles
+//           when all do it at once, so the upper half of a workgroup of eight waves begins a
+//           stage with the products that it still has to do (bf16 8K 22.6 -> 21.1 us per launch).
 // Workgroups of 128 rows with two key groups (half as many reads of every key, twice the partial
 // outputs) measured slower under the profiler: 32 against 29 us (fp32, 2K), 20.0 against 18.7 us
 // (bf16, 4109).
@@ -58,6 +63,9 @@ struct Tile {
   // 16-byte piece `c` of row `r` sits at piece c ^ k_swz(r) (K) or c ^ v_swz(r) (V) of its LDS row, so that the
   // operand reads spread over the banks: 16 rows x one piece for K; for a bf16 V 8 rows x 32 bytes (an fp32 V row is
   // read 256 consecutive bytes at a time and needs none)
+  // (k_swz repeats after 16 rows, v_swz after eight, which is so many loads)
+  static constexpr int kKPeriod = 16 / kRowsPerLoad;
+  static constexpr int kVPeriod = BF16 ? 8 / kRowsPerLoad : 1;
   static __device__ __forceinline__ int k_swz(int r) { return kRowBytes == 128 ? (r >> 1) & 7 : r & 15; }
   static __device__ __forceinline__ int v_swz(int r) {
     return !BF16 ? 0 : kRowBytes == 128 ? ((r >> 1) & 3) << 1 : (r & 7) << 1;
@@ -92,7 +100,14 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   using T = Tile<D, BF16>;
   constexpr int kStageBytes = KG * 2 * T::kBytes;
   constexpr int kStages = stages_of(kStageBytes);
-  constexpr int kLoadsPerStage = 2 * T::kLoads / RB;       // of one wave
+  constexpr int kSlotBytes = 2 * T::kBytes;                // one key group's place for a stage: K tile, V tile
+  constexpr int kGroupBytes = kStages * kSlotBytes;        // its ring; the key groups' rings stand side by side
+  constexpr int kTileLoads = T::kLoads / RB;               // direct loads of one wave per K or V tile
+  constexpr int kLoadsPerStage = 2 * kTileLoads;
+  // The first stage's V tiles, requested behind its K tiles, are waited for behind the first products only.  fp32 with 512-byte
+  // rows, whose products take long enough: 8 nodes of 4 heads, 1000 keys 6.26 -> 5.8 us, 80 rows at 2K 11.15 -> 10.3; the
+  // others are 0.1 - 0.3 us faster without the second barrier.
+  constexpr bool kSplitV = !BF16 && D == 128;
   constexpr int kSubTiles = T::kKeys / 16;                 // S^T blocks of 16 keys per tile
   constexpr int kQRegs = BF16 ? D / 32 : D / 16;           // 16-byte pieces of a query row per lane
   constexpr int kOBlocks = D / 16;                         // 16 x 16 output blocks per 16 rows
@@ -122,49 +137,113 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   const int ld_row = lane / T::kPieces;                    // row within one load
   const int ld_piece = lane % T::kPieces;
 
-  // this wave's share of the tile of its key group in stage st; keys past the split's end repeat its last one (masked below)
-  auto issue_stage = [&](int st) {
-    if (st >= my_tiles) return;
-    const int key0 = key_lo + (st * KG + kg) * T::kKeys;
-    const int last = key_hi - 1 - key0;
-    const unsigned dst = lds0 + (st % kStages) * kStageBytes + kg * (2 * T::kBytes);
-    const unsigned char* ksrc = kbase + key0 * key_bytes;
-    const unsigned char* vsrc = vbase + key0 * key_bytes;
+  // The loads of a stage, which is requested in order.  A whole tile's take a lane's offset within the tile, which stays the same,
+  // and a uniform base that moves on: no vector instructions, which would stand still while the other wave of the SIMD issues
+  // fp32 products (those run on the vector multipliers).  Keys past the split's end repeat its last one (masked below).
+  constexpr int kKOffs = T::kKPeriod > RB ? (kTileLoads < T::kKPeriod / RB ? kTileLoads : T::kKPeriod / RB) : 1;
+  constexpr int kVOffs = T::kVPeriod > RB ? T::kVPeriod / RB : 1;
+  const unsigned row_off = static_cast<unsigned>(ld_row) * static_cast<unsigned>(key_bytes);
+  unsigned k_off[kKOffs], v_off[kVOffs];
 #pragma unroll
-    for (int i = 0; i < T::kLoads / RB; ++i) {
-      const int u = rb + i * RB;
-      const int r = u * T::kRowsPerLoad + ld_row;
-      const unsigned off = static_cast<unsigned>(min(r, last)) * static_cast<unsigned>(key_bytes);
-      load_to_lds_16(dst + u * 1024, off + ((ld_piece ^ T::k_swz(r)) << 4), ksrc);
-      load_to_lds_16(dst + T::kBytes + u * 1024, off + ((ld_piece ^ T::v_swz(r)) << 4), vsrc);
+  for (int i = 0; i < kKOffs; ++i) k_off[i] = row_off + ((ld_piece ^ T::k_swz((rb + i * RB) * T::kRowsPerLoad + ld_row)) << 4);
+#pragma unroll
+  for (int i = 0; i < kVOffs; ++i) v_off[i] = row_off + ((ld_piece ^ T::v_swz((rb + i * RB) * T::kRowsPerLoad + ld_row)) << 4);
+  const int64_t first_off = (static_cast<int64_t>(key_lo) + kg * T::kKeys + rb * T::kRowsPerLoad) * key_bytes;
+  const unsigned char *k_next = kbase + first_off, *v_next = vbase + first_off;
+  const int64_t load_step = RB * T::kRowsPerLoad * key_bytes, stage_step = KG * T::kKeys * key_bytes;
+  const int whole_tiles = ((key_hi - key_lo) / T::kKeys - kg + KG - 1) / KG;       // of this key group
+  const unsigned group_lds = lds0 + kg * kGroupBytes;
+  auto issue_stage = [&](auto slot_c, int st) __attribute__((always_inline)) {
+    if (st >= my_tiles) return;
+    const unsigned dst = group_lds + decltype(slot_c)::value * kSlotBytes + rb * 1024;
+    if (__builtin_expect(st < whole_tiles, 1)) {
+      const unsigned char *ksrc = k_next, *vsrc = v_next;
+#pragma unroll
+      for (int i = 0; i < kTileLoads; ++i) {
+        load_to_lds_16(dst + i * RB * 1024, k_off[i % kKOffs], ksrc);
+        ksrc += load_step;
+      }
+#pragma unroll
+      for (int i = 0; i < kTileLoads; ++i) {
+        load_to_lds_16(dst + T::kBytes + i * RB * 1024, v_off[i % kVOffs], vsrc);
+        vsrc += load_step;
+      }
+      k_next += stage_step;
+      v_next += stage_step;
+    } else {
+      const int key0 = key_lo + (st * KG + kg) * T::kKeys;
+      const int last = key_hi - 1 - key0;
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const unsigned char* src = (v ? vbase : kbase) + key0 * key_bytes;
+#pragma unroll
+        for (int i = 0; i < kTileLoads; ++i) {
+          const int r = (rb + i * RB) * T::kRowsPerLoad + ld_row;
+          const unsigned off = static_cast<unsigned>(min(r, last)) * static_cast<unsigned>(key_bytes);
+          load_to_lds_16(dst + v * T::kBytes + i * RB * 1024, off + ((ld_piece ^ (v ? T::v_swz(r) : T::k_swz(r))) << 4), src);
+        }
+      }
     }
   };
 
-  // queries (B operand of S^T); rows past the last one repeat it and are never stored
-  uintx4 qf[NSUB][kQRegs];
+  // Queries (B operand of S^T) go through LDS, too, each row group's rows loaded once for all key groups, into the place of the
+  // last stage of the ring, which is requested when they have left it.  (Loaded into registers by every wave for itself they
+  // were four times the bytes, and the compiler, which counts only such loads, waited for the first stage behind them before
+  // their scaling.)  Rows past the last one repeat it and are never stored.
+  constexpr int kQLoads = kRows * T::kRowBytes / 1024;     // of a row group
+  static_assert(kRows * T::kRowBytes <= kSlotBytes && RB <= KG, "a row group's queries fit one key group's slot");
+  constexpr int kQSlot = kStages - 1;
+  const unsigned q_lds = lds0 + rb * kGroupBytes + kQSlot * kSlotBytes;
 #pragma unroll
-  for (int s = 0; s < NSUB; ++s) {
-    const int m = min(row0 + 16 * s + li, p.M - 1);
-    const int t = m / p.G;
-    const int h = g * p.G + (m - t * p.G);
-    const unsigned char* src = static_cast<const unsigned char*>(p.q) + (t * p.q_st + h * p.q_sh) * T::kElem + 16 * qt;
-#pragma unroll
-    for (int j = 0; j < kQRegs; ++j) qf[s][j] = *reinterpret_cast<const uintx4*>(src + 64 * j);
+  for (int i = 0; i < (kQLoads + KG - 1) / KG; ++i) {
+    const int u = kg + i * KG;
+    if (u < kQLoads) {
+      const int r = u * T::kRowsPerLoad + ld_row;
+      const int m = min(row0 + r, p.M - 1);
+      const int t = static_cast<int>((static_cast<float>(m) + 0.5f) * (1.0f / static_cast<float>(p.G)));      // m / G, exact for m < 2^20
+      const int h = g * p.G + (m - t * p.G);
+      load_to_lds_16_at(q_lds + u * 1024, static_cast<const unsigned char*>(p.q) + (t * p.q_st + h * p.q_sh) * T::kElem + ((ld_piece ^ T::k_swz(r)) << 4));
+    }
   }
-  issue_stage(0);
-  // All query loads have landed, stage 0 may still be in flight (0x0F70: other counters untouched).  The compiler counts only
-  // the query loads, the tiles being requested by inline assembly, and waits for each of them once more where the scaling below
-  // uses it: down to vmcnt(0), which is stage 0, and for head_dim 64 the later stages requested by then.  So the scaling follows
-  // the first stage's landing; inside the loop there is no such wait.
-  constexpr int kInFlight = kLoadsPerStage;
-  if (my_tiles > 0) __builtin_amdgcn_s_waitcnt((kInFlight & 15) | (kInFlight >> 4 << 14) | 0x0F70);
-  else __builtin_amdgcn_s_waitcnt(0x0F70);
+  static_for<0, kStages - 1>([&](auto st_c) { issue_stage(st_c, decltype(st_c)::value); });
+  const int ahead = min(my_tiles, kStages - 1);            // stages requested so far
+
+  // Operand reads take these as LDS addresses plus immediates (again no vector instructions in a stage), pinned in registers so
+  // that the compiler does not rebuild them.  K (and query) piece 4 j + quarter of row 16 u + li: from j = 4 on 256 bytes further.
+  constexpr int kKAddrs = kQRegs < 4 ? kQRegs : 4;
+  unsigned kq_off[kKAddrs], k_addr[kKAddrs];
 #pragma unroll
-  for (int st = 1; st < kStages - 1; ++st) issue_stage(st);
+  for (int j = 0; j < kKAddrs; ++j) {
+    kq_off[j] = li * T::kRowBytes + (((4 * j + qt) ^ T::k_swz(li)) << 4);
+    k_addr[j] = group_lds + kq_off[j];
+    asm volatile("" : "+v"(k_addr[j]));
+  }
+  // V: fp32 key 4 quarter + i, 16 bytes of a 64-column block; bf16 transposing reads of keys 16 u + 4 quarter ..
+  constexpr int kVAddrs = BF16 ? kOBlocks : 1;
+  unsigned v_addr[kVAddrs];
+#pragma unroll
+  for (int b = 0; b < kVAddrs; ++b) {
+    if constexpr (BF16) {
+      const int r = 4 * qt + (li >> 2);
+      v_addr[b] = group_lds + T::kBytes + r * T::kRowBytes + (((2 * b + ((li & 3) >> 1)) ^ T::v_swz(r)) << 4) + ((li & 1) << 3);
+    } else {
+      v_addr[b] = group_lds + T::kBytes + 4 * qt * T::kRowBytes + (li << 4);
+    }
+    asm volatile("" : "+v"(v_addr[b]));
+  }
+  auto lds_read = [&](unsigned addr) { return *reinterpret_cast<const lds_uintx4*>(static_cast<uintptr_t>(addr)); };
+
   // The scale's power of two goes into the queries (exact), so that a logit that is finite scaled is finite as the product
   // leaves it: 1 / sqrt(d) and the factor of base 2 make it a sixth to an eighth.
   const int scale_exp = max(-16, min(0, static_cast<int>(__float_as_uint(p.scale_log2) >> 23) - 127));
   const float q_scale = __uint_as_float(static_cast<uint32_t>(127 + scale_exp) << 23);
+  uintx4 qf[NSUB][kQRegs];
+  wait_vmcnt_even(kLoadsPerStage * ahead);                 // this wave's query rows have landed
+  lds_barrier();
+#pragma unroll
+  for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+    for (int j = 0; j < kQRegs; ++j) qf[s][j] = lds_read(q_lds + kq_off[j % kKAddrs] + 16 * s * T::kRowBytes + 256 * (j / kKAddrs));
 #pragma unroll
   for (int s = 0; s < NSUB; ++s)
 #pragma unroll
@@ -203,19 +282,15 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   floatx4 s_acc[NSUB][kSubTiles];      // the tile's logits, then its probabilities
   uintx4 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
   uintx4 vf[kOBlocks];                 // fp32: [key i of the quarter][64-column block]; bf16: [16-column block]
-  auto tile_logits = [&](int st) __attribute__((always_inline)) {
-    const unsigned char* ktile = lds + (st % kStages) * kStageBytes + kg * (2 * T::kBytes);
-    const unsigned char* vtile = ktile + T::kBytes;
+  auto tile_logits = [&](auto slot_c, int st) __attribute__((always_inline)) {
+    constexpr unsigned slot = decltype(slot_c)::value * kSlotBytes;
     // all K fragments of the tile are requested before the first product (one at a time, every product would wait for
     // its own LDS read)
     uintx4 kf[kSubTiles][kQRegs];
 #pragma unroll
     for (int u = 0; u < kSubTiles; ++u)
 #pragma unroll
-      for (int j = 0; j < kQRegs; ++j) {
-        const int r = 16 * u + li;
-        kf[u][j] = *reinterpret_cast<const uintx4*>(ktile + r * T::kRowBytes + (((4 * j + qt) ^ T::k_swz(r)) << 4));
-      }
+      for (int j = 0; j < kQRegs; ++j) kf[u][j] = lds_read(k_addr[j % kKAddrs] + (slot + 16 * u * T::kRowBytes + 256 * (j / kKAddrs)));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < kSubTiles; ++u) {
@@ -239,20 +314,22 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
         }
       }
     }
+    if (kSplitV && st == 0) {
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vmcnt_even(kLoadsPerStage * max(0, min(my_tiles, kStages) - 1));
+      lds_barrier();
+    }
     // and the V fragments before the softmax, which hides their reads
 #pragma unroll
     for (int b = 0; b < kOBlocks; ++b) {
       if constexpr (BF16) {
         shortx4 half[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int r = 16 * u + 4 * qt + (li >> 2);
-          const unsigned char* src = vtile + r * T::kRowBytes + (((2 * b + ((li & 3) >> 1)) ^ T::v_swz(r)) << 4) + ((li & 1) << 3);
-          half[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)src);
-        }
+        for (int u = 0; u < 2; ++u)
+          half[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)static_cast<uintptr_t>(v_addr[b] + (slot + 16 * u * T::kRowBytes)));
         vf[b] = __builtin_bit_cast(uintx4, __builtin_shufflevector(half[0], half[1], 0, 1, 2, 3, 4, 5, 6, 7));
       } else {
-        vf[b] = *reinterpret_cast<const uintx4*>(vtile + (4 * qt + b / (D / 64)) * T::kRowBytes + ((16 * (b % (D / 64)) + li) << 4));
+        vf[b] = lds_read(v_addr[0] + (slot + b / (D / 64) * T::kRowBytes + 256 * (b % (D / 64))));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -395,24 +472,36 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   };
   auto key_loop = [&](auto rotated_c) __attribute__((always_inline)) {
     constexpr bool kRotated = decltype(rotated_c)::value;
-    for (int st = 0; st < n_stages; ++st) {
-      // this wave's loads of stage st have landed when no more than those of the stages requested behind it are pending
-      // (score stores in between only make the wait longer); its reads of the stage before, whose place is filled next, are done
-      wait_vmcnt_even(kLoadsPerStage * max(0, min(my_tiles - 1 - st, kStages - 2)));
-      if (kRotated) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      lds_barrier();
-      issue_stage(st + kStages - 1);
-      if (kRotated) {
-        if (st > 0 && st <= my_tiles) second_product();
-        if (st < my_tiles) {
-          tile_logits(st);
-          tile_softmax(st);
+    for (int s0 = 0; s0 < n_stages; s0 += kStages) {
+      static_for<0, kStages>([&](auto slot_c) {
+        constexpr int slot = decltype(slot_c)::value;
+        const int st = s0 + slot;
+        if (__builtin_expect(st < n_stages, 1)) {
+          // this wave's loads of stage st (in the first perhaps of its K tile alone) have landed when no more than those requested behind
+          // them are pending (score stores in between only make the wait longer); its reads of the stage before, whose place is
+          // filled next, are done
+          if (__builtin_expect(st == 0, 0)) wait_vmcnt_even(my_tiles > 0 ? kLoadsPerStage * (ahead - 1) + (kSplitV ? kTileLoads : 0) : 0);
+          else if (kStages == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          else wait_vmcnt_even(kLoadsPerStage * max(0, min(my_tiles - 1 - st, kStages - 2)));
+          if (kRotated || slot == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          lds_barrier();
+          if (kRotated) {
+            if (st > 0 && st <= my_tiles) second_product();
+            issue_stage(ic<(slot + kStages - 1) % kStages>{}, st + kStages - 1);
+            if (st < my_tiles) {
+              tile_logits(slot_c, st);
+              tile_softmax(st);
+            } else if (kSplitV && st == 0) lds_barrier();
+          } else {
+            issue_stage(ic<(slot + kStages - 1) % kStages>{}, st + kStages - 1);
+            if (st < my_tiles) {
+              tile_logits(slot_c, st);
+              tile_softmax(st);
+              second_product();
+            } else if (kSplitV && st == 0) lds_barrier();
+          }
         }
-      } else if (st < my_tiles) {
-        tile_logits(st);
-        tile_softmax(st);
-        second_product();
-      }
+      });
     }
     if (kRotated && my_tiles == n_stages) second_product();
   };

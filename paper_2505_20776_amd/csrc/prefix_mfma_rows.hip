@@ -68,17 +68,6 @@ constexpr int kPrivBytes = 32 * kPatchStride;
 constexpr int lds_bytes(int waves, int stages) { return ring_bytes(stages) + waves * kPrivBytes + tail_private_bytes(waves * 64); }
 static_assert(kDeepStages >= 2 && lds_bytes(8, kDeepStages) <= 160 * 1024, "rings and private areas must fit the 160 KB of LDS");
 
-template <int I>
-using ic = std::integral_constant<int, I>;
-// f(ic<0>{}), f(ic<1>{}), ..., f(ic<N-1>{})
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(ic<I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 // KPR = keys per 256-byte LDS row: 1 for head_dim 128.  For head_dim 64 (KPR = 2, keys
 // contiguous in memory) two consecutive keys share a row and the whole tile machinery -
 // loads, swizzles, operand reads - is the same; a tile is then 64 keys, the logits of the
