@@ -8,7 +8,7 @@
 // heads per group is matrix-bound (0.12 us of K/V traffic per us of matrix work), everything
 // else - softmax, LDS reads, loads - fits beside it.  One thread per query row on the vector
 // ALUs, which this replaces, left three of a compute unit's four SIMDs idle and read every K/V
-// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 24.7 us
+// element from LDS once per row: 3370 us at fp32, 2K tokens, 32/8 heads, 60 nodes; here 24.5 us
 // (13.6 us of matrix instructions at 2.4 GHz; the rest is the way to the first tile, 2 us, the
 // workgroup's own merge and stores, 3 us, and the loop's other instructions: products of fp32 run on
 // the vector multipliers, so while one wave of a SIMD issues them the other's vector instructions
@@ -16,7 +16,7 @@
 // With bf16 inputs Q K^T is exact in bf16 products, and the probabilities go into P V as three
 // bf16 terms whose sum is the fp32 value (8 + 8 + 8 mantissa bits), so that nothing is rounded
 // and the product runs at a third of the bf16 rate instead of the fp32 one's sixteenth (4109
-// keys, 60 nodes: 6250 us before, 16.3 us here).
+// keys, 60 nodes: 6250 us before, 16.0 us here).
 // The range is that of plain fp32 attention but for |V| near its end (the lagging reference lets
 // P reach 2^10: an exact running maximum takes 28.4 instead of 27.1 us at 2K and 86 instead of
 // 79.5 at 8K): infinite V, logits of minus infinity, of any finite size and scales of any size
@@ -280,6 +280,7 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   // matrix pipe idle; so the upper half of a workgroup of eight waves (wave w + 4 shares wave w's SIMD) starts a stage with
   // the second product of the tile before (bf16 inputs, 4109 keys: 18.7 instead of 19.9 us; fp32 inputs: equal).
   floatx4 s_acc[NSUB][kSubTiles];      // the tile's logits, then its probabilities
+  float score_part[NSUB][kSubTiles];   // a lane's sums of them
   uintx4 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
   uintx4 vf[kOBlocks];                 // fp32: [key i of the quarter][64-column block]; bf16: [16-column block]
   auto tile_logits = [&](auto slot_c, int st) __attribute__((always_inline)) {
@@ -409,23 +410,9 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
       for (int u = 0; u < kSubTiles; ++u) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) s_acc[s][u][i] = fast_exp2(s_acc[s][u][i]);
-        float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
+        const float part = (s_acc[s][u][0] + s_acc[s][u][1]) + (s_acc[s][u][2] + s_acc[s][u][3]);
         run_sum[s] += part;
-        if constexpr (SCORES == 2) {
-          // blocks of 16 keys, the usual case: no choices
-          part = halves_sum(rows16_sum(part));
-          if (16 * u < left && qt == 0 && row0 + 16 * s + li < p.M)
-            *reinterpret_cast<floatx2*>(score_row + (static_cast<int64_t>(key0 / 16 + u) * p.M + 16 * s) * 2) = floatx2{part, ref[s]};
-        } else if constexpr (SCORES == 1) {
-          // one (sum, reference) pair per score_gran keys: 4 (a lane quarter), 8 or 16
-          if (p.score_gran >= 8) part = rows16_sum(part);
-          if (p.score_gran >= 16) part = halves_sum(part);
-          const int key = key0 + 16 * u + 4 * qt;
-          const int m = row0 + 16 * s + li;
-          if (((4 * qt) & (p.score_gran - 1)) == 0 && key < key_hi && m < p.M)
-            *reinterpret_cast<floatx2*>(p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + (key >> gran_log2)) * p.M + m) * 2) =
-                floatx2{part, ref[s]};
-        }
+        if (SCORES) score_part[s][u] = part;
       }
     }
     if constexpr (BF16) {
@@ -446,6 +433,34 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
           }
         }
     }
+  };
+  // The (sum, reference) pairs of the score blocks of the tile that the softmax was last done for, in stage st.  The upper waves
+  // end a stage with their softmax, which nothing overlaps, so they store behind the second product that follows (fp32 4K 41.3
+  // -> 40.5 us, bf16 4109 keys 16.3 -> 16.0; the lower ones doing so as well: 24.5 -> 24.7 us at fp32 2K, 16.0 -> 16.1).
+  auto store_scores = [&](int st) __attribute__((always_inline)) {
+    const int key0 = key_lo + (st * KG + kg) * T::kKeys;
+    const int left = key_hi - key0;
+#pragma unroll
+    for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+      for (int u = 0; u < kSubTiles; ++u) {
+        float part = score_part[s][u];
+        if constexpr (SCORES == 2) {
+          // blocks of 16 keys, the usual case: no choices
+          part = halves_sum(rows16_sum(part));
+          if (16 * u < left && qt == 0 && row0 + 16 * s + li < p.M)
+            *reinterpret_cast<floatx2*>(score_row + (static_cast<int64_t>(key0 / 16 + u) * p.M + 16 * s) * 2) = floatx2{part, ref[s]};
+        } else if constexpr (SCORES == 1) {
+          // one (sum, reference) pair per score_gran keys: 4 (a lane quarter), 8 or 16
+          if (p.score_gran >= 8) part = rows16_sum(part);
+          if (p.score_gran >= 16) part = halves_sum(part);
+          const int key = key0 + 16 * u + 4 * qt;
+          const int m = row0 + 16 * s + li;
+          if (((4 * qt) & (p.score_gran - 1)) == 0 && key < key_hi && m < p.M)
+            *reinterpret_cast<floatx2*>(p.chunk_part + ((static_cast<int64_t>(g) * p.n_sub + (key >> gran_log2)) * p.M + m) * 2) =
+                floatx2{part, ref[s]};
+        }
+      }
   };
   auto second_product = [&]() __attribute__((always_inline)) {
     if constexpr (BF16) {
@@ -486,7 +501,10 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
           if (kRotated || slot == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           lds_barrier();
           if (kRotated) {
-            if (st > 0 && st <= my_tiles) second_product();
+            if (st > 0 && st <= my_tiles) {
+              second_product();
+              store_scores(st - 1);
+            }
             issue_stage(ic<(slot + kStages - 1) % kStages>{}, st + kStages - 1);
             if (st < my_tiles) {
               tile_logits(slot_c, st);
@@ -497,13 +515,17 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
             if (st < my_tiles) {
               tile_logits(slot_c, st);
               tile_softmax(st);
+              store_scores(st);
               second_product();
             } else if (kSplitV && st == 0) lds_barrier();
           }
         }
       });
     }
-    if (kRotated && my_tiles == n_stages) second_product();
+    if (kRotated && my_tiles == n_stages) {
+      second_product();
+      store_scores(n_stages - 1);
+    }
   };
   if (RB * KG == 8 && wave >= 4) key_loop(std::integral_constant<bool, true>{});
   else key_loop(std::integral_constant<bool, false>{});
