@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
   constexpr int kThreads = kShareWaves * 64;
   static_assert(SPECEXT_MAX_TREE <= kThreads, "one parent entry per thread");
   static_assert(PER >= 1 && PER <= 16, "a group of 16 lanes holds one (max, sum) pair per lane");
-  __shared__ int parent_lds[SPECEXT_MAX_TREE];
+  __shared__ int parent_lds[SPECEXT_MAX_TREE], fourth_lds[SPECEXT_MAX_TREE];
   __shared__ __attribute__((aligned(16))) float slots[kShareWaves][kRowsPerWave][kShareSlot];
   __shared__ int any_bad;
   const int tid = threadIdx.x;
@@ -435,7 +435,12 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
 
   // parent[] first, then everything else that depends on nothing; loads return in issue order
   const int par_reg = tid < p.T ? p.parent[tid] : -1;
-  const int row_raw = blockIdx.x * kRowsPerWave + rg;
+  // Workgroups 256 apart share a compute unit, where those of 64 or 128 nodes' heads would have nodes of like depth: every other
+  // 256 are taken from their end.
+  const int chunk_lo = static_cast<int>(blockIdx.x) & ~255;
+  const int chunk_hi = min(chunk_lo + 256, (n_rows + kRowsPerWave - 1) / kRowsPerWave);
+  const int block = (chunk_lo & 256) ? chunk_lo + chunk_hi - 1 - static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x);
+  const int row_raw = block * kRowsPerWave + rg;
   const bool live = row_raw < n_rows;
   const int row = live ? row_raw : n_rows - 1;   // groups past the end repeat the last row and store nothing
   const int g = static_cast<int>((static_cast<float>(row) + 0.5f) * (1.0f / static_cast<float>(p.M)));
@@ -484,36 +489,80 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
   }
 
-  // Ancestor chain of the row's node (the node itself first).  Every wave walks the whole
-  // chain and keeps the nodes at positions wave, wave + 4, ...; kAnc of them per batch.  A
-  // malformed parent entry ends the walk (the node is then treated as a root).
+  // Ancestor chain of the row's node (the node itself first).  Wave w takes the nodes at positions w, w + 4, ...  Every
+  // wave walks the first eight, and their K/V rows are requested here: most trees are not deeper.  A malformed parent
+  // entry ends the walk (the node is then treated as a root).
   constexpr int kAnc = 8 / kShareWaves;
-  int a = t;
-  int anc[kAnc];
-  RowWords kraw[kAnc], vraw[kAnc];
-  auto request_batch = [&]() {
+  auto parent_of = [&](int node) {
+    const int par = parent_lds[node];
+    return par >= node || par < -1 ? -1 : par;
+  };
+  // a wave's share of the ancestors, N at a time: nodes (-1 behind the chain's end), K and V rows
+  auto request_rows = [&](const auto& anc, auto& kraw, auto& vraw) __attribute__((always_inline)) {
+    constexpr int kN = sizeof(anc) / sizeof(int);
 #pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
-#pragma unroll
-      for (int w = 0; w < kShareWaves; ++w) {
-        if (w == wave) anc[u] = a;
-        if (a >= 0) {
-          const int par = parent_lds[a];
-          a = (par >= a || par < -1) ? -1 : par;
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
+    for (int u = 0; u < kN; ++u) {
       const int64_t off = g * p.kt_sh + max(anc[u], 0) * p.kt_st + li * E;
       kraw[u] = load_words<RW, false>(reinterpret_cast<const uint32_t*>(static_cast<const unsigned char*>(p.kt) + off * kInBytes));
       vraw[u] = load_words<RW, false>(reinterpret_cast<const uint32_t*>(static_cast<const unsigned char*>(p.vt) + off * kInBytes));
     }
   };
-  request_batch();
+  int a = t;
+  auto walk_eight = [&](int (&nodes)[kAnc]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kAnc; ++u) {
+#pragma unroll
+      for (int w = 0; w < kShareWaves; ++w) {
+        if (w == wave) nodes[u] = a;
+        if (a >= 0) a = parent_of(a);
+      }
+    }
+  };
+  int anc[kAnc];
+  RowWords kraw[kAnc], vraw[kAnc];
+  walk_eight(anc);
+  request_rows(anc, kraw, vraw);
   // the rest of the partials goes behind the K/V rows, which would otherwise queue behind all of them
 #pragma unroll
   for (int u = kFirst; u < PER; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
+
+  // A deeper chain (the same for all four waves, which serve the same rows): positions 8 to 15 the same way, and behind those
+  // every node's fourth ancestor goes to LDS, so that a wave steps from one of its nodes to the next with one read, and the rows
+  // are requested a batch ahead, without a branch.  Chains, us per launch (32 heads in 8 groups, bf16): with every wave walking
+  // the whole chain and a batch's rows requested when the one before was done 16 nodes 4.7, 60 nodes at 2K 10.1, 128 at 4K 24.3;
+  // so 4.2, 8.3 and 18.7, with the workgroups' turn above 7.4 and 14.9 (flat trees 3.8, 4.7 and 6.8 either way).
+  constexpr int kDeep = RW == 8 ? 2 : 4;         // (more would cost registers that a second workgroup needs)
+  const bool deep = __any(a >= 0);
+  bool deeper = false;
+  int next = -1;
+  int anc2[kAnc], anc_a[kDeep], anc_b[kDeep];
+  RowWords k2[kAnc], v2[kAnc], k_a[kDeep], v_a[kDeep], k_b[kDeep], v_b[kDeep];
+  auto walk = [&](int (&nodes)[kDeep]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      nodes[u] = next;
+      if (next >= 0) next = fourth_lds[next];
+    }
+  };
+  if (__builtin_expect(deep, 0)) {
+    walk_eight(anc2);
+    request_rows(anc2, k2, v2);
+    deeper = __any(a >= 0);
+    if (deeper) {
+      next = a;                                  // position 16, then this wave's first node behind it
+      int x = tid < p.T ? tid : -1;
+#pragma unroll
+      for (int i = 0; i < kShareWaves; ++i) {
+        const int from_x = parent_of(max(x, 0)), from_next = parent_of(max(next, 0));
+        if (x >= 0) x = from_x;
+        if (next >= 0 && i < wave) next = from_next;
+      }
+      if (tid < p.T) fourth_lds[tid] = x;
+      __syncthreads();
+      walk(anc_a);
+      request_rows(anc_a, k_a, v_a);
+    }
+  }
 
 #ifdef SPECEXT_TAIL_STAMPS
   if constexpr (PART_F16) {
@@ -557,10 +606,11 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
   else add_splits(std::integral_constant<bool, false>{});
 
   // the wave's share of the tree part, one online-softmax step per batch
-  while (true) {
-    float sc[kAnc];
+  auto add_rows = [&](const auto& anc, const auto& kraw, auto& vraw) __attribute__((always_inline)) {
+    constexpr int kN = sizeof(anc) / sizeof(int);
+    float sc[kN];
 #pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
+    for (int u = 0; u < kN; ++u) {
       float dot = 0.f;
 #pragma unroll
       for (int e = 0; e < E; ++e) dot = fmaf(q[e], row_element<IN_BF16>(kraw[u], e), dot);
@@ -569,7 +619,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
     float bm = sc[0];
 #pragma unroll
-    for (int u = 1; u < kAnc; ++u) bm = fmaxf(bm, sc[u]);
+    for (int u = 1; u < kN; ++u) bm = fmaxf(bm, sc[u]);
     const float new_max = fmaxf(run_max, bm);
     // nothing seen so far and nothing in this batch: keep the empty state
     const float alpha = new_max > -INFINITY ? fast_exp2(run_max - new_max) : 1.f;
@@ -578,7 +628,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] *= alpha;
 #pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
+    for (int u = 0; u < kN; ++u) {
       const float pr = anc[u] >= 0 ? fast_exp2(sc[u] - new_max) : 0.f;
       // the row read in place of an ancestor that there is not may be infinite (fp16 partials hold no infinite V anyway)
       if (!PART_F16 && anc[u] < 0) vraw[u] = RowWords{};
@@ -586,8 +636,22 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
       for (int e = 0; e < E; ++e) o[e] = fmaf(pr, row_element<IN_BF16>(vraw[u], e), o[e]);
       run_sum += pr;
     }
-    if (!__any(a >= 0)) break;
-    request_batch();
+  };
+  add_rows(anc, kraw, vraw);
+  if (__builtin_expect(deep, 0)) add_rows(anc2, k2, v2);
+  if (__builtin_expect(deeper, 0)) {
+    while (true) {
+      bool more = __any(next >= 0);
+      walk(anc_b);
+      request_rows(anc_b, k_b, v_b);
+      add_rows(anc_a, k_a, v_a);
+      if (!more) break;
+      more = __any(next >= 0);
+      walk(anc_a);
+      request_rows(anc_a, k_a, v_a);
+      add_rows(anc_b, k_b, v_b);
+      if (!more) break;
+    }
   }
 
   // the wave's partial goes to LDS; wave w then finishes row w, one or two output elements per lane
@@ -598,7 +662,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     if (li == 0) *reinterpret_cast<float2*>(slot + D) = make_float2(run_max, run_sum);
   }
   __syncthreads();
-  const int frow = blockIdx.x * kRowsPerWave + wave;
+  const int frow = block * kRowsPerWave + wave;
   if (wave >= kRowsPerWave || frow >= n_rows) return;
   float2 st[kShareWaves];
 #pragma unroll
