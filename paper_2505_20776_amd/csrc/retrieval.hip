@@ -24,8 +24,9 @@ namespace {
 // [rows], as the prefix kernels write them), fetched from behind another XCD's L2, so the kernel is one
 // trip to memory if all of a thread's loads are in flight together and enough compute units ask.  Hence
 // one wavefront and 16 chunks per workgroup; 64 chunks per workgroup with a head's loads one after the
-// other took 5.5 us for 512 chunks of one block and 7.9 us for 512 of two (32 heads in 8 groups), this
-// 2.5 and 2.9 us.
+// other took 5.5 us for 512 chunks of one block and 7.9 us for 512 of two (32 heads in 8 groups), so
+// 2.5 and 2.9 us; with the accepted row read in one trip, the inputs among the first arguments and no
+// divisions by the group size 2.35 and 2.7.
 constexpr int kHeadsAtOnce = 8;                // heads of one thread whose loads are in flight together
 
 // NSUB score blocks per lane and step, QUADS quads per chunk: the smallest pair whose product covers a chunk's blocks
@@ -53,12 +54,26 @@ __host__ void with_score_shape(int blocks, F&& f) {
   else f(ScoreShape<4, 64>{});
 }
 
-// the tree row to score: given, or the acceptance walk's last accepted node read on the device
-__device__ __forceinline__ int scored_row(const AttnParams& p, int first_row, const int* row_path, const int* row_count) {
-  if (!row_path) return first_row;
-  const int cnt = min(*row_count, p.T);          // never past the path array, whatever the count says
-  const int node = cnt > 0 ? row_path[cnt - 1] : 0;
-  return (node >= 0 && node < p.T) ? node : 0;
+// The scores' inputs, the first arguments of both kernels (in registers at their start: common.h).
+#define SPECEXT_SCORE_PARAMS uint64_t path_at, uint64_t count_at, uint64_t part_at, uint64_t lse2_at, int T, int M, int G, int Hq, int n_sub, int per_chunk
+#define SPECEXT_SCORE_ARGS(p) address_of(row_path), address_of(row_count), address_of((p).chunk_part), address_of((p).lse2), (p).T, (p).M, (p).G, (p).Hq, (p).n_sub, (p).B / (p).score_gran
+struct ScoreInputs {
+  const float *part, *lse2;      // AttnParams::chunk_part, lse2
+  int M, G, Hq, n_sub, per_chunk;      // per_chunk: score blocks of a chunk
+};
+
+// The tree row to score: given, or the acceptance walk's last accepted node read on the device.  The count and all of the path
+// (n_tree entries, whatever the count says) are requested together: one trip to memory instead of two in front of the pairs'.
+__device__ __forceinline__ int scored_row(uint64_t path_at, uint64_t count_at, int T, int first_row) {
+  if (!path_at) return first_row;
+  const int* path = in_global<const int>(path_at);
+  const int lane = threadIdx.x & 63;
+  int count = *in_global<const int>(count_at), low = path[min(lane, T - 1)], high = path[min(lane + 64, T - 1)];
+  asm volatile("" : "+s"(count), "+v"(low), "+v"(high));
+  const int last = min(count, T) - 1;
+  if (last < 0) return 0;
+  const int node = last < 64 ? __builtin_amdgcn_readlane(low, last) : __builtin_amdgcn_readlane(high, last - 64);
+  return (node >= 0 && node < T) ? node : 0;
 }
 
 // value of quad lane I in every lane of the quad
@@ -70,12 +85,12 @@ __device__ __forceinline__ float quad_lane(float v) {
 // The four partial sums of chunk c that chunk_score adds, by the chunk's lanes; `lane` = number among them.  QUADS = 1: lane
 // p returns the p-th.  4 or 16: every lane returns the first, the others are zero.  64: the lanes of wave p return the p-th.
 template <class Shape>
-__device__ __forceinline__ float chunk_partial(const AttnParams& p, int t, int c, int lane) {
+__device__ __forceinline__ float chunk_partial(const ScoreInputs& p, int t, int c, int lane) {
   constexpr int kBlocks = Shape::kBlocks;
   const int part = lane & 3;
-  const int per_chunk = p.B / p.score_gran;
-  const int sub_lo = min(c, p.C - 1) * per_chunk;               // chunks past the end re-read the last one, unused
-  const int sub_hi = min(sub_lo + per_chunk, p.n_sub);
+  const int sub_lo = min(c * p.per_chunk, (p.n_sub - 1) / p.per_chunk * p.per_chunk);      // chunks past the end re-read the last one, unused
+  const int sub_hi = min(sub_lo + p.per_chunk, p.n_sub);
+  const float inv_g = 1.0f / static_cast<float>(p.G);
   float acc = 0.f;
   for (int sb0 = sub_lo + (lane >> 2); sb0 < sub_hi; sb0 += kBlocks * Shape::kQuads) {
     for (int hb = part; hb < p.Hq; hb += 4 * kHeadsAtOnce) {
@@ -84,10 +99,10 @@ __device__ __forceinline__ float chunk_partial(const AttnParams& p, int t, int c
 #pragma unroll
       for (int u = 0; u < kHeadsAtOnce; ++u) {
         const int h = min(hb + 4 * u, p.Hq - 1);                 // heads past the end re-read the last one, unused
-        const int g = h / p.G;
+        const int g = static_cast<int>((static_cast<float>(h) + 0.5f) * inv_g);      // h / G, exact for h < 2^20
         const int m = t * p.G + (h - g * p.G);
         l2[u] = p.lse2[g * p.M + m];
-        const float* src = p.chunk_part + (static_cast<int64_t>(g) * p.n_sub * p.M + m) * 2;
+        const float* src = p.part + (static_cast<int64_t>(g) * p.n_sub * p.M + m) * 2;
 #pragma unroll
         for (int b = 0; b < kBlocks; ++b)                         // blocks past the chunk's end re-read its last one, unused
           pair[u][b] = *reinterpret_cast<const float2*>(src + static_cast<int64_t>(min(sb0 + b * Shape::kQuads, sub_hi - 1)) * p.M * 2);
@@ -111,12 +126,12 @@ __device__ __forceinline__ float chunk_score(const AttnParams& p, int c, float p
 }
 
 template <class Shape>
-__global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(AttnParams p, int first_row, const int* row_path,
-                                                                       const int* row_count, float* scores) {
-  const int t = scored_row(p, first_row + blockIdx.y, row_path, row_count);
+__global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(SPECEXT_SCORE_PARAMS, AttnParams p, int first_row, float* scores) {
+  const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
+  const int t = scored_row(path_at, count_at, T, first_row + blockIdx.y);
   const int c = blockIdx.x * Shape::kChunks + threadIdx.x / Shape::kLanes;
   const int lane = threadIdx.x % Shape::kLanes;
-  const float acc = chunk_partial<Shape>(p, t, c, lane);
+  const float acc = chunk_partial<Shape>(in, t, c, lane);
   float parts[4] = {acc, 0.f, 0.f, 0.f};
   if constexpr (Shape::kQuads == 1) {
     parts[0] = quad_lane<0>(acc), parts[1] = quad_lane<1>(acc), parts[2] = quad_lane<2>(acc), parts[3] = quad_lane<3>(acc);
@@ -398,15 +413,15 @@ __global__ __launch_bounds__(kSelThreads) void select_radix_kernel(const float* 
 // chunks, up to 1024 threads), for problems whose pairs one compute unit takes in faster than a second launch
 // costs.  Scores with the arithmetic of chunk_scores_kernel: the same bits.  scores may be null.
 template <class Shape>
-__global__ __launch_bounds__(kRankMax) void score_select_kernel(AttnParams p, int score_row, const int* row_path,
-                                                               const int* row_count, int k, float* scores,
+__global__ __launch_bounds__(kRankMax) void score_select_kernel(SPECEXT_SCORE_PARAMS, AttnParams p, int score_row, int k, float* scores,
                                                                int* __restrict__ idx_out, int* __restrict__ n_out) {
   __shared__ RadixLds<1> radix;
   __shared__ float partial[kRankMax][4];
-  const int t = scored_row(p, score_row, row_path, row_count);
+  const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
+  const int t = scored_row(path_at, count_at, T, score_row);
   const int lane = threadIdx.x % Shape::kLanes;
   for (int c = threadIdx.x / Shape::kLanes; c < p.C; c += blockDim.x / Shape::kLanes) {
-    const float acc = chunk_partial<Shape>(p, t, c, lane);
+    const float acc = chunk_partial<Shape>(in, t, c, lane);
     if constexpr (Shape::kQuads == 1) partial[c][lane] = acc;
     else if constexpr (Shape::kQuads == 64) partial[c][lane >> 6] = acc;
     else if (lane < 4) partial[c][lane] = lane == 0 ? acc : 0.f;
@@ -556,7 +571,7 @@ hipError_t launch_chunk_scores(const AttnParams& p, int32_t score_row, const int
   with_score_shape(p.B / p.score_gran, [&](auto shape) {
     using Shape = decltype(shape);
     const dim3 grid((p.C + Shape::kChunks - 1) / Shape::kChunks, rows), block(Shape::kThreads);
-    chunk_scores_kernel<Shape><<<grid, block, 0, stream>>>(p, first, row_path, row_count, scores);
+    chunk_scores_kernel<Shape><<<grid, block, 0, stream>>>(SPECEXT_SCORE_ARGS(p), p, first, scores);
   });
   return hipGetLastError();
 }
@@ -583,7 +598,7 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
   with_score_shape(p.B / p.score_gran, [&](auto shape) {
     using Shape = decltype(shape);
     const int threads = Shape::kQuads > 1 ? 1024 : p.C <= 64 ? 256 : p.C <= 128 ? 512 : 1024;
-    score_select_kernel<Shape><<<dim3(1), dim3(threads), 0, stream>>>(p, score_row, row_path, row_count, k, scores, idx_out, n_out);
+    score_select_kernel<Shape><<<dim3(1), dim3(threads), 0, stream>>>(SPECEXT_SCORE_ARGS(p), p, score_row, k, scores, idx_out, n_out);
   });
   return hipGetLastError();
 }

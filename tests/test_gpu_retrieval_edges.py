@@ -144,6 +144,34 @@ def _launches(call):
 
 
 # both sides of the line between one launch and two: 128 chunks, 1600 pair groups
+def test_accepted_row_at_the_ends_of_the_path():
+    """The row that a walk of 128 nodes ends at: counts around a wavefront's 64 entries, at and beyond both ends, and entries that
+    are no node (row 0)."""
+    import paper_2505_20776_amd as sx
+    from paper_2505_20776_amd import harness as hx
+    T, L, B, k = 128, 200, 16, 4
+    wl = make_workload("path", seed=5, dtype="f32", n_q_heads=2, n_kv_heads=1, head_dim=64, prefix_len=L, parent=chain_tree(T),
+                       chunk_size=B, top_k=k, n_needles=0, value_std=1.0)
+    t = [hx.to_device(a, "f32") for a in (wl.q, wl.k_prefix, wl.v_prefix, wl.k_tree, wl.v_tree)]
+    buf = hx.make_buffers(dtype="f32", n_q_heads=2, n_kv_heads=1, head_dim=64, prefix_len=L, n_tree=T, chunk_size=B, want_scores=True)
+    sx.verify_attn(buf.desc, *t, torch.from_numpy(wl.parent).cuda(), buf.out, buf.lse, buf.workspace)
+    sx.chunk_scores(buf.desc, buf.workspace, -1, buf.scores)
+    order = np.random.default_rng(0).permutation(T).astype(np.int32)
+    order[[10, 70]] = -1, 128
+    path = torch.from_numpy(order).cuda()
+    for count in (-3, 0, 1, 2, 11, 63, 64, 65, 71, 127, 128, 129, 2 ** 30):
+        last = min(count, T) - 1
+        row = int(order[last]) if last >= 0 and 0 <= order[last] < T else 0
+        n_acc = torch.tensor([count], dtype=torch.int32, device="cuda")
+        one, both = (torch.zeros(buf.scores.shape[1], device="cuda") for _ in range(2))
+        idx, n_out = torch.empty(k, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+        sx.chunk_scores_accepted(buf.desc, buf.workspace, path, n_acc, one)
+        sx.chunk_scores_select(buf.desc, buf.workspace, 0, k, idx, n_out, scores=both, path=path, n_accept=n_acc)
+        torch.cuda.synchronize()
+        assert torch.equal(one, buf.scores[row]) and torch.equal(both, buf.scores[row]), count
+    buf.check_guards()
+
+
 @pytest.mark.parametrize("Hkv,L,B,with_scores,launches", [
     (8, 4096, 32, True, 1), (8, 4097, 32, True, 2), (8, 5120, 64, True, 1), (16, 2560, 64, True, 1), (32, 1600, 32, True, 1),
     (8, 6400, 64, True, 1), (8, 6401, 64, True, 2), (8, 12000, 128, True, 2), (8, 12000, 128, False, 1), (2, 32768, 32, False, 1)])
