@@ -508,27 +508,24 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
   };
   int a = t;
-  auto walk_eight = [&](int (&nodes)[kAnc]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
-#pragma unroll
-      for (int w = 0; w < kShareWaves; ++w) {
-        if (w == wave) nodes[u] = a;
-        if (a >= 0) a = parent_of(a);
-      }
-    }
-  };
   int anc[kAnc];
   RowWords kraw[kAnc], vraw[kAnc];
-  walk_eight(anc);
+#pragma unroll
+  for (int u = 0; u < kAnc; ++u) {
+#pragma unroll
+    for (int w = 0; w < kShareWaves; ++w) {
+      if (w == wave) anc[u] = a;
+      if (a >= 0) a = parent_of(a);
+    }
+  }
   request_rows(anc, kraw, vraw);
   // the rest of the partials goes behind the K/V rows, which would otherwise queue behind all of them
 #pragma unroll
   for (int u = kFirst; u < PER; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
 
-  // A deeper chain (the same for all four waves, which serve the same rows): positions 8 to 15 the same way, and behind those
-  // every node's fourth ancestor goes to LDS, so that a wave steps from one of its nodes to the next with one read, and the rows
-  // are requested a batch ahead, without a branch.  Chains, us per launch (32 heads in 8 groups, bf16): with every wave walking
+  // A deeper chain (the same for all four waves, which serve the same rows): positions 8 to 15 the same way.  Every node's fourth
+  // ancestor goes to LDS beside that, so that behind them a wave steps from one of its nodes to the next with one read, and the
+  // rows are requested a batch ahead, without a branch.  Chains, us per launch (32 heads in 8 groups, bf16): with every wave walking
   // the whole chain and a batch's rows requested when the one before was done 16 nodes 4.7, 60 nodes at 2K 10.1, 128 at 4K 24.3;
   // so 4.2, 8.3 and 18.7, with the workgroups' turn above 7.4 and 14.9 (flat trees 3.8, 4.7 and 6.8 either way).
   constexpr int kDeep = RW == 8 ? 2 : 4;         // (more would cost registers that a second workgroup needs)
@@ -545,20 +542,26 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
   };
   if (__builtin_expect(deep, 0)) {
-    walk_eight(anc2);
+    int fourth = tid < p.T ? tid : -1;           // of node tid, found beside the walk's first steps
+#pragma unroll
+    for (int u = 0; u < kAnc; ++u) {
+#pragma unroll
+      for (int w = 0; w < kShareWaves; ++w) {
+        if (w == wave) anc2[u] = a;
+        const int up = parent_of(max(a, 0));
+        if (u == 0) {
+          const int fourth_up = parent_of(max(fourth, 0));
+          if (fourth >= 0) fourth = fourth_up;
+        }
+        if (a >= 0) a = up;
+      }
+    }
     request_rows(anc2, k2, v2);
+    if (tid < p.T) fourth_lds[tid] = fourth;
+    __syncthreads();
     deeper = __any(a >= 0);
     if (deeper) {
-      next = a;                                  // position 16, then this wave's first node behind it
-      int x = tid < p.T ? tid : -1;
-#pragma unroll
-      for (int i = 0; i < kShareWaves; ++i) {
-        const int from_x = parent_of(max(x, 0)), from_next = parent_of(max(next, 0));
-        if (x >= 0) x = from_x;
-        if (next >= 0 && i < wave) next = from_next;
-      }
-      if (tid < p.T) fourth_lds[tid] = x;
-      __syncthreads();
+      next = anc2[kAnc - 1] >= 0 ? fourth_lds[anc2[kAnc - 1]] : -1;
       walk(anc_a);
       request_rows(anc_a, k_a, v_a);
     }
