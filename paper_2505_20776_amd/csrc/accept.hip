@@ -76,10 +76,9 @@ __global__ __launch_bounds__(kCommitThreads) void commit_tree_kv_kernel(CommitAr
 hipError_t launch_accept_greedy(const int32_t* parent, const int32_t* draft_token, const int32_t* target_token,
                                 const int32_t* first_target, int32_t n_tree, int32_t* path_out,
                                 int32_t* n_accept_out, int32_t* next_token_out, hipStream_t stream) {
-  accept_greedy_kernel<<<dim3(1), dim3(64), 0, stream>>>(address_of(parent), address_of(draft_token), address_of(target_token),
-                                                        address_of(first_target), n_tree, address_of(path_out),
-                                                        address_of(n_accept_out), address_of(next_token_out));
-  return hipGetLastError();
+  return launch_kernel(accept_greedy_kernel, dim3(1), dim3(64), 0, stream, address_of(parent), address_of(draft_token),
+                       address_of(target_token), address_of(first_target), n_tree, address_of(path_out),
+                       address_of(n_accept_out), address_of(next_token_out));
 }
 
 hipError_t launch_commit_tree_kv(const void* k_tree, const void* v_tree, void* k_cache, void* v_cache,
@@ -99,8 +98,8 @@ hipError_t launch_commit_tree_kv(const void* k_tree, const void* v_tree, void* k
                         static_cast<uint4*>(k_cache), static_cast<uint4*>(v_cache), tree_sl_bytes / 16, tree_sh_bytes / 16,
                         tree_st_bytes / 16, cache_sy_bytes / 16, cache_sh_bytes / 16, cache_sl_bytes / 16, max_accept, n_tree,
                         row_bytes / 16, n_kv_heads, prefix_len, static_cast<int32_t>(share)};
-  commit_tree_kv_kernel<<<dim3(static_cast<unsigned>(heads), static_cast<unsigned>(share)), dim3(kCommitThreads), 0, stream>>>(c);
-  return hipGetLastError();
+  return launch_kernel(commit_tree_kv_kernel, dim3(static_cast<unsigned>(heads), static_cast<unsigned>(share)), dim3(kCommitThreads), 0,
+                       stream, c);
 }
 
 }  // namespace specext

@@ -454,8 +454,7 @@ hipError_t launch_key_groups(const PrefillParams& p, hipStream_t stream) {
   }
   const int rows_per_wg = kWaves / KG * 32;
   dim3 grid(p.Hkv, (p.M + rows_per_wg - 1) / rows_per_wg);
-  kernel<<<grid, dim3(kWaves * 64), lds_bytes(KG), stream>>>(p);
-  return hipGetLastError();
+  return launch_kernel(kernel, grid, dim3(kWaves * 64), lds_bytes(KG), stream, p);
 }
 
 }  // namespace

@@ -615,9 +615,8 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   }
   const int rows_per_wg = 16 * NSUB * RB;
   dim3 grid(p.head_fastest ? p.Hkv : p.S, p.head_fastest ? p.S : p.Hkv, (p.M + rows_per_wg - 1) / rows_per_wg);
-  kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L, p.keys_per_split, p.M, p.G,
-                                                             static_cast<int>(p.kp_sl), p.head_fastest, p);
-  return hipGetLastError();
+  return launch_kernel(kernel, grid, dim3(kWaves * 64), kLdsBytes, stream, address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L,
+                       p.keys_per_split, p.M, p.G, static_cast<int>(p.kp_sl), p.head_fastest, p);
 }
 
 template <int D, bool BF16, int NSUB, int RB>

@@ -448,9 +448,8 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
     attr_set[dev].store(true, std::memory_order_release);
   }
   dim3 grid(p.S, p.Hkv, (p.M + 32 * RB - 1) / (32 * RB));
-  kernel<<<grid, dim3(kWaves * 64), kLdsBytes, stream>>>(address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L, p.keys_per_split, p.M, p.G,
-                                                             static_cast<int>(p.kp_sl), p);
-  return hipGetLastError();
+  return launch_kernel(kernel, grid, dim3(kWaves * 64), kLdsBytes, stream, address_of(p.kp), address_of(p.vp), address_of(p.q), p.kp_sh, p.L,
+                       p.keys_per_split, p.M, p.G, static_cast<int>(p.kp_sl), p);
 }
 
 }  // namespace

@@ -120,13 +120,15 @@ __device__ __forceinline__ float chunk_partial(const ScoreInputs& p, int t, int 
   return Shape::kQuads == 1 ? acc : Shape::kQuads == 4 ? row16_sum(acc) : wave_sum(acc);
 }
 
-__device__ __forceinline__ float chunk_score(const AttnParams& p, int c, float p0, float p1, float p2, float p3) {
-  const int size = min(p.B, p.L - c * p.B);
-  return (((p0 + p1) + p2) + p3) / (static_cast<float>(size) * static_cast<float>(p.Hq));
+// of chunk c of B keys of L
+__device__ __forceinline__ float chunk_score(int c, int B, int L, int Hq, float p0, float p1, float p2, float p3) {
+  const int size = min(B, L - c * B);
+  return (((p0 + p1) + p2) + p3) / (static_cast<float>(size) * static_cast<float>(Hq));
 }
 
 template <class Shape>
-__global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(SPECEXT_SCORE_PARAMS, AttnParams p, int first_row, float* scores) {
+__global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(SPECEXT_SCORE_PARAMS, int C, int B, int L, int first_row,
+                                                                       float* scores) {
   const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
   const int t = scored_row(path_at, count_at, T, first_row + blockIdx.y);
   const int c = blockIdx.x * Shape::kChunks + threadIdx.x / Shape::kLanes;
@@ -141,7 +143,8 @@ __global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(SPECEXT_S
     __syncthreads();
     for (int w = 0; w < 4; ++w) parts[w] = of_wave[w];
   }
-  if (lane == 0 && c < p.C) scores[static_cast<int64_t>(blockIdx.y) * p.C + c] = chunk_score(p, c, parts[0], parts[1], parts[2], parts[3]);
+  if (lane == 0 && c < C)
+    scores[static_cast<int64_t>(blockIdx.y) * C + c] = chunk_score(c, B, L, Hq, parts[0], parts[1], parts[2], parts[3]);
 }
 
 // --------------------------------------------------------------------------
@@ -413,14 +416,14 @@ __global__ __launch_bounds__(kSelThreads) void select_radix_kernel(const float* 
 // chunks, up to 1024 threads), for problems whose pairs one compute unit takes in faster than a second launch
 // costs.  Scores with the arithmetic of chunk_scores_kernel: the same bits.  scores may be null.
 template <class Shape>
-__global__ __launch_bounds__(kRankMax) void score_select_kernel(SPECEXT_SCORE_PARAMS, AttnParams p, int score_row, int k, float* scores,
-                                                               int* __restrict__ idx_out, int* __restrict__ n_out) {
+__global__ __launch_bounds__(kRankMax) void score_select_kernel(SPECEXT_SCORE_PARAMS, int C, int B, int L, int score_row, int k,
+                                                               float* scores, int* __restrict__ idx_out, int* __restrict__ n_out) {
   __shared__ RadixLds<1> radix;
   __shared__ float partial[kRankMax][4];
   const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
   const int t = scored_row(path_at, count_at, T, score_row);
   const int lane = threadIdx.x % Shape::kLanes;
-  for (int c = threadIdx.x / Shape::kLanes; c < p.C; c += blockDim.x / Shape::kLanes) {
+  for (int c = threadIdx.x / Shape::kLanes; c < C; c += blockDim.x / Shape::kLanes) {
     const float acc = chunk_partial<Shape>(in, t, c, lane);
     if constexpr (Shape::kQuads == 1) partial[c][lane] = acc;
     else if constexpr (Shape::kQuads == 64) partial[c][lane >> 6] = acc;
@@ -429,11 +432,11 @@ __global__ __launch_bounds__(kRankMax) void score_select_kernel(SPECEXT_SCORE_PA
   __syncthreads();
   const int c = threadIdx.x;
   float score[1] = {0.f};
-  if (c < p.C) {
-    score[0] = chunk_score(p, c, partial[c][0], partial[c][1], partial[c][2], partial[c][3]);
+  if (c < C) {
+    score[0] = chunk_score(c, B, L, Hq, partial[c][0], partial[c][1], partial[c][2], partial[c][3]);
     if (scores) scores[c] = score[0];
   }
-  radix_select_and_write<1>(score, p.C, k, idx_out, n_out, radix);
+  radix_select_and_write<1>(score, C, k, idx_out, n_out, radix);
 }
 
 // --------------------------------------------------------------------------
@@ -554,26 +557,21 @@ hipError_t launch_select_chunks(const float* scores, int32_t n_chunks, int32_t k
                                 int32_t* n_out, hipStream_t stream) {
   // a small input needs only as many waves as it has scores (fewer waves, cheaper barriers)
   const int threads = n_chunks >= kSelThreads ? kSelThreads : ((n_chunks + 63) / 64) * 64;
-  if (n_chunks <= kRankMax) {
-    select_radix_kernel<1><<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
-  } else if (n_chunks <= kRadixMax) {
-    select_radix_kernel<4><<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
-  } else {
-    select_kernel<<<dim3(1), dim3(threads), 0, stream>>>(scores, n_chunks, k, idx_out, n_out);
-  }
-  return hipGetLastError();
+  const auto kernel = n_chunks <= kRankMax ? select_radix_kernel<1> : n_chunks <= kRadixMax ? select_radix_kernel<4> : select_kernel;
+  return launch_kernel(kernel, dim3(1), dim3(threads), 0, stream, scores, n_chunks, k, idx_out, n_out);
 }
 
 hipError_t launch_chunk_scores(const AttnParams& p, int32_t score_row, const int32_t* row_path,
                                const int32_t* row_count, float* scores, hipStream_t stream) {
   const int rows = (score_row < 0 && !row_path) ? p.T : 1;
   const int first = score_row < 0 ? 0 : score_row;
+  hipError_t e = hipErrorInvalidValue;
   with_score_shape(p.B / p.score_gran, [&](auto shape) {
     using Shape = decltype(shape);
     const dim3 grid((p.C + Shape::kChunks - 1) / Shape::kChunks, rows), block(Shape::kThreads);
-    chunk_scores_kernel<Shape><<<grid, block, 0, stream>>>(SPECEXT_SCORE_ARGS(p), p, first, scores);
+    e = launch_kernel(chunk_scores_kernel<Shape>, grid, block, 0, stream, SPECEXT_SCORE_ARGS(p), p.C, p.B, p.L, first, scores);
   });
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int32_t* row_path,
@@ -595,12 +593,14 @@ hipError_t launch_score_select(const AttnParams& p, int32_t score_row, const int
     return e != hipSuccess ? e : launch_select_chunks(scores, p.C, k, idx_out, n_out, stream);
   }
   // at least one thread per chunk (selection), four or more for the scores as far as 1024 go
+  hipError_t e = hipErrorInvalidValue;
   with_score_shape(p.B / p.score_gran, [&](auto shape) {
     using Shape = decltype(shape);
     const int threads = Shape::kQuads > 1 ? 1024 : p.C <= 64 ? 256 : p.C <= 128 ? 512 : 1024;
-    score_select_kernel<Shape><<<dim3(1), dim3(threads), 0, stream>>>(SPECEXT_SCORE_ARGS(p), p, score_row, k, scores, idx_out, n_out);
+    e = launch_kernel(score_select_kernel<Shape>, dim3(1), dim3(threads), 0, stream, SPECEXT_SCORE_ARGS(p), p.C, p.B, p.L, score_row, k,
+                      scores, idx_out, n_out);
   });
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_gather(const void* k_src, const void* v_src, void* k_dst, void* v_dst,
@@ -609,15 +609,13 @@ hipError_t launch_gather(const void* k_src, const void* v_src, void* k_dst, void
                          int32_t chunk_size, int32_t* pos_out, int32_t* len_out, hipStream_t stream) {
   if (max_idx > 0 && n_lh > 0) {
     dim3 grid(max_idx, n_lh, 2);
-    gather_copy_kernel<<<grid, dim3(kGatherThreads), 0, stream>>>(
-        idx, n_idx, max_idx, src_len, chunk_size, row_bytes / 16, src_cap, dst_cap, static_cast<const uint4*>(k_src),
-        static_cast<const uint4*>(v_src), static_cast<uint4*>(k_dst), static_cast<uint4*>(v_dst), pos_out, len_out);
-    return hipGetLastError();
+    return launch_kernel(gather_copy_kernel, grid, dim3(kGatherThreads), 0, stream, idx, n_idx, max_idx, src_len, chunk_size, row_bytes / 16,
+                         src_cap, dst_cap, static_cast<const uint4*>(k_src), static_cast<const uint4*>(v_src),
+                         static_cast<uint4*>(k_dst), static_cast<uint4*>(v_dst), pos_out, len_out);
   }
   if (pos_out || len_out) {
-    gather_meta_kernel<<<dim3(1), dim3(256), 0, stream>>>(idx, n_idx, max_idx, src_len, dst_cap, chunk_size,
-                                                          pos_out, len_out);
-    return hipGetLastError();
+    return launch_kernel(gather_meta_kernel, dim3(1), dim3(256), 0, stream, idx, n_idx, max_idx, src_len, dst_cap, chunk_size, pos_out,
+                         len_out);
   }
   return hipSuccess;
 }

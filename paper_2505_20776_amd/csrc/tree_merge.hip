@@ -724,16 +724,15 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
 }
 
 template <int D, bool IN_BF16, bool PART_F16>
-void launch_shared(const AttnParams& p, dim3 grid, hipStream_t stream) {
-  const dim3 block(kShareWaves * 64);
-#define SPECEXT_MERGE_ARGS address_of(p.parent), address_of(p.part_ml), address_of(p.part_o), address_of(p.q), p.T, p.Hq, p.M, p.G, p.S, p
+hipError_t launch_shared(const AttnParams& p, dim3 grid, hipStream_t stream) {
   const int per = (p.S + kShareWaves - 1) / kShareWaves;       // splits per wave, rounded up to a power of two
-  if (per <= 1) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 1><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
-  else if (per <= 2) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 2><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
-  else if (per <= 4) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 4><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
-  else if (per <= 8) tree_merge_shared_kernel<D, IN_BF16, PART_F16, 8><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
-  else tree_merge_shared_kernel<D, IN_BF16, PART_F16, 16><<<grid, block, 0, stream>>>(SPECEXT_MERGE_ARGS);
-#undef SPECEXT_MERGE_ARGS
+  const auto kernel = per <= 1   ? tree_merge_shared_kernel<D, IN_BF16, PART_F16, 1>
+                      : per <= 2 ? tree_merge_shared_kernel<D, IN_BF16, PART_F16, 2>
+                      : per <= 4 ? tree_merge_shared_kernel<D, IN_BF16, PART_F16, 4>
+                      : per <= 8 ? tree_merge_shared_kernel<D, IN_BF16, PART_F16, 8>
+                                 : tree_merge_shared_kernel<D, IN_BF16, PART_F16, 16>;
+  return launch_kernel(kernel, grid, dim3(kShareWaves * 64), 0, stream, address_of(p.parent), address_of(p.part_ml), address_of(p.part_o),
+                       address_of(p.q), p.T, p.Hq, p.M, p.G, p.S, p);
 }
 
 }  // namespace
@@ -747,12 +746,11 @@ hipError_t launch_tree_merge(const AttnParams& p, hipStream_t stream) {
   const bool pre = p.S > 0;
 #ifndef SPECEXT_MERGE_ONE_WAVE_PER_ROWS
   if (p.S >= 1 && p.S <= 16 * kShareWaves) {
-    if (p.part_f16) launch_shared<128, true, true>(p, grid, stream);
-    else if (p.d == 128 && bf16) launch_shared<128, true, false>(p, grid, stream);
-    else if (p.d == 128) launch_shared<128, false, false>(p, grid, stream);
-    else if (bf16) launch_shared<64, true, false>(p, grid, stream);
-    else launch_shared<64, false, false>(p, grid, stream);
-    return hipGetLastError();
+    if (p.part_f16) return launch_shared<128, true, true>(p, grid, stream);
+    if (p.d == 128 && bf16) return launch_shared<128, true, false>(p, grid, stream);
+    if (p.d == 128) return launch_shared<128, false, false>(p, grid, stream);
+    if (bf16) return launch_shared<64, true, false>(p, grid, stream);
+    return launch_shared<64, false, false>(p, grid, stream);
   }
 #endif
 #define SPECEXT_LAUNCH(D_, BF_, F16_)                                                              \
