@@ -1,7 +1,8 @@
 // Prefix pass of Hybrid Tree Attention (SpecExtend Sec. 3.1) on the gfx950
 // matrix cores, row-split form: bf16 K/V streamed ONCE from HBM into ONE compute
 // unit each, fp32 accumulation.  Used when a KV head has more than 32 query rows
-// (tree nodes x heads in the GQA group); smaller problems take the key-split kernel.
+// (tree nodes x heads in the GQA group); smaller problems take it, with fp32 partials, for short
+// prefixes and where the K/V stream decides, else the key-split kernel (the rule is at the dispatch).
 //
 // Why this shape.  Measured on MI355X: the memory system delivers the same 5.5 - 6 TB/s
 // whether the bytes come from L2, the Infinity Cache or HBM, so every byte that passes
@@ -499,10 +500,10 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
 #endif
   const float l_tot = halves_sum(run_sum);
   const int64_t slot0 = static_cast<int64_t>(split) * p.Hq * p.T + g * p.M + row0;     // slot of the wave's first row
-  if constexpr (KPR == 2) {
-    // ---- head_dim 64: the partial goes out as it is, (reference, row sum) and the unnormalised
-    // O in fp32 (what the merge kernel reads for this head size); a lane owns one row and
-    // holds four consecutive columns per register quad
+  if (KPR == 2 || (WAVES == 4 && !p.part_f16)) {
+    // ---- head_dim 64, and at most 32 rows: the partial goes out as it is, (reference, row sum) and
+    // the unnormalised O in fp32 (what the merge kernel reads then); a lane owns one row and holds
+    // four consecutive columns per register quad.  (Through LDS as whole rows, stored by all four waves: equal.)
     if (m < p.M) {
       float* dst = p.part_o + (slot0 + c32) * kHeadDim;
 #pragma unroll
@@ -589,7 +590,7 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
       }
     }
   }
-  if (KPR == 1 && threadIdx.x == 0) {
+  if (KPR == 1 && p.part_f16 && threadIdx.x == 0) {
     unsigned long long* st = reinterpret_cast<unsigned long long*>(reinterpret_cast<unsigned char*>(p.part_o) +
                                                                    static_cast<size_t>(p.S) * p.Hq * p.T * kD * 2) +
                              ((blockIdx.z * p.Hkv + g) * p.S + split) * 8;
