@@ -150,13 +150,14 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   }
   // Automatic split count of a short prefix in the bf16 kernels: 256 keys per split, 128 while that keeps the count at 16 or
   // below (measured at 1K - 8K tokens: more splits shorten the prefix kernel by less than they add to the merge, fewer leave most
-  // compute units idle), in the row-split kernel 64 while it also leaves a quarter of the compute units without a workgroup of 128
+  // compute units idle), in the row-split kernel 64 while it also leaves a third of the compute units without a workgroup of 128
   // rows.  Attention call,
   // us, with 128 / 64: head_dim 128, 32 heads in 8 groups, 60 nodes 256 keys 9.9 / 9.1, 512 10.25 / 9.8, 1024 (all compute units)
   // 10.8 / 11.5, 20 nodes 512 keys 9.25 / 8.4, 128 nodes 600 keys (more workgroups than compute units) 12.4 / 14.8; head_dim 64, 12
-  // heads, 60 nodes 512 keys 7.7 / 7.2, 1024 7.85 / 7.7, 32 heads in 8 groups 1000 keys (all compute units) 10.05 / 10.45.
+  // heads, 60 nodes 512 keys 7.7 / 7.2, 1024 (192 workgroups) 7.85 / 7.7 in a graph but 8.42 / 8.5 launched one by one, 32 heads in 8
+  // groups 1000 keys (all compute units) 10.05 / 10.45.
   auto at_most_16 = [&](int keys) { return (p->L + keys - 1) / keys < 16 ? static_cast<int>((p->L + keys - 1) / keys) : 16; };
-  const bool by_64 = p->use_mfma == 2 && static_cast<int64_t>(at_most_16(64)) * p->Hkv * ((p->M + 127) / 128) * 4 <= device_cu_count() * 3;
+  const bool by_64 = p->use_mfma == 2 && static_cast<int64_t>(at_most_16(64)) * p->Hkv * ((p->M + 127) / 128) * 3 <= device_cu_count() * 2;
   const int by_256 = static_cast<int>((p->L + 255) / 256), by_less = at_most_16(by_64 ? 64 : 128);
   const int by_len = by_256 > by_less ? by_256 : by_less;
   // At most 32 rows: one wave of a row-split workgroup has rows, so its tiles come one after the other, but all four waves stream
