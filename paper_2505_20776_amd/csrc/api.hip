@@ -103,10 +103,14 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
 
   // Which prefix kernel runs.  The matrix-core kernels take bf16, d = 128, at least one
   // full 32-key tile and, when scores are wanted, chunk sizes that are whole tiles.
-  // The row-split kernel: a workgroup owns 128 or 256 rows, so each K/V byte enters one compute unit only
-  // (measured faster from 33 rows on, also when most of a workgroup's rows are padding).  Up to 32 query rows
-  // per KV head it shares with the key-split kernel (the four waves of a workgroup share the rows and split
-  // the keys): the rule is below, where the split count is known.
+  // Up to 32 query rows per KV head: the key-split kernel (the four waves of a
+  // workgroup share the rows and split the keys).  More rows: the row-split kernel
+  // (a workgroup owns 128 or 256 rows, so each K/V byte enters one compute unit only;
+  // measured faster from 33 rows on, also when most of a workgroup's rows are padding).
+  // (With at most 32 rows the row-split kernel streams long prefixes faster, 8 nodes of 32 heads in 8 groups 16K keys 21.2 -> 19.9
+  // us per attention call, 100000 87 -> 73, but rounds more: a reference is the largest logit of the first tile that it serves,
+  // whose probability is then exactly one, and each of the key-split kernel's four waves has a reference of its own.  Distance of
+  // the output from 64 bits 1.15e-3 -> 1.43e-3 at 512 keys in splits of 128 / 64, 1.55e-3 -> 1.64e-3 at 16K.)
   // Their address arithmetic inside a tile and inside Q is 32-bit, hence the stride limits.
   const bool mfma_common = p->in_dtype == SPECEXT_BF16 && (!p->want_scores || p->B % 32 == 0) &&
                            !(d->flags & SPECEXT_FLAG_VALU_PREFIX) && p->kp_sl <= (1 << 24) &&
@@ -125,13 +129,13 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   } else if (!mfma_ok) {
     p->use_mfma = f32_ok ? 3 : 0;
     p->rows_per_group = !f32_ok || p->M > 32 ? 64 : p->M > 16 ? 32 : 16;
-  } else if (p->M <= 32 && d->num_splits != 0) {
+  } else if (p->M <= 32) {
     p->use_mfma = 1;
     p->rows_per_group = 32;
   } else {
     p->use_mfma = 2;
     p->rows_per_group = p->M > 128 ? 256 : 128;
-    p->part_f16 = p->M > 32;
+    p->part_f16 = 1;
   }
   p->score_gran = p->use_mfma == 3 ? (p->B % 16 == 0 ? 16 : p->B % 8 == 0 ? 8 : 4) : p->use_mfma ? 32 : p->B;
   p->n_sub = p->want_scores ? (p->L + p->score_gran - 1) / p->score_gran : 0;
@@ -160,21 +164,6 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   const bool by_64 = p->use_mfma == 2 && static_cast<int64_t>(at_most_16(64)) * p->Hkv * ((p->M + 127) / 128) * 3 <= device_cu_count() * 2;
   const int by_256 = static_cast<int>((p->L + 255) / 256), by_less = at_most_16(by_64 ? 64 : 128);
   const int by_len = by_256 > by_less ? by_256 : by_less;
-  // At most 32 rows: one wave of a row-split workgroup has rows, so its tiles come one after the other, but all four waves stream
-  // them; in the key-split kernel all four have tiles of their own.  The former is faster while it has two tiles (short prefixes)
-  // and where the stream decides (at least eight KV heads whose workgroups fill the device; with fewer heads the many splits
-  // of each do not pay).  Attention call, us, key-split / row-split, 8 nodes of 32 heads in 8 groups unless noted: 256 keys 8.7 / 7.8,
-  // 512 8.75 / 8.1, 1024 9.3 / 8.9, 2K 10.0 / 10.0, 4K 12.1 / 12.3, 8K (one node) 14.7 / 13.5, 16K 20.4 / 19.1, 32K 34.4 / 30.6, 100000
-  // 81.3 / 72.2; 32 KV heads 4000 keys 18.8 / 17.3; four KV heads 1024 keys 8.4 / 8.9, 9000 13.8 / 15.6, two 60000 30.8 / 34.5.
-  // A requested split count is always cut for the key-split kernel, whose splits are whole multiples of 128 keys.
-  if (p->use_mfma == 2 && p->M <= 32 && p->d == 128) {
-    const int at_once = device_cu_count() / p->Hkv;
-    const bool filled = p->Hkv >= 8 && static_cast<int64_t>(at_once < by_len ? at_once : by_len) * p->Hkv * 16 >= device_cu_count() * 15;
-    if (!filled && !(by_64 && p->L <= (p->Hkv >= 8 ? 1024 : 768))) {
-      p->use_mfma = 1;
-      p->rows_per_group = 32;
-    }
-  }
   // With so few splits that workgroups of 128 rows still fit the device at once, the row-split kernel takes those: twice as
   // many compute units, and a wave has its SIMD to itself.  Every K/V byte then enters two compute units, of one XCD where
   // the KV head is the fastest grid index.  Prefix launch with 256 / with 128 rows, 60 nodes, 32 heads in 8 groups, us:

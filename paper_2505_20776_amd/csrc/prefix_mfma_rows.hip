@@ -1,8 +1,7 @@
 // Prefix pass of Hybrid Tree Attention (SpecExtend Sec. 3.1) on the gfx950
 // matrix cores, row-split form: bf16 K/V streamed ONCE from HBM into ONE compute
 // unit each, fp32 accumulation.  Used when a KV head has more than 32 query rows
-// (tree nodes x heads in the GQA group); smaller problems take it, with fp32 partials, for short
-// prefixes and where the K/V stream decides, else the key-split kernel (the rule is at the dispatch).
+// (tree nodes x heads in the GQA group); smaller problems take the key-split kernel.
 //
 // Why this shape.  Measured on MI355X: the memory system delivers the same 5.5 - 6 TB/s
 // whether the bytes come from L2, the Infinity Cache or HBM, so every byte that passes
@@ -75,8 +74,7 @@ static_assert(kDeepStages >= 2 && lds_bytes(8, kDeepStages) <= 160 * 1024, "ring
 // even and of the odd keys of the rows come from the first and the second half of the
 // K fragments against the same four query fragments, and the even / odd probabilities
 // meet V^T's first / second pair of 32-column blocks in the same two output blocks.
-// PART_F32: the partial outputs in fp32 (head_dim 64, and at most 32 rows; a choice at run time takes 0.2 - 0.3 us of a launch).
-template <int WAVES, bool SCORES, int KPR, int STAGES, bool PART_F32>
+template <int WAVES, bool SCORES, int KPR, int STAGES>
 __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, uint64_t v_at, uint64_t q_at, int64_t kp_sh, int L, int keys_per_split, int M, int G,
                                                             int kp_sl, int head_fastest, AttnParams p) {
   p.kp = in_global<const void>(k_at);
@@ -501,10 +499,10 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
 #endif
   const float l_tot = halves_sum(run_sum);
   const int64_t slot0 = static_cast<int64_t>(split) * p.Hq * p.T + g * p.M + row0;     // slot of the wave's first row
-  if constexpr (PART_F32) {
-    // ---- head_dim 64, and at most 32 rows: the partial goes out as it is, (reference, row sum) and
-    // the unnormalised O in fp32 (what the merge kernel reads then); a lane owns one row and holds
-    // four consecutive columns per register quad.  (Through LDS as whole rows, stored by all four waves: equal.)
+  if constexpr (KPR == 2) {
+    // ---- head_dim 64: the partial goes out as it is, (reference, row sum) and the unnormalised
+    // O in fp32 (what the merge kernel reads for this head size); a lane owns one row and
+    // holds four consecutive columns per register quad
     if (m < p.M) {
       float* dst = p.part_o + (slot0 + c32) * kHeadDim;
 #pragma unroll
@@ -591,7 +589,7 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
       }
     }
   }
-  if (KPR == 1 && !PART_F32 && threadIdx.x == 0) {
+  if (KPR == 1 && threadIdx.x == 0) {
     unsigned long long* st = reinterpret_cast<unsigned long long*>(reinterpret_cast<unsigned char*>(p.part_o) +
                                                                    static_cast<size_t>(p.S) * p.Hq * p.T * kD * 2) +
                              ((blockIdx.z * p.Hkv + g) * p.S + split) * 8;
@@ -607,9 +605,9 @@ __global__ __launch_bounds__(WAVES * 64) void prefix_rows_kernel(uint64_t k_at, 
   }
 }
 
-template <int WAVES, bool SCORES, int KPR, int STAGES = kDeepStages, bool PART_F32 = KPR == 2>
+template <int WAVES, bool SCORES, int KPR, int STAGES = kDeepStages>
 hipError_t launch_rows(const AttnParams& p, hipStream_t stream) {
-  auto kernel = prefix_rows_kernel<WAVES, SCORES, KPR, STAGES, PART_F32>;
+  auto kernel = prefix_rows_kernel<WAVES, SCORES, KPR, STAGES>;
   constexpr int kLdsBytes = lds_bytes(WAVES, STAGES);
   if (kLdsBytes > 64 * 1024) {
     // more than the default 64 KB of dynamic LDS: raise the cap once per device
@@ -638,7 +636,6 @@ hipError_t launch_prefix_mfma_rows(const AttnParams& p, hipStream_t stream) {
     if (big) return p.want_scores ? launch_rows<8, true, 2>(p, stream) : launch_rows<8, false, 2>(p, stream);
     return p.want_scores ? launch_rows<4, true, 2>(p, stream) : launch_rows<4, false, 2>(p, stream);
   }
-  if (!p.part_f16) return p.want_scores ? launch_rows<4, true, 1, kDeepStages, true>(p, stream) : launch_rows<4, false, 1, kDeepStages, true>(p, stream);
   const int split_tiles = (p.keys_per_split + kTile - 1) / kTile;
   if (big) {
     if (split_tiles <= kShortSplitTiles)

@@ -90,6 +90,18 @@ def test_the_reported_split_count_gives_the_automatic_problem(sx, dtype, d, hq, 
         assert sx.num_splits(asked) == sx.num_splits(auto) and sx.workspace_bytes(asked) == sx.workspace_bytes(auto)
 
 
+@pytest.mark.parametrize("d,hq,hkv,T", [
+    (128, 32, 8, 8), (128, 32, 8, 1), (128, 4, 1, 8), (128, 8, 4, 16), (128, 32, 32, 1), (128, 32, 32, 20), (128, 32, 8, 9), (128, 32, 8, 20),
+    (128, 32, 8, 60), (128, 8, 2, 128), (64, 12, 12, 60), (64, 32, 8, 8), (64, 8, 2, 128)])
+def test_the_reported_split_count_holds_at_every_length(sx, d, hq, hkv, T):
+    """bf16, few rows and many, chunks of a tile to chunks that are longer than a split."""
+    for L in [*range(32, 1200, 8), *range(1200, 8300, 97), 10000, 16384, 50000, 100000]:
+        for B in (0, 32, 96, 1024):
+            kw = dict(dtype=sx.SPECEXT_BF16, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=L, n_tree=T, chunk_size=B, want_scores=B > 0)
+            splits = sx.num_splits(sx.make_desc(**kw))
+            assert sx.num_splits(sx.make_desc(num_splits=splits, **kw)) == splits, (L, B)
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("struct_size", 4, -1), ("n_q_heads", 0, -1), ("n_kv_heads", 5, -1), ("prefix_len", -1, -1),
     ("n_tree", 0, -1), ("chunk_size", 0, -1), ("num_splits", -2, -1), ("softmax_scale", -1.0, -1),
