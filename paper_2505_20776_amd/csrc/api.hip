@@ -154,14 +154,18 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   }
   // Automatic split count of a short prefix in the bf16 kernels: 256 keys per split, 128 while that keeps the count at 16 or
   // below (measured at 1K - 8K tokens: more splits shorten the prefix kernel by less than they add to the merge, fewer leave most
-  // compute units idle), in the row-split kernel 64 while it also leaves a third of the compute units without a workgroup of 128
-  // rows.  Attention call,
-  // us, with 128 / 64: head_dim 128, 32 heads in 8 groups, 60 nodes 256 keys 9.9 / 9.1, 512 10.25 / 9.8, 1024 (all compute units)
-  // 10.8 / 11.5, 20 nodes 512 keys 9.25 / 8.4, 128 nodes 600 keys (more workgroups than compute units) 12.4 / 14.8; head_dim 64, 12
-  // heads, 60 nodes 512 keys 7.7 / 7.2, 1024 (192 workgroups) 7.85 / 7.7 in a graph but 8.42 / 8.5 launched one by one, 32 heads in 8
-  // groups 1000 keys (all compute units) 10.05 / 10.45.
+  // compute units idle), in the row-split kernel 64 while that needs workgroups of 128 rows for two thirds of the compute units at
+  // most, or for half of them where 64-wide heads have more than 128 rows: there it is never slower.  Attention call in a graph,
+  // us, with 128 / 64, workgroups with 64 in brackets, 32 heads in 8 groups unless noted:
+  //   head_dim 128, 60 nodes 300 keys (80) 10.3 / 9.7, 512 (128) 10.5 / 9.8, 640 (160) 10.4 / 10.3, 768 (192) 10.5 / 10.2, 1024 (256)
+  //     10.8 / 11.5; 20 nodes 1024 keys (128) 9.5 / 9.0; 32 KV heads, 40 nodes 320 keys (160) 10.1 / 9.1
+  //   64, 60 nodes 512 keys (128) 8.9 / 8.8, 576 (144) 9.0 / 9.2, 640 (160) 9.1 / 9.3, 1000 (256) 10.0 / 10.4; 128 nodes 320 keys (160)
+  //     10.0 / 10.1; 20 nodes, one group of rows, 896 keys (112) 8.1 / 7.9; 12 heads, 60 nodes 512 keys (96) 8.2 / 7.6, 832 (156) 8.35 /
+  //     8.35, 1024 (192) 8.4 / 8.35; 32 KV heads, 60 nodes 320 keys (160) 8.5 / 8.1
   auto at_most_16 = [&](int keys) { return (p->L + keys - 1) / keys < 16 ? static_cast<int>((p->L + keys - 1) / keys) : 16; };
-  const bool by_64 = p->use_mfma == 2 && static_cast<int64_t>(at_most_16(64)) * p->Hkv * ((p->M + 127) / 128) * 3 <= device_cu_count() * 2;
+  const int groups_128 = (p->M + 127) / 128;
+  const int64_t workgroups_64 = static_cast<int64_t>(at_most_16(64)) * p->Hkv * groups_128;
+  const bool by_64 = p->use_mfma == 2 && (p->d == 64 && groups_128 > 1 ? workgroups_64 * 2 <= device_cu_count() : workgroups_64 * 3 <= device_cu_count() * 2);
   const int by_256 = static_cast<int>((p->L + 255) / 256), by_less = at_most_16(by_64 ? 64 : 128);
   const int by_len = by_256 > by_less ? by_256 : by_less;
   // With so few splits that workgroups of 128 rows still fit the device at once, the row-split kernel takes those: twice as

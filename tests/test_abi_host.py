@@ -77,6 +77,16 @@ def test_automatic_splits_with_fp32_probabilities(sx, dtype, L, B, splits):
     assert sx.num_splits(d) == splits
 
 
+@pytest.mark.parametrize("d,hq,hkv,T,L,splits", [
+    (128, 32, 8, 60, 640, 10), (128, 32, 8, 60, 704, 6), (128, 32, 8, 20, 1024, 16), (128, 32, 32, 40, 320, 5), (128, 32, 32, 40, 384, 3),
+    (64, 32, 8, 60, 512, 8), (64, 32, 8, 60, 576, 5), (64, 32, 8, 60, 640, 5), (64, 32, 8, 128, 256, 4), (64, 32, 8, 128, 320, 3),
+    (64, 32, 8, 20, 1024, 16), (64, 12, 12, 60, 832, 13), (64, 12, 12, 60, 1024, 8), (64, 32, 32, 60, 320, 5)])
+def test_automatic_splits_of_short_prefixes(sx, d, hq, hkv, T, L, splits):
+    """bf16, 256 compute units: splits of 64 keys up to 170 workgroups of 128 rows, 128 where 64-wide heads have more than 128 rows."""
+    kw = dict(dtype=sx.SPECEXT_BF16, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefix_len=L, n_tree=T)
+    assert sx.num_splits(sx.make_desc(**kw)) == splits
+
+
 @pytest.mark.parametrize("dtype,d,hq,hkv,T,L,B", [
     ("bf16", 128, 32, 8, 60, 4109, 16), ("f32", 128, 32, 8, 60, 1100, 32), ("f32", 128, 32, 8, 60, 3333, 64),
     ("f32", 64, 4, 1, 8, 512, 32), ("f32", 64, 4, 1, 8, 300, 8), ("bf16", 64, 8, 2, 20, 1000, 12), ("bf16", 128, 32, 8, 8, 8155, 32),
