@@ -120,7 +120,11 @@ const char* specext_strerror(int status);
  * descriptor (split partials, final log-sum-exp, chunk partial sums when
  * want_scores, and the status word).  Returns 0 for an invalid descriptor.  The size
  * follows from the kernels that this build of the library chooses (8 bytes per query row
- * and score block, for one): ask for it, rather than keep one from another build.
+ * and score block, for one): ask for it, rather than keep one from another build.  Ask per
+ * descriptor: a shorter prefix may be cut into more splits.  With bf16 inputs, an automatic
+ * split count and chunks of whole 32 keys (or no scores) the size covers that up to prefixes of
+ * 1024 keys, so that one workspace serves shorter prefixes and smaller trees as well as splits
+ * of 128 keys would let it.
  * Host-only; needs a visible GPU only when num_splits == 0 (to read the
  * compute-unit count).
  */
@@ -191,7 +195,7 @@ int specext_verify_attn(const specext_desc* desc, const void* q, const void* k_p
  *   status_out  device int32 [1] that receives the status word (0, or 1 for a
  *               malformed parent index); may be NULL
  *
- * Limits: a descriptor whose specext_workspace_bytes exceeds the scratch array is
+ * Limits: a descriptor whose call needs more than the scratch array is
  * rejected with SPECEXT_ERR_WORKSPACE_TOO_SMALL before anything is launched (unless, in the
  * kernel with fp32 probabilities, a requested num_splits fits when it is cut into fewer
  * splits at 64 fp32 or 128 bf16 keys: then it is cut so; the

@@ -55,8 +55,9 @@ int64_t gcd64(int64_t a, int64_t b) {
   return a;
 }
 
-// Validate the descriptor and resolve every default.  Pointers are not looked at here.
-int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
+// Validate the descriptor and resolve every default.  Pointers are not looked at here.  no_64: automatic splits of short prefixes
+// have 128 keys at the least (for the workspace size that is reported; no call is cut so).
+int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false, bool no_64 = false) {
   if (!d || d->struct_size != sizeof(specext_desc)) return SPECEXT_ERR_INVALID_ARG;
   if (d->n_q_heads <= 0 || d->n_kv_heads <= 0 || d->prefix_len < 0 || d->n_tree <= 0 || d->num_splits < 0)
     return SPECEXT_ERR_INVALID_ARG;
@@ -165,7 +166,7 @@ int resolve(const specext_desc* d, AttnParams* p, bool stage_cut = false) {
   auto at_most_16 = [&](int keys) { return (p->L + keys - 1) / keys < 16 ? static_cast<int>((p->L + keys - 1) / keys) : 16; };
   const int groups_128 = (p->M + 127) / 128;
   const int64_t workgroups_64 = static_cast<int64_t>(at_most_16(64)) * p->Hkv * groups_128;
-  const bool by_64 = p->use_mfma == 2 && (p->d == 64 && groups_128 > 1 ? workgroups_64 * 2 <= device_cu_count() : workgroups_64 * 3 <= device_cu_count() * 2);
+  const bool by_64 = !no_64 && p->use_mfma == 2 && (p->d == 64 && groups_128 > 1 ? workgroups_64 * 2 <= device_cu_count() : workgroups_64 * 3 <= device_cu_count() * 2);
   const int by_256 = static_cast<int>((p->L + 255) / 256), by_less = at_most_16(by_64 ? 64 : 128);
   const int by_len = by_256 > by_less ? by_256 : by_less;
   // With so few splits that workgroups of 128 rows still fit the device at once, the row-split kernel takes those: twice as
@@ -239,6 +240,28 @@ WorkspaceLayout layout_of(const AttnParams& p) {
   if (p.want_scores) off += align_up(rows * static_cast<size_t>(p.n_sub) * 2 * sizeof(float));
   w.total = off;
   return w;
+}
+
+// What specext_workspace_bytes reports.  A call needs layout_of(p).total.  Automatic splits of a short prefix may have 64 keys
+// where slightly longer prefixes and larger trees have splits of 128 and need less (60 nodes of 32 heads in 8 groups 10.1 MB at 640
+// keys, 6.1 at 648), so that a workspace for the longest prefix would not hold the shorter ones.  Splits of 64 are at most twice
+// those of 128 and fit two thirds of the compute units in workgroups of 128 rows: with twice the need of splits of 128, up to what that many
+// workgroups leave behind (11.5 MB with 256 compute units), every call is served that splits of 128 alone would allow.
+size_t reported_bytes(const specext_desc* d, const AttnParams& p) {
+  const size_t need = layout_of(p).total;
+  if ((p.use_mfma != 1 && p.use_mfma != 2) || p.L == 0) return need;
+  specext_desc automatic = *d;
+  automatic.num_splits = 0;
+  AttnParams a;
+  // (the automatic count asked for by number is the same problem)
+  if (d->num_splits != 0 && (resolve(&automatic, &a) != SPECEXT_OK || a.S != p.S)) return need;
+  if (resolve(&automatic, &a, false, true) != SPECEXT_OK) return need;
+  // per row and split: partial output and (max, sum), two score blocks of 32 keys; per row: log-sum-exp
+  const size_t rows = static_cast<size_t>(device_cu_count()) * 2 / 3 * 128;
+  const size_t most = kHeaderBytes + rows * (128 * 4 + 8 + 2 * 8 + 4) + 4 * kAlign;
+  const size_t twice = 2 * layout_of(a).total - kHeaderBytes;
+  const size_t wanted = twice < most ? twice : most;
+  return align_up(wanted > need ? wanted : need);
 }
 
 void bind_workspace(AttnParams* p, const WorkspaceLayout& w, void* workspace) {
@@ -371,7 +394,7 @@ const char* specext_strerror(int status) {
 size_t specext_workspace_bytes(const specext_desc* desc) {
   AttnParams p;
   if (resolve(desc, &p) != SPECEXT_OK) return 0;
-  return layout_of(p).total;
+  return reported_bytes(desc, p);
 }
 
 int specext_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {

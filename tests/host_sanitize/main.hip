@@ -115,6 +115,32 @@ int main() {
     EXPECT(specext_verify_attn_static(&x, ok, ok, ok, ok, ok, iok, ok, fok, iok, nullptr) == SPECEXT_ERR_WORKSPACE_TOO_SMALL);
   }
 
+  // a workspace for the longest prefix and the largest tree serves all shorter prefixes and smaller trees
+  {
+    const struct { int hq, hkv, dim; } shapes[] = {{32, 8, 128}, {32, 8, 64}, {12, 12, 64}, {8, 2, 128}, {4, 1, 128}, {16, 16, 64}};
+    const int prefixes[] = {40, 64, 65, 200, 256, 300, 512, 600, 640, 648, 704, 832, 896, 904, 1000, 1024, 1032, 1280, 1536, 1920, 2048};
+    const int trees[] = {1, 8, 9, 20, 32, 33, 50, 60, 64, 65, 96, 128};
+    for (const auto& s : shapes)
+      for (int scores = 0; scores < 2; ++scores) {
+        specext_desc x = good_desc();
+        x.n_q_heads = s.hq, x.n_kv_heads = s.hkv, x.head_dim = s.dim, x.want_scores = scores, x.num_splits = 0;
+        int refused = 0;
+        for (int L : prefixes)
+          for (int T : trees) {
+            x.prefix_len = L, x.n_tree = T;
+            const size_t bytes = specext_workspace_bytes(&x);
+            for (int shorter : prefixes)
+              for (int smaller : trees)
+                if (shorter <= L && smaller <= T) {
+                  specext_desc y = x;
+                  y.prefix_len = shorter, y.n_tree = smaller;
+                  refused += specext_verify_attn(&y, ok, ok, ok, ok, ok, iok, ok, nullptr, ok, bytes, nullptr) != 0;
+                }
+          }
+        EXPECT(refused == 0);
+      }
+  }
+
   // pointers and sizes of verify_attn
   EXPECT(specext_verify_attn(&d, nullptr, ok, ok, ok, ok, iok, ok, fok, ok, ws, nullptr) == -1);
   EXPECT(specext_verify_attn(&d, ok, nullptr, ok, ok, ok, iok, ok, fok, ok, ws, nullptr) == -1);
