@@ -327,8 +327,8 @@ int specext_commit_tree_kv(const void* k_tree, const void* v_tree, void* k_cache
  * path[*n_accept - 1], or row 0 when nothing was accepted.
  *
  *   desc, workspace   as for specext_chunk_scores
- *   path, n_accept    as written by specext_accept_greedy (device); all n_tree entries
- *                     of path may be read
+ *   path, n_accept    as written by specext_accept_greedy (device): path holds
+ *                     min(*n_accept, n_tree) entries at least
  *   scores            fp32 [C]
  */
 int specext_chunk_scores_accepted(const specext_desc* desc, const void* workspace, size_t workspace_bytes,
@@ -345,8 +345,8 @@ int specext_chunk_scores_accepted(const specext_desc* desc, const void* workspac
  *   desc, workspace   as for specext_chunk_scores
  *   score_row         the tree row when path is NULL (0 <= score_row < n_tree); else the
  *                     row is path[*n_accept - 1] read on the device (row 0 when nothing
- *                     was accepted), path and n_accept as written by specext_accept_greedy;
- *                     all n_tree entries of path may be read
+ *                     was accepted), path and n_accept as written by specext_accept_greedy:
+ *                     path holds min(*n_accept, n_tree) entries at least
  *   k, idx_out, n_out as for specext_select_chunks
  *   scores            fp32 [C] that also receives the scores, or NULL (allowed up to
  *                     1024 chunks; beyond that SPECEXT_ERR_INVALID_ARG)

@@ -4,6 +4,7 @@
 //   select_*_kernel      - SelectChunks: top-k by ranking (short inputs) or radix select, ascending output
 //   gather_*_kernel      - UpdateDraftCache: copy the chosen chunks verbatim
 #include "common.h"
+#include "score_row.h"
 
 namespace specext {
 namespace {
@@ -25,8 +26,7 @@ namespace {
 // trip to memory if all of a thread's loads are in flight together and enough compute units ask.  Hence
 // one wavefront and 16 chunks per workgroup; 64 chunks per workgroup with a head's loads one after the
 // other took 5.5 us for 512 chunks of one block and 7.9 us for 512 of two (32 heads in 8 groups), so
-// 2.5 and 2.9 us; with the accepted row read in one trip, the inputs among the first arguments and no
-// divisions by the group size 2.35 and 2.7.
+// 2.9 and 3.65 us; with the inputs among the first arguments and no divisions by the group size 2.7 and 3.2.
 constexpr int kHeadsAtOnce = 8;                // heads of one thread whose loads are in flight together
 
 // NSUB score blocks per lane and step, QUADS quads per chunk: the smallest pair whose product covers a chunk's blocks
@@ -61,20 +61,6 @@ struct ScoreInputs {
   const float *part, *lse2;      // AttnParams::chunk_part, lse2
   int M, G, Hq, n_sub, per_chunk;      // per_chunk: score blocks of a chunk
 };
-
-// The tree row to score: given, or the acceptance walk's last accepted node read on the device.  The count and all of the path
-// (n_tree entries, whatever the count says) are requested together: one trip to memory instead of two in front of the pairs'.
-__device__ __forceinline__ int scored_row(uint64_t path_at, uint64_t count_at, int T, int first_row) {
-  if (!path_at) return first_row;
-  const int* path = in_global<const int>(path_at);
-  const int lane = threadIdx.x & 63;
-  int count = *in_global<const int>(count_at), low = path[min(lane, T - 1)], high = path[min(lane + 64, T - 1)];
-  asm volatile("" : "+s"(count), "+v"(low), "+v"(high));
-  const int last = min(count, T) - 1;
-  if (last < 0) return 0;
-  const int node = last < 64 ? __builtin_amdgcn_readlane(low, last) : __builtin_amdgcn_readlane(high, last - 64);
-  return (node >= 0 && node < T) ? node : 0;
-}
 
 // value of quad lane I in every lane of the quad
 template <int I>
@@ -130,7 +116,7 @@ template <class Shape>
 __global__ __launch_bounds__(Shape::kThreads) void chunk_scores_kernel(SPECEXT_SCORE_PARAMS, int C, int B, int L, int first_row,
                                                                        float* scores) {
   const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
-  const int t = scored_row(path_at, count_at, T, first_row + blockIdx.y);
+  const int t = scored_row(in_global<const int>(path_at), in_global<const int>(count_at), T, first_row + blockIdx.y);
   const int c = blockIdx.x * Shape::kChunks + threadIdx.x / Shape::kLanes;
   const int lane = threadIdx.x % Shape::kLanes;
   const float acc = chunk_partial<Shape>(in, t, c, lane);
@@ -421,7 +407,7 @@ __global__ __launch_bounds__(kRankMax) void score_select_kernel(SPECEXT_SCORE_PA
   __shared__ RadixLds<1> radix;
   __shared__ float partial[kRankMax][4];
   const ScoreInputs in = {in_global<const float>(part_at), in_global<const float>(lse2_at), M, G, Hq, n_sub, per_chunk};
-  const int t = scored_row(path_at, count_at, T, score_row);
+  const int t = scored_row(in_global<const int>(path_at), in_global<const int>(count_at), T, score_row);
   const int lane = threadIdx.x % Shape::kLanes;
   for (int c = threadIdx.x / Shape::kLanes; c < C; c += blockDim.x / Shape::kLanes) {
     const float acc = chunk_partial<Shape>(in, t, c, lane);

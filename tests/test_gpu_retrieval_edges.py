@@ -143,7 +143,6 @@ def _launches(call):
     return n.value
 
 
-# both sides of the line between one launch and two: 128 chunks, 1600 pair groups
 def test_accepted_row_at_the_ends_of_the_path():
     """The row that a walk of 128 nodes ends at: counts around a wavefront's 64 entries, at and beyond both ends, and entries that
     are no node (row 0)."""
@@ -172,6 +171,7 @@ def test_accepted_row_at_the_ends_of_the_path():
     buf.check_guards()
 
 
+# both sides of the line between one launch and two: 128 chunks, 1600 pair groups
 @pytest.mark.parametrize("Hkv,L,B,with_scores,launches", [
     (8, 4096, 32, True, 1), (8, 4097, 32, True, 2), (8, 5120, 64, True, 1), (16, 2560, 64, True, 1), (32, 1600, 32, True, 1),
     (8, 6400, 64, True, 1), (8, 6401, 64, True, 2), (8, 12000, 128, True, 2), (8, 12000, 128, False, 1), (2, 32768, 32, False, 1)])
