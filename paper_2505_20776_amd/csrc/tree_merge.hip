@@ -523,17 +523,20 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
 #pragma unroll
   for (int u = kFirst; u < PER; ++u) raw[u] = load_words<PW, true>(po + min(s_lo + u, s_last) * split_words);
 
-  // A deeper chain (the same for all four waves, which serve the same rows): positions 8 to 15 the same way.  Every node's fourth
-  // ancestor goes to LDS beside that, so that behind them a wave steps from one of its nodes to the next with one read, and the
-  // rows are requested a batch ahead, without a branch.  Chains, us per launch (32 heads in 8 groups, bf16): with every wave walking
-  // the whole chain and a batch's rows requested when the one before was done 16 nodes 4.7, 60 nodes at 2K 10.1, 128 at 4K 24.3;
-  // so 4.2, 8.3 and 18.7, with the workgroups' turn above 7.4 and 14.9 (flat trees 3.8, 4.7 and 6.8 either way).
-  constexpr int kDeep = RW == 8 ? 2 : 4;         // (more would cost registers that a second workgroup needs)
+  // A deeper chain (the same for all four waves, which serve the same rows): every node's fourth ancestor goes to LDS beside the next
+  // four steps of the walk, so that from there a wave gets from one of its nodes to the next with one read, and the rows are requested
+  // a batch ahead, without a branch.  Batches are as small as still hides a trip, because every tree pays for their registers in
+  // waves per SIMD: 7 with fp16 partials of up to eight splits and 5 with fp32 rows of 128 and up to four, where batches of twice the size
+  // behind a second eight positions left 4 and 3 (bf16 64 heads in 8 groups, 128 flat nodes 8.8 us per launch instead of 9.8, fp32 32
+  // heads 6.9 instead of 7.4) and were no faster (chains of 60 and 128 bf16 nodes 7.3 and 14.6, fp32 128 17.6).  Chains,
+  // us per launch (32 heads in 8 groups, bf16): with every wave walking the whole chain and a batch's rows requested when the one
+  // before was done 16 nodes at 32K 4.7, 60 at 2K 10.2, 128 at 4K 24.3, fp32 128 at 2K 23.6; so 4.05, 7.0, 13.4 and 13.9, of which the
+  // workgroups' turn above is 0.0, 0.7, 4.3 and 6.5.  bf16 rows one at a time: 60 nodes 7.4, 128 14.3.
+  constexpr int kDeep = RW == 8 ? 1 : 2;
   const bool deep = __any(a >= 0);
-  bool deeper = false;
   int next = -1;
-  int anc2[kAnc], anc_a[kDeep], anc_b[kDeep];
-  RowWords k2[kAnc], v2[kAnc], k_a[kDeep], v_a[kDeep], k_b[kDeep], v_b[kDeep];
+  int anc_a[kDeep], anc_b[kDeep];
+  RowWords k_a[kDeep], v_a[kDeep], k_b[kDeep], v_b[kDeep];
   auto walk = [&](int (&nodes)[kDeep]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kDeep; ++u) {
@@ -542,29 +545,19 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
   };
   if (__builtin_expect(deep, 0)) {
-    int fourth = tid < p.T ? tid : -1;           // of node tid, found beside the walk's first steps
+    int fourth = tid < p.T ? tid : -1;           // of node tid
+    static_assert(kShareWaves == 4, "a wave's next node is the fourth ancestor");
 #pragma unroll
-    for (int u = 0; u < kAnc; ++u) {
-#pragma unroll
-      for (int w = 0; w < kShareWaves; ++w) {
-        if (w == wave) anc2[u] = a;
-        const int up = parent_of(max(a, 0));
-        if (u == 0) {
-          const int fourth_up = parent_of(max(fourth, 0));
-          if (fourth >= 0) fourth = fourth_up;
-        }
-        if (a >= 0) a = up;
-      }
+    for (int w = 0; w < kShareWaves; ++w) {
+      if (w == wave) next = a;
+      const int up = parent_of(max(a, 0)), fourth_up = parent_of(max(fourth, 0));
+      if (a >= 0) a = up;
+      if (fourth >= 0) fourth = fourth_up;
     }
-    request_rows(anc2, k2, v2);
     if (tid < p.T) fourth_lds[tid] = fourth;
     __syncthreads();
-    deeper = __any(a >= 0);
-    if (deeper) {
-      next = anc2[kAnc - 1] >= 0 ? fourth_lds[anc2[kAnc - 1]] : -1;
-      walk(anc_a);
-      request_rows(anc_a, k_a, v_a);
-    }
+    walk(anc_a);
+    request_rows(anc_a, k_a, v_a);
   }
 
 #ifdef SPECEXT_TAIL_STAMPS
@@ -641,8 +634,7 @@ __global__ __launch_bounds__(kShareWaves * 64) void tree_merge_shared_kernel(uin
     }
   };
   add_rows(anc, kraw, vraw);
-  if (__builtin_expect(deep, 0)) add_rows(anc2, k2, v2);
-  if (__builtin_expect(deeper, 0)) {
+  if (__builtin_expect(deep, 0)) {
     while (true) {
       bool more = __any(next >= 0);
       walk(anc_b);

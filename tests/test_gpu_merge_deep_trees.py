@@ -1,6 +1,6 @@
-"""GPU parity of the merge kernel on deep trees: chain lengths at the edges of its batches of ancestors (eight and eight more from
-the walk, then sixteen, or eight with wide rows, at a time by fourth ancestors), chains of different length in one tree, broken
-chains, and row counts whose workgroups are taken from their end (more than 256 of four rows)."""
+"""GPU parity of the merge kernel on deep trees: chain lengths at the edges of its batches of ancestors (eight from the walk, then
+eight, or four with wide rows, at a time by fourth ancestors), chains of different length in one tree, broken chains, and row
+counts whose workgroups are taken from their end (more than 256 of four rows)."""
 import numpy as np
 import pytest
 
@@ -25,16 +25,18 @@ def _branching(n):
 
 CASES = [
     # dtype, d, Hq, Hkv, L, parents
-    *[("f32", 64, 4, 2, 200, chain_tree(n)) for n in (8, 9, 16, 17, 20, 21, 32, 33, 48, 49)],
-    *[("f32", 128, 3, 1, 130, chain_tree(n)) for n in (16, 17, 24, 25, 128)],
+    *[("f32", 64, 4, 2, 200, chain_tree(n)) for n in (8, 9, 12, 13, 16, 17, 20, 21, 24, 25, 32, 33, 48, 49)],
+    *[("f32", 128, 3, 1, 130, chain_tree(n)) for n in (9, 12, 13, 16, 17, 20, 21, 24, 25, 128)],
     *[("bf16", 128, 8, 2, 700, chain_tree(n)) for n in (17, 31, 36, 64, 128)],
     ("bf16", 64, 5, 5, 300, chain_tree(127)),
     ("f32", 64, 2, 1, 100, _comb(128, 7)),
     ("f32", 128, 1, 1, 100, _comb(61, 3)),
     ("f32", 64, 3, 1, 100, _branching(100)),
-    ("bf16", 128, 32, 8, 150, _branching(90)),          # 720 workgroups: the last 208 of the third 256 and a short fourth
+    ("bf16", 128, 32, 8, 150, _branching(90)),          # 720 workgroups: a short third 256
     ("f32", 64, 21, 21, 64, _comb(99, 2)),              # 520 workgroups, the last of three rows
-    ("f32", 64, 16, 4, 64, chain_tree(65)),             # 260
+    ("f32", 64, 16, 4, 64, chain_tree(65)),             # 260: a short second 256, taken from its end
+    ("f32", 64, 21, 7, 64, _comb(51, 2)),               # 268, and the last, which comes first of those, of three rows
+    ("bf16", 128, 27, 9, 96, _branching(115)),     # 777: a short fourth 256, its last workgroup of one row
 ]
 
 
