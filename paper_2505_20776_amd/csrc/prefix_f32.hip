@@ -18,9 +18,9 @@
 // and the product runs at a third of the bf16 rate instead of the fp32 one's sixteenth (4109
 // keys, 60 nodes: 6250 us before, 16.0 us here).
 // The range is that of plain fp32 attention but for |V| near its end (the lagging reference lets
-// P reach 2^10: an exact running maximum takes 28.4 instead of 27.1 us at 2K and 86 instead of
-// 79.5 at 8K): infinite V, logits of minus infinity, of any finite size and scales of any size
-// are answered; scaling the queries for that costs 0.2 - 0.5 us of prologue.
+// P reach 2^10: an exact running maximum takes 25.4 instead of 24.4 us at 2K and 77.3 instead of
+// 73.0 at 8K): infinite V, logits of minus infinity, of any finite size and scales of any size
+// are answered, for which the queries are scaled in the prologue.
 //
 // Shape.  A workgroup owns 16 * NSUB * RB query rows of one KV head and one split of the keys.
 // Its waves form RB row groups x KG key groups: the key groups take the split's tiles in turns
@@ -33,8 +33,8 @@
 //           when all do it at once, so the upper half of a workgroup of eight waves begins a
 //           stage with the products that it still has to do (bf16 8K 22.6 -> 21.1 us per launch).
 // Workgroups of 128 rows with two key groups (half as many reads of every key, twice the partial
-// outputs) measured slower under the profiler: 32 against 29 us (fp32, 2K), 20.0 against 18.7 us
-// (bf16, 4109).
+// outputs) measured slower in an earlier form of this kernel, under the profiler: 32 against 29 us
+// (fp32, 2K), 20.0 against 18.7 us (bf16, 4109).
 // Matrix-core mapping, transposed so that a lane owns one query row (l & 15) in both products:
 //   S^T[key][row]   = K Q^T     A = K rows from LDS, B = Q in registers.  The contraction index
 //                               is permuted alike on both sides: a lane quarter (l >> 4) takes
@@ -278,7 +278,8 @@ __global__ __launch_bounds__(RB * KG * 64) void prefix_f32_kernel(uint64_t k_at,
   // A tile in three parts: the logits (and the V fragments: all that reads the ring), the softmax, the second product (from
   // registers).  With every wave in the same order both waves of a SIMD would be in their softmax at the same time and the
   // matrix pipe idle; so the upper half of a workgroup of eight waves (wave w + 4 shares wave w's SIMD) starts a stage with
-  // the second product of the tile before (bf16 inputs, 4109 keys: 18.7 instead of 19.9 us; fp32 inputs: equal).
+  // the second product of the tile before (bf16 inputs, 4109 keys: 16.1 instead of 17.1 us, 8K 23.3 instead of 25.2; fp32 inputs, 2K:
+  // 24.4 instead of 24.8).
   floatx4 s_acc[NSUB][kSubTiles];      // the tile's logits, then its probabilities
   float score_part[NSUB][kSubTiles];   // a lane's sums of them
   uintx4 pf[NSUB][3];                  // bf16 inputs: the probabilities as three terms
